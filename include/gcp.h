@@ -189,8 +189,9 @@ typedef struct {
     int32_t host_syncs;  /* host synchronisations of the iteration loop (gcp_purify) */
     double gemm_flops;   /* algorithmic flops of those launches (M^3 per product,
                             upper-triangle output; split products not counted) */
-    double mfma_flops;   /* flops issued to the matrix cores (whole 128x128 tiles of the
-                            padded size, times the number of split products) */
+    double mfma_flops;   /* flops issued to the matrix cores, counted as whole 128x128
+                            tiles of M rounded up to 256, times the number of split
+                            products */
 } gcp_result;
 
 /* Fills *opt with the defaults listed above (precision FP64). */
@@ -198,11 +199,12 @@ int gcp_options_default(gcp_options *opt);
 
 /* Creates a context for M x M problems on the current device and the given
  * stream and allocates its device workspace (four copies of the operand
- * encoding of an M x M matrix, O(M^2 / 64) FP64 partial sums, and 128 KB per
- * block of a product whose tiles are split along K: at most 16 MB for
+ * encoding of an M x M matrix, O(M^2 / 64) FP64 partial sums, and the partial
+ * tiles of a product whose tiles are split along K: at most 13 MB for
  * M <= GCP_STATIC_MAX_M and 64 MB above, more with the ksplit option).  M >= 1;
- * M is padded internally to a multiple of 256 with zero rows/columns (exact:
- * the padding is an invariant zero block).  *ctx is set to NULL on failure. */
+ * M is padded internally to whole tiles (a multiple of 64 or 256) with zero
+ * rows/columns (exact: the padding is an invariant zero block).  *ctx is set
+ * to NULL on failure. */
 int gcp_create(gcp_ctx **ctx, int64_t M, const gcp_options *opt, void *stream);
 
 /* Releases the context and its workspace (NULL is accepted). */

@@ -67,7 +67,8 @@ struct gcp_ctx {
   // D_0 built in place in Dp[0], no host-side history kept
   bool one_shot = false;
   int64_t M = 0, Mp = 0;
-  int nt = 0, ntiles = 0, ntpart = 0, nred = 0;
+  int ntpart = 0, nred = 0;
+  int nt_nominal = 0;   // 128-wide tiles of the size rounded up to 256
   gcp_options opt{};
   hipStream_t stream = nullptr;
   int device = 0;
@@ -86,9 +87,11 @@ struct gcp_ctx {
     int prec = GCP_FP64;
     int ntpart = 0;   // tile partial sums the reduction adds
     int fold = 1;     // fold period of the product's accumulator (K stages)
-    int nfull = 0;    // product units (tile pairs, or tiles for FP64 / FP32) computed whole ...
-    int ntail = 0;    // ... and units split along K (0: none) ...
+    int path = PATH_T64;   // product kernels (PATH_*)
+    int nfull = 0;    // product units (tiles, or tile pairs) whose kernel runs the epilogue ...
+    int ntail = 0;    // ... and units split along K ...
     int nsplit = 1;   // ... over this many blocks each
+    size_t ws = 0;    // bytes of their partial tiles
     double floor_ddbar = 0.0;   // rounding floor of |Tr(D Dbar)| (set by gcp_init)
     double enter_ddbar = 0.0;   // schedule: this encoding from |Tr(D Dbar)| <= enter_ddbar
   } pc[3];                      // the phases of the precision schedule, in order
@@ -97,6 +100,7 @@ struct gcp_ctx {
   void *split_ws = nullptr;   // partial tiles of the K-split units
   unsigned *split_cnt = nullptr;   // their arrival counters
   unsigned *counter = nullptr;
+  unsigned *rcnt = nullptr;   // tiles done per 64-row block (tile kernels)
   Scalars *sc = nullptr;    // device
   Scalars *sc_host = nullptr;  // pinned
   double *hist = nullptr;   // device, (max_iter + 1) x 9
@@ -129,7 +133,7 @@ struct gcp_ctx {
   double *btpart = nullptr; // per-tile partial sums of kappa (2 ntri + nt^2)
   double *bvec = nullptr;   // 2 Mp row scratch + kappa + 2 sums
   // verification workspace (allocated by the first gcp_verify)
-  double *vD = nullptr, *vH = nullptr, *vHD = nullptr, *vaux = nullptr;
+  double *vD = nullptr, *vH = nullptr, *vaux = nullptr;
   // profiling
   std::vector<hipEvent_t> events;
   ErrText err;
@@ -143,6 +147,12 @@ struct gcp_ctx {
       return GCP_ERR_HIP;                                                          \
     }                                                                              \
   } while (0)
+
+// Flops of one 128 x 128 tile of a product of the size rounded up to 256, the
+// unit of the mfma_flops that results report.
+static double nominal_tile_flops(const gcp_ctx *c) {
+  return 2.0 * 128.0 * 128.0 * (128.0 * c->nt_nominal);
+}
 
 static size_t plane_bytes_of(const gcp_ctx *c, int prec) {
   return (size_t)plane_count(prec) * (size_t)c->Mp * (size_t)c->Mp * (size_t)elem_size(prec);
@@ -160,11 +170,11 @@ static size_t plane_bytes(const gcp_ctx *c) {
 static void free_all(gcp_ctx *c) {
   void *ptrs[] = {c->Dp[0], c->Dp[1], c->X2p, c->dg[0], c->dg[1], c->rD[0], c->rD[1],
                   c->d2[0], c->d2[1], c->s2, c->d3, c->part, c->tpart, c->bpart, c->hvec,
-                  c->counter, c->sc, c->hist, c->D0p, c->dg0, c->rD0, c->d20};
+                  c->counter, c->rcnt, c->sc, c->hist, c->D0p, c->dg0, c->rD0, c->d20};
   for (void *p : ptrs)
     if (p) (void)hipFree(p);
   void *bptrs[] = {c->bG[0], c->bG[1], c->bX2, c->bAT, c->bCT, c->btpart, c->bvec, c->split_ws,
-                   c->split_cnt, c->vD, c->vH, c->vHD, c->vaux, c->Xc};
+                   c->split_cnt, c->vD, c->vH, c->vaux, c->Xc};
   for (void *p : bptrs)
     if (p) (void)hipFree(p);
   for (void *p : c->slots)
@@ -180,83 +190,113 @@ static void free_all(gcp_ctx *c) {
   c->events.clear();
 }
 
+// Product kernel of an encoding at size M.  FP64 and FP32 products run as 64 x
+// 64 tiles at every size.  The 16-bit pair kernel needs about 200 pairs of
+// 128 x 128 tiles to fill the chip (one block per CU); below that 64 x 64
+// tiles are faster.  Measured per product, 64 x 64 tiles / pairs, in us:
+//   FP16X3  M = 512: 22 / 56   1000: 29 / 72   2048: 53 / 137   3000: 127 / 126
+//   BF16X6  M = 512: 23 / 62   1000: 34 / 80   2048: 80 / 157   3000: 210 / 233
+// (at M = 3584 one round of 210 pairs takes little longer than the 156 of
+// M = 3000, while tiles grow with M^3.)  The ksplit option is the pair
+// kernel's.
+static int product_path(int prec, int64_t M, const gcp_options &o) {
+  if (elem_size(prec) != 2) return PATH_T64;
+  if (o.ksplit >= 2 || M > 3008) return PATH_PAIR;
+  return PATH_T64;
+}
+
+// Fold period of a product's FP32 accumulator over nk K stages, in stages:
+// sqrt(stages / accumulations per stage) unless given.
+static int fold_period(const gcp_ctx *c, int prec, double nk) {
+  if (c->opt.fold_every > 0) return c->opt.fold_every;
+  const double per_stage = prec == GCP_FP32 ? 8.0 : plane_count(prec) == 1 ? 2.0 : products(prec);
+  const int f = (int)std::lround(std::sqrt(nk / per_stage));
+  return f < 1 ? 1 : f;
+}
+
 // Launch configuration of encoding pc[k].prec: tile partial count, fold
 // period and the K-split units of the product kernel.
-static void PrecCfgInit(gcp_ctx *c, int k) {
+static void init_prec_cfg(gcp_ctx *c, int k) {
   gcp_ctx::PrecCfg &q = c->pc[k];
   const int prec = q.prec;
   const int np = plane_count(prec);
-  q.ntpart = elem_size(prec) == 2 ? 2 * pair_count(c->nt) : c->ntiles;
-  // fold period of the 16-bit kernel, in K stages: sqrt(stages / products
-  // per stage) unless given.  One- and two-plane encodings stage 64 halves
-  // per row (64 K values of one plane, or 32 of both); three planes 32 K.
-  const int nk = np <= 2 ? (int)(c->Mp * np / 64) : (int)(c->Mp / 32);
-  const double per_stage = np == 1 ? 2.0 : (double)products(prec);
-  // every pair split along K over `ks` blocks (the ksplit option), each
-  // folding its own nk / ks stages
-  const int ks = elem_size(prec) == 2 && c->opt.ksplit >= 2 ? std::min(c->opt.ksplit, nk) : 1;
-  int f = c->opt.fold_every;
-  if (f <= 0)
-    f = prec == GCP_FP32 ? fp32_fold(c->Mp)
-                         : (int)std::lround(std::sqrt((double)nk / ks / per_stage));
-  q.fold = f < 1 ? 1 : f;
-  q.nsplit = 1;
-  q.ntail = 0;
   int cus = 0;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess ||
       cus <= 0)
     cus = 256;
-  if (elem_size(prec) != 2) {
-    // FP64 / FP32: tiles are equal units of work, two resident blocks per
-    // CU.  The tiles of a last partial round (all tiles when there are fewer
-    // than one round) would leave most slots idle, so each is split along K
-    // over up to 8 blocks of at least 64 (FP64) or 256 (FP32) K values.  At
-    // most 128 split blocks in all for M <= GCP_STATIC_MAX_M (16 MB of
-    // partial tiles, within the static workspace of gcp_purify_static), 512
-    // above.  Measured per product (FP64 / FP32): M = 1024 0.19 -> 0.13 /
-    // 0.11 -> 0.09 ms, M = 4096 1.69 -> 1.40 / 0.91 -> 0.70 ms, M = 8192
-    // 9.54 -> 9.53 / 5.03 -> 4.57 ms.
-    const int slots = 2 * cus;
-    const int nkt = (int)(c->Mp / (128 / elem_size(prec)));
-    const int tail = c->ntiles % slots;
-    const int cap = c->M <= GCP_STATIC_MAX_M ? 128 : 512;
-    int S = tail > 0 ? slots / tail : 1;
-    S = std::min(S, 8);
-    S = std::min(S, nkt / (prec == GCP_FP32 ? 8 : 4));
-    if (tail > 0 && tail * S > cap) S = cap / tail;
-    q.nfull = c->ntiles;
-    if (tail > 0 && S >= 2) {
-      q.nfull = c->ntiles - tail;
-      q.ntail = tail;
-      q.nsplit = S;
+  // K stages: 128 bytes of a row, or 32 values of three planes
+  const int nk = elem_size(prec) != 2 ? (int)(c->Mp * elem_size(prec) / 128)
+                 : np <= 2            ? (int)(c->Mp * np / 64)
+                                      : (int)(c->Mp / 32);
+  q.nsplit = 1;
+  q.ntail = 0;
+  if (q.path == PATH_T64) {
+    // Tiles are equal units of work.  Those of a last partial round over the
+    // CUs (all of them when there are fewer than one round) would leave most
+    // CUs idle, so each is split along K over S blocks; the tail of a larger
+    // product over no more than fill one round.  S minimises the estimated
+    // time: a K stage takes about 0.5 us in a block that is alone on its CU
+    // (0.8 us with six products), and a split costs 2 us plus, per partial
+    // tile, 1.2 us (FP64) or 0.6 us to publish and add.  Measured per product
+    // with 1 / 3 / 6 splits: FP64 M = 256 23 / 24 / 27, M = 512 32 / 29 / 33,
+    // M = 1536 115 / 87 / 95, M = 2048 197 / 160 / 152 us; FP16X3 M = 1000
+    // 31 / 29 / 36 us.  Up to GCP_STATIC_MAX_M the partials stay within 13 MB,
+    // for the static workspace of gcp_purify_static.
+    const int nt = (int)(c->Mp / 64), ntiles = nt * (nt + 1) / 2, tail = ntiles % cus;
+    const size_t unit = 64 * 64 * (size_t)(prec == GCP_FP64 ? 8 : 4);
+    const size_t cap = c->M <= GCP_STATIC_MAX_M ? (size_t)13 << 20 : SIZE_MAX;
+    const double t_stage = np == 3 ? 0.8 : 0.5, t_part = prec == GCP_FP64 ? 1.2 : 0.6;
+    q.ntpart = ntiles;
+    q.nfull = ntiles;
+    double best = t_stage * nk;
+    for (int S = 2; tail > 0 && S <= 16; ++S) {
+      if (nk / S < 4 || (size_t)tail * S * unit > cap || (ntiles > cus && tail * S > cus)) break;
+      const double t = t_stage * nk * ((tail * S + cus - 1) / cus) / S + 2.0 + t_part * S;
+      if (t < best) {
+        best = t;
+        q.nsplit = S;
+      }
     }
+    if (q.nsplit > 1) {
+      q.nfull = ntiles - tail;
+      q.ntail = tail;
+      q.ws = (size_t)tail * q.nsplit * unit;
+    }
+    q.fold = fold_period(c, prec, q.nfull > 0 ? nk : (double)nk / q.nsplit);
     return;
   }
-  const int npairs = pair_count(c->nt);
+  // every pair split along K over `ks` blocks (the ksplit option), each
+  // folding its own nk / ks stages
+  const int ks = c->opt.ksplit >= 2 ? std::min(c->opt.ksplit, nk) : 1;
+  q.fold = fold_period(c, prec, (double)nk / ks);
+  const int npairs = pair_count((int)(c->Mp / 128));
+  q.ntpart = 2 * npairs;
   q.nfull = npairs;
   if (ks >= 2) {
     q.nfull = 0;
     q.ntail = npairs;
     q.nsplit = ks;
-    return;
+  } else {
+    // Pairs are equal units of work, one resident block per CU: the last
+    // partial round of np % CUs pairs would leave most CUs idle, so each of
+    // those pairs is split along K over up to min(CUs / tail, 4) blocks (at
+    // least 8 K stages each) and finished by the last of its splits.  At
+    // M = 8192 (32 tail pairs) 2, 4 and 8 splits measured 1.63, 1.63 and
+    // 1.62 ms per product (FP16X3), 3.16, 3.01 and 3.02 ms (BF16X6); each
+    // split re-pays the pipeline fill and writes a 128 KB partial.
+    const int tail = npairs % cus;
+    int S = tail > 0 ? cus / tail : 1;
+    if (S > nk / 8) S = nk / 8;
+    if (S > 4) S = 4;
+    if (tail > 0 && S >= 2) {
+      q.nfull = npairs - tail;
+      q.ntail = tail;
+      q.nsplit = S;
+    }
   }
-  // Pairs are equal units of work, one resident block per CU: the last
-  // partial round of np % CUs pairs would leave most CUs idle, so each of
-  // those pairs is split along K over up to min(CUs / tail, 4) blocks (at
-  // least 8 K stages each) and finished by the last of its splits.  At
-  // M = 8192 (32 tail pairs) 2, 4 and 8 splits measured 1.63, 1.63 and
-  // 1.62 ms per product (FP16X3), 3.16, 3.01 and 3.02 ms (BF16X6); each
-  // split re-pays the pipeline fill and writes a 128 KB partial.
-  const int tail = npairs % cus;
-  int S = tail > 0 ? cus / tail : 1;
-  if (S > nk / 8) S = nk / 8;
-  if (S > 4) S = 4;
-  if (tail > 0 && S >= 2) {
-    q.nfull = npairs - tail;
-    q.ntail = tail;
-    q.nsplit = S;
-  }
+  q.ws = (size_t)q.ntail * q.nsplit * 128 * 1024;   // FP32 128 x 256 per split block
 }
+
 
 extern "C" int gcp_options_default(gcp_options *opt) {
   if (!opt) return GCP_ERR_INVALID_ARG;
@@ -330,10 +370,6 @@ static int check_options(const gcp_options &o, int64_t M, ErrText &err) {
 // Sizes and launch configuration of a context for M x M problems.
 static void setup_ctx(gcp_ctx *c, int64_t M, const gcp_options &o, void *stream) {
   c->M = M;
-  c->Mp = (M + 255) / 256 * 256;   // whole pairs of 128-wide tiles
-  c->nt = (int)(c->Mp / 128);
-  c->ntiles = c->nt * (c->nt + 1) / 2;
-  c->nred = (int)((c->Mp + 63) / 64);   // k_reduce blocks (64 rows each)
   c->opt = o;
   c->stream = (hipStream_t)stream;
   (void)hipGetDevice(&c->device);
@@ -349,25 +385,35 @@ static void setup_ctx(gcp_ctx *c, int64_t M, const gcp_options &o, void *stream)
       c->pc[c->nprec].enter_ddbar = enter[q];
       ++c->nprec;
     }
-  // tile partial sums: one per upper tile (FP64/FP32 kernel) or two per
-  // tile pair (16-bit kernel, zero for the half of a pair below the diagonal)
+  // padded size: whole tiles of every phase's path
+  c->nt_nominal = (int)((M + 255) / 256 * 2);
+  int64_t edge = 64;
+  for (int k = 0; k < c->nprec; ++k) {
+    c->pc[k].path = product_path(c->pc[k].prec, M, o);
+    if (c->pc[k].path == PATH_PAIR) edge = 256;
+  }
+  c->Mp = (M + edge - 1) / edge * edge;
+  c->nred = (int)(c->Mp / 64);   // k_reduce blocks (64 rows each)
+  // tile partial sums: one per upper 64 x 64 tile, or two per tile pair (zero
+  // for the half of a pair below the diagonal)
   c->ntpart = 0;
   for (int k = 0; k < c->nprec; ++k) {
-    PrecCfgInit(c, k);
+    init_prec_cfg(c, k);
     if (c->pc[k].ntpart > c->ntpart) c->ntpart = c->pc[k].ntpart;
   }
 }
 
-// K-split units of the product launches of any phase: the most units
-// (arrival counters) and the most split blocks (partial tiles of 128 KB).
-static void split_tail(const gcp_ctx *c, int &tail, int &blocks) {
-  tail = 0;
-  blocks = 0;
+// Largest workspace of partial tiles, and most arrival counters, of any phase.
+static size_t split_ws_bytes(const gcp_ctx *c) {
+  size_t b = 0;
+  for (int k = 0; k < c->nprec; ++k) b = std::max(b, c->pc[k].ws);
+  return b;
+}
+static int split_counters(const gcp_ctx *c) {
+  int n = 0;
   for (int k = 0; k < c->nprec; ++k)
-    if (c->pc[k].ntail > 0) {
-      tail = std::max(tail, c->pc[k].ntail);
-      blocks = std::max(blocks, c->pc[k].ntail * c->pc[k].nsplit);
-    }
+    n = std::max(n, c->pc[k].ntail);
+  return n;
 }
 
 // Every device buffer of the context with its size, in a fixed order.
@@ -402,14 +448,9 @@ static void for_each_buffer(gcp_ctx *c, bool one_shot, F &&f) {
   f((void **)&c->counter, sizeof(unsigned));
   f((void **)&c->sc, sizeof(Scalars));
   f((void **)&c->hist, (size_t)(c->opt.max_iter + 1) * GCP_HIST_COLS * sizeof(double));
-  int tail, blocks;
-  split_tail(c, tail, blocks);
-  if (tail > 0) {
-    // one partial tile of 128 KB per split block (FP32 128 x 256 of the
-    // 16-bit kernel, FP64 128 x 128 of the FP64 one)
-    f(&c->split_ws, (size_t)blocks * 128 * 1024);
-    f((void **)&c->split_cnt, (size_t)tail * sizeof(unsigned));
-  }
+  f((void **)&c->rcnt, (size_t)c->nred * sizeof(unsigned));
+  if (split_ws_bytes(c) > 0) f(&c->split_ws, split_ws_bytes(c));
+  if (split_counters(c) > 0) f((void **)&c->split_cnt, (size_t)split_counters(c) * sizeof(unsigned));
   if (c->nprec > 1) f(&c->Xc, pb);
   if (!one_shot && c->opt.keep_iterates) {
     const size_t bb = Mp * Mp * (size_t)elem_size(c->opt.bwd_precision);
@@ -418,7 +459,8 @@ static void for_each_buffer(gcp_ctx *c, bool one_shot, F &&f) {
     f(&c->bX2, bb);
     f(&c->bAT, bb);
     f(&c->bCT, bb);
-    f((void **)&c->btpart, ((size_t)c->nt * (c->nt + 1) + (size_t)c->nt * c->nt) * sizeof(double));
+    const size_t nt = Mp / 64;
+    f((void **)&c->btpart, (nt * (nt + 1) + nt * nt) * sizeof(double));
     f((void **)&c->bvec, (2 * Mp + 8) * sizeof(double));
   }
 }
@@ -455,11 +497,10 @@ extern "C" int gcp_create(gcp_ctx **out, int64_t M, const gcp_options *opt, void
     g_create_error = "gcp_create: device allocation failed";
     return GCP_ERR_NO_MEMORY;
   }
-  int ntail, nblk;
-  split_tail(c, ntail, nblk);
   const size_t vec = (size_t)c->Mp * sizeof(double);
-  if ((c->split_cnt && hipMemsetAsync(c->split_cnt, 0, (size_t)ntail * sizeof(unsigned),
+  if ((c->split_cnt && hipMemsetAsync(c->split_cnt, 0, (size_t)split_counters(c) * sizeof(unsigned),
                                      c->stream) != hipSuccess) ||
+      hipMemsetAsync(c->rcnt, 0, (size_t)c->nred * sizeof(unsigned), c->stream) != hipSuccess ||
       hipMemsetAsync(c->counter, 0, sizeof(unsigned), c->stream) != hipSuccess ||
       hipMemsetAsync(c->s2, 0, vec, c->stream) != hipSuccess ||
       hipStreamSynchronize(c->stream) != hipSuccess) {
@@ -483,12 +524,14 @@ extern "C" const char *gcp_last_error(const gcp_ctx *c) {
   return c ? c->err.c_str() : g_create_error.c_str();
 }
 
-static int reduce(gcp_ctx *c, const double *part, int nslots, int mode, double *out,
-                  const double *extra, const double *tpart, int ntp, int iter,
-                  bool skip_if_stopped = false, double floor_ddbar = 0.0,
-                  bool early_stop = false, bool recheck = false) {
+// The reduction of row sums and tile sums, with the scalar step, that follows
+// the initial guess (mode 0), D^2 (mode 1) or an update (mode 2).
+static RedArgs reduction(const gcp_ctx *c, int nslots, int mode, double *out, const double *extra,
+                         const double *tpart, int ntp, int iter, bool skip_if_stopped = false,
+                         double floor_ddbar = 0.0, bool early_stop = false, bool recheck = false) {
   RedArgs a{};
-  a.part = part;
+  a.part = c->part;
+  a.rcnt = c->rcnt;
   a.nslots = nslots;
   a.mode = mode;
   a.Mp = c->Mp;
@@ -509,8 +552,7 @@ static int reduce(gcp_ctx *c, const double *part, int nslots, int mode, double *
   a.recheck = recheck ? 1 : 0;
   a.sc = c->sc;
   a.hist = c->hist;
-  HIPCHK(c, launch_reduce(a, c->stream));
-  return GCP_OK;
+  return a;
 }
 
 static int build_guess(gcp_ctx *c, const double *H, int64_t ldh, double theta, double beta,
@@ -539,16 +581,19 @@ static double rounding_floor(const gcp_ctx *c, int k) {
     default: break;
   }
   const double u_acc = std::ldexp(1.0, prec == GCP_FP64 ? -53 : -24);
-  double kappa = (double)c->Mp + 1.0;   // one accumulator over K
-  if (prec == GCP_FP32) {                // chunks of fold stages of 32 K values
-    const double f = (double)c->pc[k].fold;
-    kappa = 32.0 * f + (double)(c->Mp / 32) / f;
+  // one accumulator over K, or chunks of the default (or given) fold period;
+  // a product that is also split along K rounds less often
+  const double Mn = 128.0 * c->nt_nominal;
+  double kappa = Mn + 1.0;
+  if (prec == GCP_FP32) {                // stages of 32 K values
+    const double f = (double)fold_period(c, prec, Mn / 32.0);
+    kappa = 32.0 * f + Mn / 32.0 / f;
   } else if (elem_size(prec) == 2) {
     const int np = plane_count(prec);
-    const double stages = np <= 2 ? (double)c->Mp * np / 64.0 : (double)c->Mp / 32.0;
+    const double stages = np <= 2 ? Mn * np / 64.0 : Mn / 32.0;
     const double per_stage = np == 1 ? 2.0 : (double)products(prec);
-    const double f = (double)c->pc[k].fold;
-    const double ks = c->pc[k].nfull == 0 ? (double)c->pc[k].nsplit : 1.0;   // ksplit
+    const double ks = c->opt.ksplit >= 2 ? std::min((double)c->opt.ksplit, stages) : 1.0;
+    const double f = (double)fold_period(c, prec, stages / ks);
     kappa = 32.0 * per_stage * f + stages / ks / f;
   }
   const double rho = u_enc + 2.0 * u_acc * std::sqrt(kappa);
@@ -560,8 +605,8 @@ static double rounding_floor(const gcp_ctx *c, int k) {
 static void setup_gemm(gcp_ctx *c, GemmArgs &g, int pi) {
   const gcp_ctx::PrecCfg &q = c->pc[pi];
   g.Mp = c->Mp;
-  g.pstride = c->Mp * c->Mp;
-  g.nt = c->nt;
+  g.nt = (int)(c->Mp / 128);
+  g.path = q.path;
   g.fold = q.fold;
   g.nfull = q.nfull;
   g.nsplit = q.nsplit;
@@ -696,12 +741,40 @@ static int build_guess(gcp_ctx *c, const double *H, int64_t ldh, double theta, d
   a.rD = c->rD0;
   a.part = c->part;
   HIPCHK(c, launch_init(c->opt.precision, a, c->stream));
-  int st = reduce(c, c->part, (int)(c->Mp / 64), 0, c->d20, c->dg0, nullptr, 0, 0);
-  if (st != GCP_OK) return st;
+  HIPCHK(c, launch_reduce(reduction(c, (int)(c->Mp / 64), 0, c->d20, c->dg0, nullptr, 0, 0),
+                          c->stream));
   HIPCHK(c, hipMemcpyAsync(c->sc_host, c->sc, sizeof(Scalars), hipMemcpyDeviceToHost, c->stream));
   HIPCHK(c, hipStreamSynchronize(c->stream));
   c->t1_0 = c->sc_host->t1;
   c->t2_0 = c->sc_host->t2;
+  return GCP_OK;
+}
+
+// Launch accounting of one solve (events when profiling, issued MFMA flops).
+struct LaunchLog {
+  bool prof = false;
+  int n = 0;
+  int phase[3] = {0, 0, 0};   // launches in each phase of the schedule
+  int reruns = 0;             // second K1 of an update after a change of encoding
+};
+
+// One product in encoding pc[pi] with the reduction g.red that follows it (the
+// tile kernels run it themselves).
+static int run_product(gcp_ctx *c, GemmArgs &g, int pi, LaunchLog *log) {
+  const gcp_ctx::PrecCfg &q = c->pc[pi];
+  g.path = q.path;
+  g.fold = q.fold;
+  g.nfull = q.nfull;
+  g.nsplit = q.nsplit;
+  const bool ev = log && log->prof && 2 * log->n + 1 < (int)c->events.size();
+  if (ev) HIPCHK(c, hipEventRecord(c->events[2 * log->n], c->stream));
+  HIPCHK(c, launch_gemm(q.prec, g, c->stream));
+  if (ev) HIPCHK(c, hipEventRecord(c->events[2 * log->n + 1], c->stream));
+  if (q.path == PATH_PAIR) HIPCHK(c, launch_reduce(g.red, c->stream));
+  if (log) {
+    ++log->n;
+    ++log->phase[pi];
+  }
   return GCP_OK;
 }
 
@@ -717,8 +790,8 @@ static int first_traces(gcp_ctx *c) {
   g.dg = c->dg0;
   g.rD = c->rD0;
   g.d2 = c->d20;
-  HIPCHK(c, launch_gemm(c->pc[0].prec, g, c->stream));
-  int st = reduce(c, c->part, c->nt, 1, c->d3, nullptr, c->tpart, c->pc[0].ntpart, 0);
+  g.red = reduction(c, (int)(c->Mp / 128), 1, c->d3, nullptr, c->tpart, c->pc[0].ntpart, 0);
+  int st = run_product(c, g, 0, nullptr);
   if (st != GCP_OK) return st;
   HIPCHK(c, hipMemcpyAsync(c->sc_host, c->sc, sizeof(Scalars), hipMemcpyDeviceToHost, c->stream));
   HIPCHK(c, hipStreamSynchronize(c->stream));
@@ -753,31 +826,6 @@ static int store_iterate(gcp_ctx *c, int n, int k, int prec) {
   return GCP_OK;
 }
 
-// Launch accounting of one solve (events when profiling, issued MFMA flops).
-struct LaunchLog {
-  bool prof = false;
-  int n = 0;
-  int phase[3] = {0, 0, 0};   // launches in each phase of the schedule
-  int reruns = 0;             // second K1 of an update after a change of encoding
-};
-
-// One product launch in encoding pc[pi].
-static int run_product(gcp_ctx *c, GemmArgs &g, int pi, LaunchLog *log) {
-  const gcp_ctx::PrecCfg &q = c->pc[pi];
-  g.fold = q.fold;
-  g.nfull = q.nfull;
-  g.nsplit = q.nsplit;
-  const bool ev = log && log->prof && 2 * log->n + 1 < (int)c->events.size();
-  if (ev) HIPCHK(c, hipEventRecord(c->events[2 * log->n], c->stream));
-  HIPCHK(c, launch_gemm(q.prec, g, c->stream));
-  if (ev) HIPCHK(c, hipEventRecord(c->events[2 * log->n + 1], c->stream));
-  if (log) {
-    ++log->n;
-    ++log->phase[pi];
-  }
-  return GCP_OK;
-}
-
 // K1 of update n on the iterate in buffer k: X2 = D D and the scalar step.
 // recheck: the same iterate once more, in a new encoding (after a switch).
 static int step_k1(gcp_ctx *c, GemmArgs &g, int pi, int k, int n, LaunchLog *log,
@@ -789,10 +837,9 @@ static int step_k1(gcp_ctx *c, GemmArgs &g, int pi, int k, int n, LaunchLog *log
   g.dg = c->dg[k];
   g.rD = c->rD[k];
   g.d2 = c->d2[k];
-  int st = run_product(c, g, pi, log);
-  if (st != GCP_OK) return st;
-  return reduce(c, c->part, c->nt, 1, c->d3, nullptr, c->tpart, c->pc[pi].ntpart, n,
-                g.status != nullptr, c->pc[pi].floor_ddbar, false, recheck);
+  g.red = reduction(c, (int)(c->Mp / 128), 1, c->d3, nullptr, c->tpart, c->pc[pi].ntpart, n,
+                    g.status != nullptr, c->pc[pi].floor_ddbar, false, recheck);
+  return run_product(c, g, pi, log);
 }
 
 // K2 of update n: D_{n+1} into buffer 1 - k.
@@ -803,14 +850,14 @@ static int step_k2(gcp_ctx *c, GemmArgs &g, int pi, int k, int n, LaunchLog *log
   g.out = c->Dp[1 - k];
   g.dg_new = c->dg[1 - k];
   g.rD_new = c->rD[1 - k];
-  int st = run_product(c, g, pi, log);
-  if (st != GCP_OK) return st;
   // In the solve (not when a segment is recomputed for the adjoint) the
   // stops that need only the new traces are decided here, unless the
   // idempotency test, which needs the next square, is on.
   const bool solve = g.status != nullptr;
-  return reduce(c, c->part, c->nt, 2, c->d2[1 - k], c->dg[1 - k], c->tpart, c->pc[pi].ntpart, n,
-                solve, c->pc[pi].floor_ddbar, solve && !(c->opt.tol_idem > 0.0));
+  g.red = reduction(c, (int)(c->Mp / 128), 2, c->d2[1 - k], c->dg[1 - k], c->tpart,
+                    c->pc[pi].ntpart, n, solve, c->pc[pi].floor_ddbar,
+                    solve && !(c->opt.tol_idem > 0.0));
+  return run_product(c, g, pi, log);
 }
 
 // Precision schedule: re-encode D_n (buffer k) from phase `from` into phase
@@ -1075,7 +1122,7 @@ extern "C" int gcp_purify(gcp_ctx *c, void *D, int32_t dtype, int64_t ldd, gcp_r
     res->gemm_flops = (double)real * Md * Md * (Md + 1.0);
     // issued MFMA flops: whole 128 x 128 tiles of the padded size times the
     // split products, launch by launch in each phase's encoding
-    const double tile_fl = (double)c->ntiles * 2.0 * 128.0 * 128.0 * (double)c->Mp;
+    const double tile_fl = c->nt_nominal * (c->nt_nominal + 1) / 2 * nominal_tile_flops(c);
     double mf = 0.0;
     for (int q = 0; q < c->nprec; ++q) {
       int nq = lg.phase[q];
@@ -1128,8 +1175,8 @@ extern "C" int gcp_backward(gcp_ctx *c, const void *dLdD, int64_t ldg, void *dLd
   }
   int nlaunch = 0;
   double flops = 0.0, mflops = 0.0;
-  const double Md = (double)c->M, tile_fl = 2.0 * 128.0 * 128.0 * (double)c->Mp;
-  const int ntri = c->nt * (c->nt + 1) / 2;
+  const double Md = (double)c->M, tile_fl = nominal_tile_flops(c);
+  const int nt = (int)(c->Mp / 64), ntri = nt * (nt + 1) / 2;
   auto gemm = [&](BwdArgs &a) -> int {
     if (prof) HIPCHK(c, hipEventRecord(c->events[2 * nlaunch], c->stream));
     HIPCHK(c, launch_bwd_gemm(bprec, a, c->stream));
@@ -1137,10 +1184,10 @@ extern "C" int gcp_backward(gcp_ctx *c, const void *dLdD, int64_t ldg, void *dLd
     ++nlaunch;
     if (a.mode == 1) {
       flops += 4.0 * Md * Md * Md;
-      mflops += 2.0 * c->nt * c->nt * tile_fl;
+      mflops += 2.0 * c->nt_nominal * c->nt_nominal * tile_fl;
     } else {
       flops += Md * Md * (Md + 1.0);
-      mflops += ntri * tile_fl;
+      mflops += c->nt_nominal * (c->nt_nominal + 1) / 2 * tile_fl;
     }
     return GCP_OK;
   };
@@ -1150,7 +1197,7 @@ extern "C" int gcp_backward(gcp_ctx *c, const void *dLdD, int64_t ldg, void *dLd
   double *kappa = c->bvec + 2 * c->Mp;
   BwdArgs a{};
   a.Mp = c->Mp;
-  a.nt = c->nt;
+  a.nt = nt;
   a.X2 = c->bX2;
   a.AT = c->bAT;
   a.CT = c->bCT;
@@ -1191,7 +1238,7 @@ extern "C" int gcp_backward(gcp_ctx *c, const void *dLdD, int64_t ldg, void *dLd
     a.out1 = c->bCT;
     st = gemm(a);
     if (st != GCP_OK) return st;
-    HIPCHK(c, launch_bwd_kappa(c->btpart, ntri, c->nt * c->nt, da, db, de, kappa, c->stream));
+    HIPCHK(c, launch_bwd_kappa(c->btpart, ntri, nt * nt, da, db, de, kappa, c->stream));
     // Gbar_n
     a.mode = 2;
     a.out0 = c->bG[1 - cur];
@@ -1263,11 +1310,11 @@ extern "C" int gcp_verify(gcp_ctx *c, const void *D, int32_t dtype, int64_t ldd,
   }
   const auto t_start = std::chrono::steady_clock::now();
   const size_t Mp = (size_t)c->Mp, mat = Mp * Mp * sizeof(double);
-  const int ntri = c->nt * (c->nt + 1) / 2;
+  const int nt = (int)(Mp / 64), ntri = nt * (nt + 1) / 2;
   if (!c->vD) {
-    void *p[4] = {nullptr, nullptr, nullptr, nullptr};
-    const size_t sz[4] = {mat, mat, mat, (4 * Mp + (size_t)ntri + 8) * sizeof(double)};
-    for (int k = 0; k < 4; ++k) {
+    void *p[3] = {nullptr, nullptr, nullptr};
+    const size_t sz[3] = {mat, mat, (5 * (size_t)ntri + 8) * sizeof(double)};
+    for (int k = 0; k < 3; ++k) {
       if (hipMalloc(&p[k], sz[k]) != hipSuccess) {
         for (int q = 0; q < k; ++q) (void)hipFree(p[q]);
         c->err = "gcp_verify: device allocation of the workspace failed";
@@ -1276,20 +1323,17 @@ extern "C" int gcp_verify(gcp_ctx *c, const void *D, int32_t dtype, int64_t ldd,
     }
     c->vD = (double *)p[0];
     c->vH = (double *)p[1];
-    c->vHD = (double *)p[2];
-    c->vaux = (double *)p[3];
+    c->vaux = (double *)p[2];
   }
   HIPCHK(c, launch_bwd_load(GCP_FP64, D, ldd, dtype, c->M, c->Mp, c->vD, c->stream));
   HIPCHK(c, launch_bwd_load(GCP_FP64, H, ldh, GCP_DTYPE_F64, c->M, c->Mp, c->vH, c->stream));
   VerifyArgs a{};
   a.D = c->vD;
   a.H = c->vH;
-  a.HD = c->vHD;
-  a.rows = c->vaux;
-  a.tpart = c->vaux + 4 * Mp;
-  a.out = c->vaux + 4 * Mp + ntri;
+  a.tpart = c->vaux;
+  a.out = c->vaux + 5 * (size_t)ntri;
   a.Mp = c->Mp;
-  a.nt = c->nt;
+  a.nt = nt;
   a.ntri = ntri;
   HIPCHK(c, launch_verify(a, c->stream));
   double out[5];
@@ -1297,11 +1341,11 @@ extern "C" int gcp_verify(gcp_ctx *c, const void *D, int32_t dtype, int64_t ldd,
   HIPCHK(c, hipStreamSynchronize(c->stream));
   const auto t_end = std::chrono::steady_clock::now();
   if (res) {
-    res->comm = std::sqrt(2.0 * out[0]);   // each off-diagonal pair counted once
+    res->idem = std::sqrt(out[0]);
     res->energy = out[1];
     res->fro2 = out[2];
     res->trace = out[3];
-    res->idem = std::sqrt(out[4]);
+    res->comm = std::sqrt(out[4]);
     res->ms = std::chrono::duration<double, std::milli>(t_end - t_start).count();
   }
   return GCP_OK;
@@ -1407,9 +1451,8 @@ extern "C" int gcp_purify_static(const double *H, int64_t ldh, int64_t M, int64_
   c.sc_host = &host_sc;
   // the array keeps the previous call's contents: the arrival counters and
   // the X2 diagonal residuals must start at zero
-  int ntail, nblk;
-  split_tail(&c, ntail, nblk);
-  if (launch_zero(c.split_cnt, ntail, c.stream) != hipSuccess ||
+  if (launch_zero(c.split_cnt, split_counters(&c), c.stream) != hipSuccess ||
+      launch_zero(c.rcnt, c.nred, c.stream) != hipSuccess ||
       launch_zero(c.counter, 1, c.stream) != hipSuccess ||
       launch_zero(c.s2, 2 * c.Mp, c.stream) != hipSuccess) {
     g_create_error = "gcp_purify_static: clearing the workspace failed";

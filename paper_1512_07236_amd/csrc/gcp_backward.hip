@@ -13,7 +13,7 @@
 // (Frobenius products; a', b', e' from update_coef_derivs; <Gbar', D^3> =
 // <D^2, D Gbar'>, needed only when e' != 0, i.e. for PMCP).
 //
-// One adjoint step is three launches of 128 x 128 MFMA tile products, all of
+// One adjoint step is three launches of 64 x 64 MFMA tile products, all of
 // the A * B^T row-panel form of the forward (every operand is symmetric
 // except AT and CT, which are only ever read along their rows):
 //   mode 0 (upper tiles)  X2 = D D           epilogue: per-tile sums of
@@ -63,16 +63,26 @@ __device__ __forceinline__ int xcd_linear(int b, int total) {
   return xcd * q + (xcd < r ? xcd : r) + loc;
 }
 
+template <int P> struct BwdCfg {
+  static constexpr int W = T64 * VP * 8;     // FP64 staging of a tile
+  static constexpr int MM = TileCfg<P>::SMEM > W ? TileCfg<P>::SMEM : W;
+  static constexpr int SMEM = MM + 8 * 8;    // and two sums per wave
+  static constexpr int BLOCKS = Enc<P>::KIND == 0 ? 3 : 2;   // per CU, as k_tile
+};
+
+// 64 x 64 tiles, one per block; thread tid works on columns 4 (tid % 16) .. +3
+// of rows 16 q + tid / 16 of the tile, so that the inputs are read, and the
+// result and its mirror (through LDS) written, as rows of 64 elements.
 template <int P, int MODE>
-__global__ __launch_bounds__(NTH, 2) void k_bgemm(BwdArgs a) {
+__global__ __launch_bounds__(NTH, BwdCfg<P>::BLOCKS) void k_bgemm(BwdArgs a) {
   using E = Enc<P>;
   using T = typename E::T;
-  constexpr int KIND = E::KIND;
-  using Acc = typename AccType<KIND>::type;
+  typedef T v4t __attribute__((ext_vector_type(4)));
+  using S = typename TileCfg<P>::S;
   static_assert(E::NP == 1, "the adjoint uses single-plane FP64 / FP32 storage");
 
-  __shared__ __attribute__((aligned(16))) T smem[MmaCfg<P>::SMEM];
-  __shared__ double red[4];
+  __shared__ __attribute__((aligned(16))) char smem[BwdCfg<P>::SMEM];
+  double *W = (double *)smem, *red = (double *)(smem + BwdCfg<P>::MM);
 
   const int64_t Mp = a.Mp;
   int ti, tj, lin = 0, which = 0;
@@ -84,7 +94,7 @@ __global__ __launch_bounds__(NTH, 2) void k_bgemm(BwdArgs a) {
   } else {
     tile_of_block(blockIdx.x, a.nt, ti, tj, lin);
   }
-  const int64_t arow0 = (int64_t)ti * TILE, brow0 = (int64_t)tj * TILE;
+  const int64_t arow0 = (int64_t)ti * T64, brow0 = (int64_t)tj * T64;
   const T *__restrict__ D = (const T *)a.D;
   const T *__restrict__ X2 = (const T *)a.X2;
   const T *__restrict__ G = (const T *)a.G;
@@ -102,35 +112,35 @@ __global__ __launch_bounds__(NTH, 2) void k_bgemm(BwdArgs a) {
     Bl = AT;
   }
 
-  Acc acc[4][4];
-  mma_tile<P>(Al, Bl, arow0, brow0, Mp, Mp * Mp, smem, 0, acc);
+  tile_product<P>(Al, Bl, arow0, brow0, Mp, smem, fp32_fold(Mp), 0,
+                  (int)(Mp / TileCfg<P>::KT));
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave >> 1, wn = wave & 1, l16 = lane & 15, lg = lane >> 4;
+  const int c4 = (tid & 15) * 4, r0 = tid >> 4;
+  const S *V = (const S *)smem + r0 * VP + c4;   // this thread's elements
+  const int64_t o0 = (arow0 + r0) * Mp + brow0 + c4;
+  const int64_t m0 = (brow0 + r0) * Mp + arow0 + c4;   // in the mirrored tile
 
   if constexpr (MODE == 1) {
     T *__restrict__ O = (T *)(which ? a.out1 : a.out0);
     const bool x3 = a.need_x3 && !which;   // block-uniform
     double xsum = 0.0;
 #pragma unroll
-    for (int bi = 0; bi < 4; ++bi)
+    for (int q = 0; q < 4; ++q) {
+      const int64_t o = o0 + q * 16 * Mp;
+      v4t ov;
 #pragma unroll
-      for (int bj = 0; bj < 4; ++bj)
+      for (int e = 0; e < 4; ++e) ov[e] = V[q * 16 * VP + e];
+      if (x3) {
+        const v4t xv = *(const v4t *)(X2 + o);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int64_t i = arow0 + wm * 64 + bi * 16 + acc_row<KIND>(lg, r);
-          const int64_t j = brow0 + wn * 64 + bj * 16 + l16;
-          const T o = (T)acc[bi][bj][r];
-          O[i * Mp + j] = o;
-          if (x3) xsum += (double)X2[i * Mp + j] * (double)o;
-        }
+        for (int e = 0; e < 4; ++e) xsum += (double)xv[e] * (double)ov[e];
+      }
+      *(v4t *)(O + o) = ov;
+    }
     if (x3) {
-      xsum += shfl_xor_d(xsum, 1);
-      xsum += shfl_xor_d(xsum, 2);
-      xsum += shfl_xor_d(xsum, 4);
-      xsum += shfl_xor_d(xsum, 8);
-      xsum += shfl_xor_d(xsum, 16);
-      xsum += shfl_xor_d(xsum, 32);
+#pragma unroll
+      for (int m = 1; m < 64; m <<= 1) xsum += shfl_xor_d(xsum, m);
       if (lane == 0) red[wave] = xsum;
       __syncthreads();
       if (tid == 0) {
@@ -141,70 +151,83 @@ __global__ __launch_bounds__(NTH, 2) void k_bgemm(BwdArgs a) {
     return;
   }
 
-  const bool diag_tile = (ti == tj);
+  const bool dtile = (ti == tj);
   T *__restrict__ O = (T *)a.out0;
   double tsum = 0.0, dsum = 0.0;
   const double kappa = MODE == 2 ? *a.kappa : 0.0;
-  // The inputs of BJC column blocks of a row block are loaded before any of
-  // their stores: read per element after the stores before it, each would
-  // wait for them (the compiler cannot tell the output from the inputs).
-  // (FP64 takes one block at a time, and in mode 2 two of its rows: more
-  // would spill.)
-  constexpr int BJC = sizeof(T) == 8 ? 1 : 2;
-  constexpr int RC = sizeof(T) == 8 && MODE == 2 ? 2 : 4;
-  constexpr int NIN = MODE == 0 ? 2 : 7;   // D, G (and X2, AT, AT^T, CT, CT^T)
+  double v[4][4];
 #pragma unroll
-  for (int bi = 0; bi < 4; ++bi)
+  for (int q = 0; q < 4; ++q)
 #pragma unroll
-    for (int b0 = 0; b0 < 4; b0 += BJC)
+    for (int e = 0; e < 4; ++e) v[q][e] = (double)V[q * 16 * VP + e];
+  if constexpr (MODE == 2) {
+    // b AT^T + e CT^T + e E: the transposes from rows of the mirrored tile
+    double t[4][4];
 #pragma unroll
-      for (int r0 = 0; r0 < 4; r0 += RC) {
-        T in[BJC][RC][NIN];
+    for (int q = 0; q < 4; ++q) {
+      const v4t at = *(const v4t *)(AT + m0 + q * 16 * Mp), ct = *(const v4t *)(CT + m0 + q * 16 * Mp);
 #pragma unroll
-        for (int q = 0; q < BJC; ++q)
+      for (int e = 0; e < 4; ++e) t[q][e] = a.b * (double)at[e] + a.e * (double)ct[e];
+    }
+    __syncthreads();   // V read by all
 #pragma unroll
-          for (int rr = 0; rr < RC; ++rr) {
-            const int r = r0 + rr;
-            const int64_t i = arow0 + wm * 64 + bi * 16 + acc_row<KIND>(lg, r);
-            const int64_t j = brow0 + wn * 64 + (b0 + q) * 16 + l16;
-            in[q][rr][0] = D[i * Mp + j];
-            in[q][rr][1] = G[i * Mp + j];
-            if constexpr (MODE == 2) {
-              in[q][rr][2] = X2[i * Mp + j];
-              in[q][rr][3] = AT[i * Mp + j];
-              in[q][rr][4] = AT[j * Mp + i];
-              in[q][rr][5] = CT[i * Mp + j];
-              in[q][rr][6] = CT[j * Mp + i];
-            }
-          }
+    for (int q = 0; q < 4; ++q)
 #pragma unroll
-        for (int q = 0; q < BJC; ++q)
+      for (int e = 0; e < 4; ++e) W[(q * 16 + r0) * VP + c4 + e] = t[q][e];
+    __syncthreads();
 #pragma unroll
-          for (int rr = 0; rr < RC; ++rr) {
-            const int bj = b0 + q, r = r0 + rr;
-            const int64_t i = arow0 + wm * 64 + bi * 16 + acc_row<KIND>(lg, r);
-            const int64_t j = brow0 + wn * 64 + bj * 16 + l16;
-            if (diag_tile && i > j) continue;   // covered by the mirror of (j, i)
-            const double v = (double)acc[bi][bj][r];
-            const double d = (double)in[q][rr][0];
-            double o;
-            if constexpr (MODE == 0) {
-              o = v;
-              const double wg = ((i == j) ? 1.0 : 2.0) * (double)in[q][rr][1];
-              tsum += wg * (double)(T)v;
-              dsum += wg * d;
-            } else {
-              const double g = (double)in[q][rr][1];
-              const double x2 = (double)in[q][rr][2];
-              const double at = (double)in[q][rr][3] + (double)in[q][rr][4];
-              const double ct = (double)in[q][rr][5] + (double)in[q][rr][6];
-              const double gc = ((2.0 * d - 3.0 * x2) - a.c * ((i == j ? 1.0 : 0.0) - 2.0 * d)) * a.inv_t12;
-              o = a.a * g + a.b * at + a.e * (ct + v) + kappa * gc;
-            }
-            O[i * Mp + j] = (T)o;
-            if (i != j) O[j * Mp + i] = (T)o;
-          }
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[q][e] = W[(c4 + e) * VP + q * 16 + r0] + a.e * v[q][e];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int row = q * 16 + r0;
+    const int64_t o = o0 + q * 16 * Mp;
+    const v4t dv = *(const v4t *)(D + o), gv = *(const v4t *)(G + o);
+    v4t ov;
+    if constexpr (MODE == 0) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int c = c4 + e;
+        const T x = (T)v[q][e];
+        ov[e] = x;
+        if (dtile && row > c) continue;   // covered by the mirror of (j, i)
+        const double wg = ((dtile && row == c) ? 1.0 : 2.0) * (double)gv[e];
+        tsum += wg * (double)x;
+        dsum += wg * (double)dv[e];
       }
+    } else {
+      const v4t xv = *(const v4t *)(X2 + o), av = *(const v4t *)(AT + o), cv = *(const v4t *)(CT + o);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const double d = (double)dv[e], x2 = (double)xv[e];
+        const double one = (dtile && row == c4 + e) ? 1.0 : 0.0;
+        const double gc = ((2.0 * d - 3.0 * x2) - a.c * (one - 2.0 * d)) * a.inv_t12;
+        ov[e] = (T)(a.a * (double)gv[e] + a.b * (double)av[e] + a.e * (double)cv[e] + v[q][e] +
+                    kappa * gc);
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) ((T *)smem)[row * VP + c4 + e] = ov[e];
+    if (!dtile) *(v4t *)(O + o) = ov;
+  }
+  __syncthreads();
+  // mirrored tile, from LDS; a diagonal tile is written whole from here, its
+  // lower half from the upper one
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int row = q * 16 + r0;
+    v4t ov;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int c = c4 + e;
+      const bool up = dtile && row < c;
+      ov[e] = ((const T *)smem)[(up ? row : c) * VP + (up ? c : row)];
+    }
+    *(v4t *)(O + m0 + q * 16 * Mp) = ov;
+  }
 
   if constexpr (MODE == 0) {
 #pragma unroll
@@ -212,16 +235,15 @@ __global__ __launch_bounds__(NTH, 2) void k_bgemm(BwdArgs a) {
       tsum += shfl_xor_d(tsum, m);
       dsum += shfl_xor_d(dsum, m);
     }
-    __shared__ double red2[4];
     if (lane == 0) {
       red[wave] = tsum;
-      red2[wave] = dsum;
+      red[4 + wave] = dsum;
     }
     __syncthreads();
     if (tid == 0) {
       const int ntri = a.nt * (a.nt + 1) / 2;
       a.tpart[lin] = ((red[0] + red[1]) + red[2]) + red[3];
-      a.tpart[ntri + lin] = ((red2[0] + red2[1]) + red2[2]) + red2[3];
+      a.tpart[ntri + lin] = ((red[4] + red[5]) + red[6]) + red[7];
     }
   }
 }
@@ -263,6 +285,7 @@ __global__ __launch_bounds__(256) void k_bstore(const void *planes, const double
   // rows on the x dimension of the grid (no 64K limit), 256 columns per block on y
   const int64_t i = blockIdx.x;
   const int64_t j = (int64_t)blockIdx.y * 256 + threadIdx.x;
+  if (j >= Mp) return;
   double x;
   if (i == j) {
     x = dg[i];
@@ -375,7 +398,7 @@ __global__ __launch_bounds__(256) void k_bdh(BwdInitArgs a) {
 template <int PF>
 static hipError_t store_pf(int bprec, const void *planes, const double *dg, int64_t Mp, void *out,
                            hipStream_t st) {
-  const dim3 grid((unsigned)Mp, (unsigned)(Mp / 256));
+  const dim3 grid((unsigned)Mp, (unsigned)((Mp + 255) / 256));
   if (bprec == GCP_FP64)
     k_bstore<PF, GCP_FP64><<<grid, 256, 0, st>>>(planes, dg, Mp, out);
   else

@@ -75,21 +75,47 @@ struct Scalars {
   int32_t pad;
 };
 
+struct RedArgs {
+  const double *part;
+  int nslots;
+  int mode;            // 0 after init, 1 after D^2, 2 after the update
+  int64_t Mp;
+  double *out;
+  const double *extra;
+  double *bpart;
+  unsigned *counter;
+  unsigned *rcnt;      // tiles done per 64-row block (tile kernels; self-resetting)
+  const double *tpart;
+  int ntiles;
+  int iter, max_iter;
+  int early_stop;      // mode 2: decide the stops that need only T1 and T2 of D_{n+1}
+  double tol_ddbar, tol_idem, N;
+  double floor_ddbar;  // rounding floor of |Tr(D Dbar)| of the encoding
+  int skip_if_stopped; // 1: do nothing once sc->status is non-zero
+  int recheck;         // mode 1: the same iterate again (after a change of encoding):
+                       // no stall test against, and no update of, prev_ddbar
+  Scalars *sc;
+  double *hist;
+};
+
+// Product kernels: one 64 x 64 tile per block, with the reduction that follows
+// it (every encoding), or pairs of 128 x 128 tiles (16-bit).
+enum { PATH_T64 = 0, PATH_PAIR = 1 };
+
 struct GemmArgs {
   const void *A;       // left operand planes (rows of D or X2)
   const void *B;       // right operand planes (rows of D)
   void *out;           // output planes (X2 in mode 0, D_{n+1} in mode 1)
-  int64_t Mp;          // padded size (multiple of 128)
-  int64_t pstride;     // elements between planes
-  int nt;              // Mp / 128
+  int64_t Mp;          // padded size (a multiple of the path's tile edge)
+  int nt;              // Mp / 128 (PATH_PAIR)
+  int path;            // PATH_*
   int mode;            // 0: X2 = D D, 1: D_{n+1} = (1-2c) D + (2+2c) X2 - 2 X2 D
   int fold;            // fold period of the main accumulator, in K stages
-  // Blocks [0, nfull) compute whole units (tile pairs in the 16-bit kernel,
-  // tiles in the FP64 / FP32 one); the remaining units are each split over
-  // nsplit blocks along K (nsplit = 1: no split), whose partial tiles (FP32,
-  // or the accumulator type) meet in ws and are added in FP64, in split
-  // order, by the last of them to finish (per-unit arrival counters in cnt,
-  // self-resetting)
+  // Blocks [0, nfull) compute whole units (tiles, or tile pairs); the
+  // remaining units are each split over nsplit blocks along K, whose partial
+  // tiles (FP32, or FP64 for FP64) meet in ws and are added in FP64, in split
+  // order, by the last of the splits to finish (per-unit arrival counters in
+  // cnt, self-resetting)
   int nfull;
   int nsplit;
   int method;          // 0 HPCP, 1 PMCP (update coefficients of mode 1)
@@ -102,8 +128,9 @@ struct GemmArgs {
   const double *d3;    // diag(X2 D) FP64                 (mode 1)
   double *dg_new;      // diag(D_{n+1})                   (mode 1)
   double *rD_new;      // its residual                    (mode 1)
-  double *part;        // row sums [nt][Mp]
+  double *part;        // row sums [column tile][Mp]
   double *tpart;       // tile sums [ntiles]
+  RedArgs red;         // PATH_T64: the reduction that follows the product
   const double *coef;  // coef[0] = c_n (mode 1)
   // non-NULL: the launch does nothing once *status is non-zero (the solve
   // has stopped; later launches of a batch enqueued ahead are void)
@@ -116,28 +143,6 @@ struct InitArgs {
   double theta, beta, mu;
   void *out;
   double *dg, *rD, *part;
-};
-
-struct RedArgs {
-  const double *part;
-  int nslots;
-  int mode;            // 0 after init, 1 after D^2, 2 after the update
-  int64_t Mp;
-  double *out;
-  const double *extra;
-  double *bpart;
-  unsigned *counter;
-  const double *tpart;
-  int ntiles;
-  int iter, max_iter;
-  int early_stop;      // mode 2: decide the stops that need only T1 and T2 of D_{n+1}
-  double tol_ddbar, tol_idem, N;
-  double floor_ddbar;  // rounding floor of |Tr(D Dbar)| of the encoding
-  int skip_if_stopped; // 1: do nothing once sc->status is non-zero
-  int recheck;         // mode 1: the same iterate again (after a change of encoding):
-                       // no stall test against, and no update of, prev_ddbar
-  Scalars *sc;
-  double *hist;
 };
 
 struct OutArgs {
@@ -188,10 +193,8 @@ struct BwdInitArgs {
 // symmetric parts of the caller's matrices, Mp x Mp, zero padded.
 struct VerifyArgs {
   const double *D, *H;
-  double *HD;          // Mp x Mp
-  double *tpart;       // upper-tile partials of ||D^2 - D||_F^2
-  double *rows;        // 4 Mp row partials
-  double *out;         // 5 sums: commutator^2, Tr(DH), ||D||_F^2, Tr D, ||D^2-D||_F^2
+  double *tpart;       // [5][ntri] sums over the upper 64 x 64 tiles
+  double *out;         // ||D^2-D||_F^2, Tr(DH), ||D||_F^2, Tr D, ||HD-DH||_F^2
   int64_t Mp;
   int nt, ntri;
 };

@@ -25,251 +25,499 @@
 
 namespace gcp {
 
-// FP64 / FP32 product kernel: one 128 x 128 upper-triangle tile per block of
-// 4 waves (2 x 2 grid of 64 x 64), MFMA 16x16x4, two blocks per CU.  Blocks
-// [0, nfull) compute whole tiles; each remaining tile is split along K over
-// nsplit blocks (the tiles of a last partial round, or every tile of a
-// product smaller than one round), whose partial tiles meet in ws and are
-// added in FP64, in split order, by the last of them to finish.
-template <int P>
-__global__ __launch_bounds__(NTH, 2) void k_gemm(GemmArgs g) {
+// ------------------------------------------------------- scalar step
+__device__ __forceinline__ double ld_agent(const double *p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ void st_agent(double *p, double v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// The scalar step at this point of the iteration (one thread).
+__device__ void scalar_step(const RedArgs &a, double sum_out, double sum_extra,
+                            double sum_tiles) {
+  Scalars *sc = a.sc;
+  if (a.mode == 0) {            // after the initial guess
+    sc->t2 = sum_out;
+    sc->t1 = sum_extra;
+  } else if (a.mode == 1) {     // after D^2: decide and form c
+    const double t1 = sc->t1, t2 = sc->t2, t3 = sum_out, om = sum_tiles;
+    const double ddbar = t1 - t2;
+    int status = 0;
+    double c = NAN;
+    if (!isfinite(t1) || !isfinite(t2) || !isfinite(om)) {
+      status = 3;
+    } else if (fabs(ddbar) <= a.tol_ddbar || sqrt(om) <= a.tol_idem) {
+      status = 1;
+    } else if (a.iter >= a.max_iter) {
+      status = 2;
+    } else {
+      if (ddbar > 0.0) c = (t2 - t3) / ddbar;
+      // Tr(D Dbar) <= 0 or c outside [0, 1] is a runaway, unless |Tr(D Dbar)|
+      // is already within the encoding's rounding floor, where it (and c)
+      // is rounding noise and stops decreasing: the iterate is then as
+      // idempotent as the encoding allows and the solve stops there.
+      const bool bad = !(ddbar > 0.0) || !isfinite(c) || c < 0.0 || c > 1.0;
+      const bool stalled = !a.recheck && fabs(ddbar) >= sc->prev_ddbar;
+      if ((bad || stalled) && fabs(ddbar) <= a.floor_ddbar) status = 4;
+      else if (bad) status = 3;
+    }
+    if (!a.recheck) sc->prev_ddbar = fabs(ddbar);
+    if (status != 0) sc->iter = a.iter;
+    sc->t3 = t3;
+    sc->omega = om;
+    sc->c = c;
+    sc->status = status;
+    double *h = a.hist + (int64_t)a.iter * 9;
+    const double gamma = 1.0 / 3.0 - 2.0 / 3.0 * c;
+    h[0] = a.iter; h[1] = t1; h[2] = t2; h[5] = om;
+    if (status == 0) {
+      h[3] = t3; h[4] = c; h[6] = gamma;
+      h[7] = om - gamma * (3.0 * t2 - 2.0 * t3 - a.N);
+    } else {
+      h[3] = h[4] = h[6] = h[7] = NAN;
+    }
+    h[8] = NAN;
+  } else {                      // after the update: traces of D_{n+1}
+    sc->t2 = sum_out;
+    sc->t1 = sum_extra;
+    sc->step = sum_tiles;
+    a.hist[(int64_t)a.iter * 9 + 8] = sqrt(sum_tiles);
+    if (!a.early_stop) return;
+    // The stops of the mode-1 decision that need only T1 and T2 of D_{n+1},
+    // taken here so that the square of the last iterate is never formed:
+    // |Tr(D Dbar)| within tol_ddbar, or within the rounding floor while not
+    // decreasing or not positive (below max_iter, where mode 1 would report
+    // max_iter first).  Everything else (non-finite traces, c outside
+    // [0, 1], max_iter) is left to mode 1, which would take the same
+    // decision on the same traces.
+    const double t1 = sum_extra, t2 = sum_out, ddbar = t1 - t2;
+    const int nx = a.iter + 1;
+    int status = 0;
+    if (isfinite(t1) && isfinite(t2)) {
+      if (fabs(ddbar) <= a.tol_ddbar) status = 1;
+      else if (nx < a.max_iter && (!(ddbar > 0.0) || fabs(ddbar) >= sc->prev_ddbar) &&
+               fabs(ddbar) <= a.floor_ddbar)
+        status = 4;
+    }
+    if (status == 0) return;
+    sc->status = status;
+    sc->iter = nx;
+    sc->on_traces = 1;
+    sc->omega = NAN;
+    double *h = a.hist + (int64_t)nx * 9;
+    h[0] = nx; h[1] = t1; h[2] = t2;
+    h[3] = h[4] = h[5] = h[6] = h[7] = h[8] = NAN;
+  }
+}
+
+// ------------------------------------------------- epilogue of one tile
+// The epilogues work on 64 x 64 tiles (ti <= tj) of the output with 256
+// threads: thread tid holds columns 4 (tid % 16) .. +3 of the rows
+// 16 q + tid / 16, q = 0..3, so that a row of the tile is one contiguous
+// access of 16 lanes.  The encoded results also go to LDS, from which the
+// mirrored tile is written as rows.
+template <int P> struct FinCfg {
+  using T = typename Enc<P>::T;
+  static constexpr int QC = sizeof(T) == 8 ? 2 : 4;   // rows of a thread taken together
+  static constexpr int V = Enc<P>::NP * T64 * VP * (int)sizeof(T);   // encoded results
+  static constexpr int SUMS = (V + 15) / 16 * 16;                    // then FP64 sums
+  static constexpr int SMEM_FIN = SUMS + (T64 + 4 * T64 + 4) * 8;
+  static constexpr int SMEM_RED = 8 * 64 * 8;                        // finish_rows
+  static constexpr int SMEM = SMEM_FIN > SMEM_RED ? SMEM_FIN : SMEM_RED;
+};
+
+// Row block R (64 rows) is complete when all nt64 tiles that touch it have
+// stored their row sums.  The block that completes it adds the slots (wave q
+// the slots s = q (mod 4) in ascending order, then the four wave sums), and
+// the block that completes the last row block adds the block sums and the
+// tile sums in a fixed order and runs the scalar step: the sums do not depend
+// on the order in which blocks finish.  Sums that cross blocks inside the
+// launch are stored and loaded at agent scope (the XCDs' L2s are not coherent
+// for plain accesses) and are out before the counters move.
+__device__ __forceinline__ void finish_rows(const RedArgs &a, int ti, int tj, int nt64,
+                                            double *sm) {
+  const int tid = threadIdx.x, lane = tid & 63, q = tid >> 6;
+  int *flag = (int *)sm;
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  __syncthreads();
+  if (tid == 0) {
+    int f = atomicAdd(a.rcnt + ti, 1u) == (unsigned)nt64 - 1 ? 1 : 0;
+    if (tj != ti && atomicAdd(a.rcnt + tj, 1u) == (unsigned)nt64 - 1) f |= 2;
+    *flag = f;
+  }
+  __syncthreads();
+  const int f = *flag;
+  if (f == 0) return;
+  bool last = false;
+  for (int h = 0; h < 2; ++h) {
+    if (!((f >> h) & 1)) continue;   // block-uniform
+    const int R = h ? tj : ti;
+    const int64_t i = (int64_t)R * 64 + lane;
+    double w = 0.0;
+#pragma unroll 8
+    for (int s = q; s < nt64; s += 4) w += ld_agent(a.part + (int64_t)s * a.Mp + i);
+    __syncthreads();
+    sm[q * 64 + lane] = w;
+    __syncthreads();
+    if (q == 0) {
+      double v = ((sm[lane] + sm[64 + lane]) + sm[128 + lane]) + sm[192 + lane];
+      a.out[i] = v;
+      double e = a.extra ? ld_agent(a.extra + i) : 0.0;
+      v = wave_sum(v);
+      e = wave_sum(e);
+      if (lane == 0) {
+        st_agent(a.bpart + 2 * R, v);
+        st_agent(a.bpart + 2 * R + 1, e);
+        a.rcnt[R] = 0u;   // ready for the next launch
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        flag[2 * 256] = atomicAdd(a.counter, 1u) == (unsigned)nt64 - 1;
+      }
+    }
+    __syncthreads();
+    last = last || flag[2 * 256];
+  }
+  if (!last) return;
+  double b1 = 0.0, b2 = 0.0, b3 = 0.0;
+  for (int b = tid; b < nt64; b += 256) {
+    b1 += ld_agent(a.bpart + 2 * b);
+    b2 += ld_agent(a.bpart + 2 * b + 1);
+  }
+#pragma unroll 4
+  for (int t = tid; t < a.ntiles; t += 256) b3 += ld_agent(a.tpart + t);
+  b1 = wave_sum(b1);
+  b2 = wave_sum(b2);
+  b3 = wave_sum(b3);
+  __syncthreads();
+  if (lane == 0) {
+    sm[q] = b1;
+    sm[4 + q] = b2;
+    sm[8 + q] = b3;
+  }
+  __syncthreads();
+  if (tid != 0) return;
+  *a.counter = 0u;
+  scalar_step(a, ((sm[0] + sm[1]) + sm[2]) + sm[3], ((sm[4] + sm[5]) + sm[6]) + sm[7],
+              ((sm[8] + sm[9]) + sm[10]) + sm[11]);
+}
+
+// Epilogue of tile (ti, tj): the update from the products of this thread's
+// elements (vload(q0, v) gives rows q0 .., SC^2 times the product), stored at (i, j) and
+// mirrored, with its row sums, column sums and tile sum.  lin: the tile's
+// index among all upper tiles.  DT: a diagonal tile, whose elements below
+// the diagonal are the mirror of those above and whose diagonal comes from
+// the FP64 vectors; the other tiles are compiled without those cases.
+// Elements are kept in the stored units SC x, whose scaling is exact.
+//
+// Bound by the chain of memory round trips, and for many tiles by vector
+// instructions (about 100 per element before the diagonal cases and the
+// scalings went, 40 now).
+template <int P, int MODE, bool DT, class V>
+__device__ __forceinline__ void finish_tile(const GemmArgs &g, int ti, int tj, int lin, V &&vload,
+                                            char *smem) {
   using E = Enc<P>;
   using T = typename E::T;
-  constexpr int NP = E::NP, KIND = E::KIND;
-  using Acc = typename AccType<KIND>::type;
+  typedef T v4t __attribute__((ext_vector_type(4)));
+  constexpr int NP = E::NP;
+  constexpr double SC = E::SC, INV = 1.0 / SC;
+  const int64_t Mp = g.Mp, i0 = (int64_t)ti * T64, j0 = (int64_t)tj * T64;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int c4 = (tid & 15) * 4, r0 = tid >> 4;
+  const T *__restrict__ Ag = (const T *)g.A;
+  const T *__restrict__ Bg = (const T *)g.B;
+  T *__restrict__ Og = (T *)g.out;
+  T *Vt = (T *)smem;
+  double rDj[4], colacc[4] = {}, rowacc[4], tacc = 0.0;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) rDj[e] = g.rD[j0 + c4 + e];
+  double a_coef = 0.0, b_coef = 0.0, e_coef = 0.0;
+  if constexpr (MODE == 1) update_coefs(g.method, g.coef[0], a_coef, b_coef, e_coef);
+  // the inputs of QC rows are loaded together, before any of their stores (the
+  // compiler cannot tell the output from the inputs); four FP64 rows would
+  // not fit the registers of four blocks per CU
+  constexpr int QC = FinCfg<P>::QC;
+#pragma unroll
+  for (int q0 = 0; q0 < 4; q0 += QC) {
+    v4t dv[QC][NP], xv[QC][NP];
+    double ri[QC], dgi[QC], d2i[QC], d3i[QC];   // (the last three: the diagonal, DT)
+#pragma unroll
+    for (int u = 0; u < QC; ++u) {
+      const int64_t i = i0 + (q0 + u) * 16 + r0;
+#pragma unroll
+      for (int p = 0; p < NP; ++p) {
+        dv[u][p] = *(const v4t *)(Bg + eoff<P>(i, j0 + c4, p, Mp));
+        if constexpr (MODE == 1) xv[u][p] = *(const v4t *)(Ag + eoff<P>(i, j0 + c4, p, Mp));
+      }
+      ri[u] = MODE == 0 ? g.rD[i] : g.s2[i];
+      if constexpr (DT) {
+        dgi[u] = g.dg[i];
+        d2i[u] = g.d2[i];
+        if constexpr (MODE == 1) d3i[u] = g.d3[i];
+      }
+    }
+    double v[QC][4];
+    vload(q0, v);
+#pragma unroll
+    for (int u = 0; u < QC; ++u) {
+      const int q = q0 + u, row = q * 16 + r0;
+      const int64_t i = i0 + row;
+      v4t ov[NP];
+      double rs = 0.0;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const bool diag = DT && row == c4 + e, lower = DT && row > c4 + e;
+        T dp[NP], op[NP];
+#pragma unroll
+        for (int p = 0; p < NP; ++p) dp[p] = dv[u][p][e];
+        const double pv = v[u][e] * INV;   // SC times the product
+        double Dm = E::dec_s(dp), prod, diff;
+        if constexpr (MODE == 0) {
+          // X2 = (D_enc + diag(rD))^2: exact diagonal-residual correction
+          double x2 = pv + Dm * (ri[u] + rDj[e]);
+          if (diag) {
+            Dm = SC * dgi[u];
+            x2 = SC * d2i[u];
+          }
+          E::enc_s(x2, op);
+          double x2m = E::dec_s(op);
+          if (diag) {
+            g.s2[i] = INV * (x2 - x2m);
+            x2m = x2;
+          }
+          prod = x2m * Dm;
+          diff = x2m - Dm;
+        } else {
+          T xp[NP];
+#pragma unroll
+          for (int p = 0; p < NP; ++p) xp[p] = xv[u][p][e];
+          const double X2m = E::dec_s(xp);
+          // X3 = (X2_enc + diag(s2)) (D_enc + diag(rD))
+          const double x3 = pv + X2m * rDj[e] + ri[u] * Dm;
+          double dn = a_coef * Dm + b_coef * X2m + e_coef * x3;
+          if (diag) {
+            const double d = dgi[u], x = a_coef * d + b_coef * d2i[u] + e_coef * d3i[u];
+            st_agent(g.dg_new + i, x);   // summed inside this launch
+            Dm = SC * d;
+            dn = SC * x;
+          }
+          E::enc_s(dn, op);
+          double dnm = E::dec_s(op);
+          if (diag) {
+            g.rD_new[i] = INV * (dn - dnm);
+            dnm = dn;
+          }
+          prod = dnm * dnm;
+          diff = dnm - Dm;
+        }
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+          ov[p][e] = op[p];
+          Vt[(p * T64 + row) * VP + c4 + e] = op[p];
+        }
+        if (lower) continue;   // covered by the mirror of (j, i)
+        rs += prod;
+        if (!diag) {
+          colacc[e] += prod;
+          tacc += diff * diff;
+        } else {
+          tacc += 0.5 * diff * diff;
+        }
+      }
+      rowacc[q] = rs;
+      if constexpr (!DT) {
+#pragma unroll
+        for (int p = 0; p < NP; ++p) *(v4t *)(Og + eoff<P>(i, j0 + c4, p, Mp)) = ov[p];
+      }
+    }
+  }
+  double *rp = (double *)(smem + FinCfg<P>::SUMS);   // [64] row sums
+  double *cp = rp + T64;                             // [4 waves][64] column sums
+  double *tp = cp + 4 * T64;                         // [4 waves]
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const double x = row_sum(rowacc[q]);
+    if ((lane & 15) == 0) rp[q * 16 + r0] = x;
+  }
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const double x = swap32_sum(swap16_sum(colacc[e]));
+    if (lane < 16) cp[wave * T64 + c4 + e] = x;
+  }
+  tacc = wave_sum(tacc);
+  if (lane == 0) tp[wave] = tacc;
+  __syncthreads();
+  // mirrored tile: row j0 + row, columns i0 + c4 .. +3.  A diagonal tile is
+  // written whole from here, its lower half from the upper one.
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int row = q * 16 + r0;
+#pragma unroll
+    for (int p = 0; p < NP; ++p) {
+      v4t w;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const int c = c4 + e;
+        const bool up = DT && row < c;
+        w[e] = Vt[(p * T64 + (up ? row : c)) * VP + (up ? c : row)];
+      }
+      *(v4t *)(Og + eoff<P>(j0 + row, i0 + c4, p, Mp)) = w;
+    }
+  }
+  if (tid < T64) {
+    constexpr double I2 = INV * INV;
+    const double rs = I2 * rp[tid];
+    const double cs = I2 * (((cp[tid] + cp[T64 + tid]) + cp[2 * T64 + tid]) + cp[3 * T64 + tid]);
+    if constexpr (!DT) {
+      st_agent(g.part + (int64_t)tj * Mp + i0 + tid, rs);
+      st_agent(g.part + (int64_t)ti * Mp + j0 + tid, cs);
+    } else {
+      st_agent(g.part + (int64_t)ti * Mp + i0 + tid, rs + cs);
+    }
+    // every off-diagonal element counts twice
+    if (tid == 0) st_agent(g.tpart + lin, (2.0 * I2) * (((tp[0] + tp[1]) + tp[2]) + tp[3]));
+  }
+}
 
-  __shared__ __attribute__((aligned(16))) T smem[MmaCfg<P>::SMEM];
+template <int P, class V>
+__device__ __forceinline__ void finish_any(const GemmArgs &g, int ti, int tj, int lin, V &&vload,
+                                           char *smem) {
+  if (g.mode == 0) {
+    if (ti != tj) finish_tile<P, 0, false>(g, ti, tj, lin, vload, smem);
+    else finish_tile<P, 0, true>(g, ti, tj, lin, vload, smem);
+  } else {
+    if (ti != tj) finish_tile<P, 1, false>(g, ti, tj, lin, vload, smem);
+    else finish_tile<P, 1, true>(g, ti, tj, lin, vload, smem);
+  }
+  finish_rows(g.red, ti, tj, (int)(g.Mp / T64), (double *)smem);
+}
+
+// ---------------------------------------------------- tile product kernel
+// One 64 x 64 upper tile per block, with its epilogue and the reduction that
+// follows the product.  Blocks [0, nfull) compute whole tiles; each remaining
+// tile is split along K over nsplit blocks, which publish their partial
+// tiles, and the last of them to finish adds all of them in FP64, in split
+// order (the sum does not depend on the order of arrival), and runs the
+// epilogue.
+//
+// Small tiles keep several blocks on a CU, so that the epilogue of one runs
+// under the products of the others, and fill the chip at small M.  Per
+// product, against 128 x 128 tiles of one block's 64 x 64 waves (16-bit:
+// pairs) followed by a reduction launch, in us: FP64 M = 256 55 -> 23,
+// M = 2048 310 -> 152, M = 4096 1360 -> 997; FP32 M = 4096 670 -> 575; FP16X3
+// M = 1000 80 -> 29, M = 2048 145 -> 53.
+template <int P> struct TileKernel {
+  using C = TileCfg<P>;
+  static constexpr int VS = T64 * VP * (int)sizeof(typename C::S);
+  static constexpr int MM = C::SMEM > VS ? C::SMEM : VS;
+  static constexpr int SMEM = FinCfg<P>::SMEM > MM ? FinCfg<P>::SMEM : MM;
+  static constexpr int BLOCKS = C::KIND == 0 ? 4 : C::KIND == 1 ? 2 : 3;   // per CU
+};
+
+// v[u][e] = the sum of the n partial tiles w, w + ps, .. at QC rows of this
+// thread, which blocks on other XCDs have written in this launch: stored and
+// loaded at agent scope, 8 bytes at a time.  (Plain accesses between
+// __threadfence() calls write back and invalidate a whole L2 per block:
+// measured 65 us instead of 30 per FP16X3 product at M = 1000.)
+template <class S, int QC>
+__device__ __forceinline__ void add_partials(const S *w, int64_t ps, int n, double (&v)[QC][4]) {
+  typedef S v4s __attribute__((ext_vector_type(4)));
+  constexpr int NW = (int)sizeof(v4s) / 8;
+  union Pack {
+    uint64_t u[NW];
+    v4s x;
+  };
+#pragma unroll
+  for (int q = 0; q < QC; ++q)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[q][e] = 0.0;
+#pragma unroll 2
+  for (int s = 0; s < n; ++s)
+#pragma unroll
+    for (int q = 0; q < QC; ++q) {
+      const S *p = w + s * ps + q * 16 * T64;
+      Pack t;
+#pragma unroll
+      for (int k = 0; k < NW; ++k)
+        t.u[k] = __hip_atomic_load((const uint64_t *)p + k, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[q][e] += (double)t.x[e];
+    }
+}
+
+template <class S>
+__device__ __forceinline__ void publish4(S *p, S a, S b, S c, S d) {
+  typedef S v4s __attribute__((ext_vector_type(4)));
+  constexpr int NW = (int)sizeof(v4s) / 8;
+  union Pack {
+    uint64_t u[NW];
+    v4s x;
+  } t;
+  t.x = v4s{a, b, c, d};
+#pragma unroll
+  for (int k = 0; k < NW; ++k)
+    __hip_atomic_store((uint64_t *)p + k, t.u[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+template <int P>
+__global__ __launch_bounds__(NTH, (TileKernel<P>::BLOCKS)) void k_tile(GemmArgs g) {
+  using C = TileCfg<P>;
+  using S = typename C::S;
+  __shared__ __attribute__((aligned(16))) char smem[TileKernel<P>::SMEM];
   if (g.status && *g.status != 0) return;   // the solve has stopped
 
-  // whole tile, or split s of a tail tile over K stages [kb, ke)
-  const int nk_all = (int)(g.Mp / MmaCfg<P>::KT);
+  const int nk_all = (int)(g.Mp / C::KT), nt = (int)(g.Mp / T64);
   int ti, tj, lin, split = -1, kb = 0, ke = nk_all;
-  if ((int)blockIdx.x < g.nfull) {
-    tile_of_block(blockIdx.x, g.nfull, g.nt, ti, tj, lin);
+  const int u = (int)blockIdx.x - g.nfull, ntail = ((int)gridDim.x - g.nfull) / g.nsplit;
+  if (u < 0) {
+    tile_of_block(blockIdx.x, g.nfull, nt, ti, tj, lin);
   } else {
     // split-major: the blocks in flight together cover the same K range of
     // consecutive tiles
-    const int u = (int)blockIdx.x - g.nfull;
-    const int ntail = ((int)gridDim.x - g.nfull) / g.nsplit;
     split = u / ntail;
     lin = g.nfull + u % ntail;
-    tile_of_index(lin, g.nt, ti, tj);
-    kb = split * nk_all / g.nsplit;
-    ke = (split + 1) * nk_all / g.nsplit;
+    tile_of_index(lin, nt, ti, tj);
+    kb = (int)((int64_t)split * nk_all / g.nsplit);
+    ke = (int)((int64_t)(split + 1) * nk_all / g.nsplit);
   }
-  const int64_t Mp = g.Mp, PS = g.pstride;
-  const int64_t arow0 = (int64_t)ti * TILE, brow0 = (int64_t)tj * TILE;
-  const T *__restrict__ Ag = (const T *)g.A;
-  const T *__restrict__ Bg = (const T *)g.B;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave >> 1, wn = wave & 1, l16 = lane & 15, lg = lane >> 4;
-
-  Acc acc0[4][4];
-  mma_tile<P>(Ag, Bg, arow0, brow0, Mp, PS, smem, g.fold, acc0, kb, ke);
-
+  tile_product<P>(g.A, g.B, (int64_t)ti * T64, (int64_t)tj * T64, g.Mp, smem, g.fold, kb, ke);
+  const int tid = threadIdx.x, c4 = (tid & 15) * 4, r0 = tid >> 4;
+  const S *V = (const S *)smem + r0 * VP + c4;
+  const int64_t ps = (int64_t)ntail * (T64 * T64);
+  const S *w0 = (const S *)g.ws + (int64_t)(lin - g.nfull) * (T64 * T64) + r0 * T64 + c4;
   if (split >= 0) {
-    // publish this split's partial tile; the last split to arrive adds all
-    // of them in split order (the sum does not depend on the arrival order)
-    // and runs the epilogue
-    const int t = lin - g.nfull;   // index among the split tiles
-    Acc *wsp = (Acc *)g.ws + ((int64_t)t * g.nsplit + split) * 16 * NTH;
+    S *w = (S *)w0 + split * ps;
 #pragma unroll
-    for (int bi = 0; bi < 4; ++bi)
-#pragma unroll
-      for (int bj = 0; bj < 4; ++bj) wsp[(bi * 4 + bj) * NTH + tid] = acc0[bi][bj];
-    __threadfence();
-    unsigned *last = (unsigned *)smem;   // the stage buffers are free
+    for (int q = 0; q < 4; ++q) {
+      const S *v = V + q * 16 * VP;
+      publish4(w + q * 16 * T64, v[0], v[1], v[2], v[3]);
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // out before the counter moves
     __syncthreads();
-    if (tid == 0) *last = (atomicAdd(g.cnt + t, 1u) == (unsigned)g.nsplit - 1);
+    unsigned *cnt = g.cnt + (lin - g.nfull), *last = (unsigned *)smem;
+    if (tid == 0) *last = atomicAdd(cnt, 1u) == (unsigned)g.nsplit - 1;
     __syncthreads();
     if (!*last) return;
     __syncthreads();   // flag read by all before the epilogue reuses smem
-    __threadfence();
-    const Acc *w0 = (const Acc *)g.ws + (int64_t)t * g.nsplit * 16 * NTH;
-#pragma unroll
-    for (int bi = 0; bi < 4; ++bi)
-#pragma unroll
-      for (int bj = 0; bj < 4; ++bj) {
-        double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
-#pragma unroll 4
-        for (int sp = 0; sp < g.nsplit; ++sp) {
-          const Acc v = w0[((int64_t)sp * 16 + bi * 4 + bj) * NTH + tid];
-          a0 += (double)v[0];
-          a1 += (double)v[1];
-          a2 += (double)v[2];
-          a3 += (double)v[3];
-        }
-        acc0[bi][bj] = Acc{(T)a0, (T)a1, (T)a2, (T)a3};
-      }
-    if (tid == 0) g.cnt[t] = 0u;   // ready for the next launch
+    if (tid == 0) *cnt = 0u;   // ready for the next launch
   }
-
-  // ------------------------------------------------------------ epilogue
-  const double S = E::PROD_SCALE;
-  const bool diag_tile = (ti == tj);
-  T *__restrict__ Og = (T *)g.out;
-  double rowacc[4][4], colacc[4], tacc = 0.0;
-#pragma unroll
-  for (int bi = 0; bi < 4; ++bi) {
-    colacc[bi] = 0.0;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) rowacc[bi][r] = 0.0;
-  }
-  double a_coef = 0.0, b_coef = 0.0, e_coef = 0.0;
-  if (g.mode == 1) update_coefs(g.method, g.coef[0], a_coef, b_coef, e_coef);
-
-  // The element inputs of BJC column blocks of a row block at a time are
-  // loaded before any of their stores: read per element after the stores
-  // before it, each would wait for them (the compiler cannot tell the output
-  // from the inputs), one memory round trip per element.  (FP64 loads half a
-  // row block: a whole one would spill.)
-  constexpr int BJC = sizeof(T) == 8 ? 1 : 4;
-  double rDj[4];
-#pragma unroll
-  for (int bj = 0; bj < 4; ++bj) rDj[bj] = g.rD[brow0 + wn * 64 + bj * 16 + l16];
-#pragma unroll
-  for (int bi = 0; bi < 4; ++bi) {
-    double rDi[4], s2i[4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int64_t i = arow0 + wm * 64 + bi * 16 + acc_row<KIND>(lg, r);
-      rDi[r] = g.rD[i];
-      s2i[r] = g.mode == 1 ? g.s2[i] : 0.0;
+  constexpr int QC = FinCfg<P>::QC;
+  finish_any<P>(g, ti, tj, lin, [&](int q0, double (&v)[QC][4]) {
+    if (split >= 0) {
+      add_partials(w0 + q0 * 16 * T64, ps, g.nsplit, v);
+      return;
     }
 #pragma unroll
-    for (int b0 = 0; b0 < 4; b0 += BJC) {
-      T dpb[BJC][4][NP], xpb[BJC][4][NP];
+    for (int u = 0; u < QC; ++u)
 #pragma unroll
-      for (int q = 0; q < BJC; ++q)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int64_t i = arow0 + wm * 64 + bi * 16 + acc_row<KIND>(lg, r);
-          const int64_t j = brow0 + wn * 64 + (b0 + q) * 16 + l16;
-#pragma unroll
-          for (int p = 0; p < NP; ++p) {
-            dpb[q][r][p] = Bg[p * PS + i * Mp + j];                        // D(i, j)
-            xpb[q][r][p] = g.mode == 1 ? Ag[p * PS + i * Mp + j] : T{};    // X2(i, j)
-          }
-        }
-#pragma unroll
-      for (int q = 0; q < BJC; ++q)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int bj = b0 + q;
-          const int64_t i = arow0 + wm * 64 + bi * 16 + acc_row<KIND>(lg, r);
-          const int64_t j = brow0 + wn * 64 + bj * 16 + l16;
-          if (diag_tile && i > j) continue;   // covered by the mirror of (j, i)
-          const double v = (double)acc0[bi][bj][r] * S;
-          const T *dp = dpb[q][r];
-          T op[NP];
-          double prod, diff;
-          if (g.mode == 0) {
-            // X2 = (D_enc + diag(rD))^2: exact diagonal-residual correction
-            double Dm, x2;
-            if (i == j) {
-              Dm = g.dg[i];
-              x2 = g.d2[i];
-            } else {
-              Dm = E::dec(dp);
-              x2 = v + Dm * (rDi[r] + rDj[bj]);
-            }
-            E::enc(x2, op);
-            const double x2m = (i == j) ? x2 : E::dec(op);
-            if (i == j) g.s2[i] = x2 - E::dec(op);
-            prod = x2m * Dm;
-            diff = x2m - Dm;
-          } else {
-            double Dm, dn;
-            if (i == j) {
-              Dm = g.dg[i];
-              dn = a_coef * Dm + b_coef * g.d2[i] + e_coef * g.d3[i];
-            } else {
-              Dm = E::dec(dp);
-              const double X2m = E::dec(xpb[q][r]);
-              // X3 = (X2_enc + diag(s2)) (D_enc + diag(rD))
-              const double x3 = v + X2m * rDj[bj] + s2i[r] * Dm;
-              dn = a_coef * Dm + b_coef * X2m + e_coef * x3;
-            }
-            E::enc(dn, op);
-            const double dnm = (i == j) ? dn : E::dec(op);
-            if (i == j) {
-              g.dg_new[i] = dn;
-              g.rD_new[i] = dn - E::dec(op);
-            }
-            prod = dnm * dnm;
-            diff = dnm - Dm;
-          }
-#pragma unroll
-          for (int p = 0; p < NP; ++p) {
-            Og[p * PS + i * Mp + j] = op[p];
-            if (i != j) Og[p * PS + j * Mp + i] = op[p];
-          }
-          rowacc[bi][r] += prod;
-          if (i != j) {
-            colacc[bj] += prod;
-            tacc += 2.0 * diff * diff;
-          } else {
-            tacc += diff * diff;
-          }
-        }
+      for (int e = 0; e < 4; ++e) v[u][e] = (double)V[(q0 + u) * 16 * VP + e];
+    // FP64 / FP32 results replace the products element by element; 16-bit
+    // ones lie elsewhere in the same LDS, so all products are read first
+    if constexpr (C::ES == 2) {
+      static_assert(QC == 4, "all rows at once");
+      __syncthreads();
     }
-  }
-
-  // lane reductions (fixed order): rows over the 16 lanes of a column group,
-  // columns over the 4 row groups, the tile scalar over the wave
-#pragma unroll
-  for (int bi = 0; bi < 4; ++bi)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      double v = rowacc[bi][r];
-      v += shfl_xor_d(v, 1);
-      v += shfl_xor_d(v, 2);
-      v += shfl_xor_d(v, 4);
-      v += shfl_xor_d(v, 8);
-      rowacc[bi][r] = v;
-    }
-#pragma unroll
-  for (int bj = 0; bj < 4; ++bj) {
-    double v = colacc[bj];
-    v += shfl_xor_d(v, 16);
-    v += shfl_xor_d(v, 32);
-    colacc[bj] = v;
-  }
-  tacc += shfl_xor_d(tacc, 1);
-  tacc += shfl_xor_d(tacc, 2);
-  tacc += shfl_xor_d(tacc, 4);
-  tacc += shfl_xor_d(tacc, 8);
-  tacc += shfl_xor_d(tacc, 16);
-  tacc += shfl_xor_d(tacc, 32);
-
-  double *rp = (double *)smem;    // [2 (wn)][128 rows]
-  double *cp = rp + 2 * TILE;     // [2 (wm)][128 cols]
-  double *tp = cp + 2 * TILE;     // [4 waves]
-  __syncthreads();                // main-loop LDS no longer in use
-  if (l16 == 0) {
-#pragma unroll
-    for (int bi = 0; bi < 4; ++bi)
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-        rp[wn * TILE + wm * 64 + bi * 16 + acc_row<KIND>(lg, r)] = rowacc[bi][r];
-  }
-  if (lg == 0) {
-#pragma unroll
-    for (int bj = 0; bj < 4; ++bj) cp[wm * TILE + wn * 64 + bj * 16 + l16] = colacc[bj];
-  }
-  if (lane == 0) tp[wave] = tacc;
-  __syncthreads();
-  if (tid < TILE) {
-    const double rs = rp[tid] + rp[TILE + tid];
-    const double cs = cp[tid] + cp[TILE + tid];
-    if (!diag_tile) {
-      g.part[(int64_t)tj * Mp + arow0 + tid] = rs;
-      g.part[(int64_t)ti * Mp + brow0 + tid] = cs;
-    } else {
-      g.part[(int64_t)ti * Mp + arow0 + tid] = rs + cs;
-    }
-  }
-  if (tid == 0) g.tpart[lin] = ((tp[0] + tp[1]) + tp[2]) + tp[3];
+  }, smem);
 }
 
 // ------------------------------------------------ 16-bit product kernel
@@ -311,8 +559,6 @@ __device__ __forceinline__ void pair_of_block(int b, int nt, int &ti, int &cp, i
   }
   ti = cp = 0;
 }
-
-typedef __attribute__((address_space(3))) void lds_void;
 
 constexpr int NW16 = 8;              // waves per block of the 16-bit kernel (2 per SIMD)
 constexpr int NTH16 = 64 * NW16;
@@ -637,7 +883,7 @@ __global__ __launch_bounds__(NTH16, 1) void k_gemm16(GemmArgs g) {
   const bool tvalid = tjj >= ti, dtile = tjj == ti;
   const int br = x >> 4, bc = x & 15;
   const int64_t i0 = arow0 + br * 8;
-  const double S = E::PROD_SCALE;
+  constexpr double S = 1.0 / (E::SC * E::SC);
   T *__restrict__ Og = (T *)g.out;
   double a_coef = 0.0, b_coef = 0.0, e_coef = 0.0;
   if (g.mode == 1) update_coefs(g.method, g.coef[0], a_coef, b_coef, e_coef);
@@ -1046,10 +1292,6 @@ __global__ __launch_bounds__(256) void k_init(InitArgs a) {
 // wave order.  Per-block sums of out and of extra; the last block to finish
 // adds the block sums and the tile partials in a fixed order and runs the
 // scalar step for this point of the iteration.
-__device__ __forceinline__ double ld_agent(const double *p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
 __global__ __launch_bounds__(256) void k_reduce(RedArgs a) {
   __shared__ double rq[4][64], s1[256], s2[256], s3[256];
   __shared__ int is_last;
@@ -1115,80 +1357,7 @@ __global__ __launch_bounds__(256) void k_reduce(RedArgs a) {
   }
   if (tid != 0) return;
   *a.counter = 0u;
-  Scalars *sc = a.sc;
-  const double sum_out = s1[0], sum_extra = s2[0], sum_tiles = s3[0];
-  if (a.mode == 0) {            // after the initial guess
-    sc->t2 = sum_out;
-    sc->t1 = sum_extra;
-  } else if (a.mode == 1) {     // after D^2: decide and form c
-    const double t1 = sc->t1, t2 = sc->t2, t3 = sum_out, om = sum_tiles;
-    const double ddbar = t1 - t2;
-    int status = 0;
-    double c = NAN;
-    if (!isfinite(t1) || !isfinite(t2) || !isfinite(om)) {
-      status = 3;
-    } else if (fabs(ddbar) <= a.tol_ddbar || sqrt(om) <= a.tol_idem) {
-      status = 1;
-    } else if (a.iter >= a.max_iter) {
-      status = 2;
-    } else {
-      if (ddbar > 0.0) c = (t2 - t3) / ddbar;
-      // Tr(D Dbar) <= 0 or c outside [0, 1] is a runaway, unless |Tr(D Dbar)|
-      // is already within the encoding's rounding floor, where it (and c)
-      // is rounding noise and stops decreasing: the iterate is then as
-      // idempotent as the encoding allows and the solve stops there.
-      const bool bad = !(ddbar > 0.0) || !isfinite(c) || c < 0.0 || c > 1.0;
-      const bool stalled = !a.recheck && fabs(ddbar) >= sc->prev_ddbar;
-      if ((bad || stalled) && fabs(ddbar) <= a.floor_ddbar) status = 4;
-      else if (bad) status = 3;
-    }
-    if (!a.recheck) sc->prev_ddbar = fabs(ddbar);
-    if (status != 0) sc->iter = a.iter;
-    sc->t3 = t3;
-    sc->omega = om;
-    sc->c = c;
-    sc->status = status;
-    double *h = a.hist + (int64_t)a.iter * 9;
-    const double gamma = 1.0 / 3.0 - 2.0 / 3.0 * c;
-    h[0] = a.iter; h[1] = t1; h[2] = t2; h[5] = om;
-    if (status == 0) {
-      h[3] = t3; h[4] = c; h[6] = gamma;
-      h[7] = om - gamma * (3.0 * t2 - 2.0 * t3 - a.N);
-    } else {
-      h[3] = h[4] = h[6] = h[7] = NAN;
-    }
-    h[8] = NAN;
-  } else {                      // after the update: traces of D_{n+1}
-    sc->t2 = sum_out;
-    sc->t1 = sum_extra;
-    sc->step = sum_tiles;
-    a.hist[(int64_t)a.iter * 9 + 8] = sqrt(sum_tiles);
-    if (!a.early_stop) return;
-    // The stops of the mode-1 decision that need only T1 and T2 of D_{n+1},
-    // taken here so that the square of the last iterate is never formed:
-    // |Tr(D Dbar)| within tol_ddbar, or within the rounding floor while not
-    // decreasing or not positive (below max_iter, where mode 1 would report
-    // max_iter first).  Everything else (non-finite traces, c outside
-    // [0, 1], max_iter) is left to mode 1, which would take the same
-    // decision on the same traces.
-    const double t1 = sum_extra, t2 = sum_out, ddbar = t1 - t2;
-    const int nx = a.iter + 1;
-    int status = 0;
-    if (isfinite(t1) && isfinite(t2)) {
-      if (fabs(ddbar) <= a.tol_ddbar) status = 1;
-      else if (nx < a.max_iter && (!(ddbar > 0.0) || fabs(ddbar) >= sc->prev_ddbar) &&
-               fabs(ddbar) <= a.floor_ddbar)
-        status = 4;
-    }
-    if (status == 0) return;
-    sc->status = status;
-    sc->iter = nx;
-    sc->on_traces = 1;
-    sc->omega = NAN;
-    double *h = a.hist + (int64_t)nx * 9;
-    h[0] = nx; h[1] = t1; h[2] = t2;
-    h[3] = h[4] = h[5] = h[6] = h[7] = h[8] = NAN;
-  }
+  scalar_step(a, s1[0], s2[0], s3[0]);
 }
 
 // ------------------------------------------------------------------ output
@@ -1259,6 +1428,7 @@ __global__ __launch_bounds__(256) void k_convert(int pb, const void *in, const d
   // rows on the x dimension of the grid (no 64K limit), 256 columns per block on y
   const int64_t i = blockIdx.x;
   const int64_t j = (int64_t)blockIdx.y * 256 + threadIdx.x;
+  if (j >= Mp) return;
   const double x = (i == j) ? diag[i] : dec_at<PA>(in, i, j, Mp);
   const double xe = enc_any(pb, out, i, j, Mp, x);
   if (i == j) resid[i] = x - xe;
@@ -1266,7 +1436,7 @@ __global__ __launch_bounds__(256) void k_convert(int pb, const void *in, const d
 
 hipError_t launch_convert(int pa, int pb, const void *in, const double *diag, void *out,
                           double *resid, int64_t Mp, hipStream_t st) {
-  const dim3 grid((unsigned)Mp, (unsigned)(Mp / 256));
+  const dim3 grid((unsigned)Mp, (unsigned)((Mp + 255) / 256));
   switch (pa) {
     case GCP_FP64: k_convert<GCP_FP64><<<grid, 256, 0, st>>>(pb, in, diag, out, resid, Mp); break;
     case GCP_FP32: k_convert<GCP_FP32><<<grid, 256, 0, st>>>(pb, in, diag, out, resid, Mp); break;
@@ -1282,24 +1452,27 @@ hipError_t launch_convert(int pa, int pb, const void *in, const double *diag, vo
 
 // ---------------------------------------------------------------- dispatch
 template <int P>
-static hipError_t launch_gemm_p(const GemmArgs &g, int ntiles, hipStream_t st) {
-  if constexpr (Enc<P>::KIND >= 2)
-    k_gemm16<P><<<gemm16_blocks(g), NTH16, 0, st>>>(g);
-  else
-    k_gemm<P><<<g.nfull + (ntiles - g.nfull) * g.nsplit, NTH, 0, st>>>(g);
+static hipError_t launch_gemm_p(const GemmArgs &g, hipStream_t st) {
+  const int nt = (int)(g.Mp / T64), ntail = nt * (nt + 1) / 2 - g.nfull;
+  if constexpr (Enc<P>::KIND >= 2) {
+    if (g.path == PATH_PAIR) {
+      k_gemm16<P><<<gemm16_blocks(g), NTH16, 0, st>>>(g);
+      return hipGetLastError();
+    }
+  }
+  k_tile<P><<<g.nfull + ntail * g.nsplit, NTH, 0, st>>>(g);
   return hipGetLastError();
 }
 
 hipError_t launch_gemm(int prec, const GemmArgs &g, hipStream_t st) {
-  const int ntiles = g.nt * (g.nt + 1) / 2;
   switch (prec) {
-    case GCP_FP64: return launch_gemm_p<GCP_FP64>(g, ntiles, st);
-    case GCP_FP32: return launch_gemm_p<GCP_FP32>(g, ntiles, st);
-    case GCP_BF16: return launch_gemm_p<GCP_BF16>(g, ntiles, st);
-    case GCP_FP16: return launch_gemm_p<GCP_FP16>(g, ntiles, st);
-    case GCP_BF16X3: return launch_gemm_p<GCP_BF16X3>(g, ntiles, st);
-    case GCP_FP16X3: return launch_gemm_p<GCP_FP16X3>(g, ntiles, st);
-    case GCP_BF16X6: return launch_gemm_p<GCP_BF16X6>(g, ntiles, st);
+    case GCP_FP64: return launch_gemm_p<GCP_FP64>(g, st);
+    case GCP_FP32: return launch_gemm_p<GCP_FP32>(g, st);
+    case GCP_BF16: return launch_gemm_p<GCP_BF16>(g, st);
+    case GCP_FP16: return launch_gemm_p<GCP_FP16>(g, st);
+    case GCP_BF16X3: return launch_gemm_p<GCP_BF16X3>(g, st);
+    case GCP_FP16X3: return launch_gemm_p<GCP_FP16X3>(g, st);
+    case GCP_BF16X6: return launch_gemm_p<GCP_BF16X6>(g, st);
   }
   return hipErrorInvalidValue;
 }

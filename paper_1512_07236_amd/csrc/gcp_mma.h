@@ -1,13 +1,14 @@
 // gcp_mma.h -- MFMA building blocks shared by the forward and adjoint kernels.
 //
-// A 128 x 128 output tile of an A * B^T product of row panels (A rows
-// arow0.., B rows brow0.., both Mp x Mp row-major, K contiguous) computed by
-// 4 waves in a 2 x 2 grid of 64 x 64, each a 4 x 4 grid of 16 x 16 MFMA
-// blocks.  FP64 uses v_mfma_f64_16x16x4f64, FP32 v_mfma_f32_16x16x4f32.
+// A 64 x 64 output tile of an A * B^T product of row panels (A rows arow0..,
+// B rows brow0.., both Mp x Mp row-major, K contiguous) computed by 4 waves
+// in 16 x 16 MFMA blocks.
 #pragma once
 
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include <type_traits>
 
 #include "gcp_encode.h"
 #include "gcp_kernels.h"
@@ -20,8 +21,9 @@ typedef _Float16 v8h __attribute__((ext_vector_type(8)));
 typedef __bf16 v8b __attribute__((ext_vector_type(8)));
 typedef uint32_t v4u __attribute__((ext_vector_type(4)));
 
-constexpr int TILE = 128;   // output tile edge
-constexpr int NTH = 256;    // threads per tile: 4 waves in a 2 x 2 grid of 64 x 64
+constexpr int TILE = 128;   // output tile edge of the 16-bit pair kernel
+constexpr int T64 = 64;     // edge of the tiles that the epilogues work on
+constexpr int NTH = 256;    // threads per tile: 4 waves
 
 template <int KIND> struct AccType { using type = v4f; };
 template <> struct AccType<0> { using type = v4d; };
@@ -53,37 +55,81 @@ __device__ __forceinline__ v4f mfma16(v4u a, v4u b, v4f c) {
 
 __device__ __forceinline__ double shfl_xor_d(double v, int m) { return __shfl_xor(v, m, 64); }
 
+// Sums over lanes in a fixed order, by rotations inside the rows of 16 lanes
+// (DPP) and swaps of rows and half waves: no LDS round trip per step, as a
+// general shuffle takes.  row_sum leaves the sum of its row of 16 lanes in
+// every lane, wave_sum that of the wave.
+template <int CTRL>
+__device__ __forceinline__ double dpp_d(double v) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, false);
+  return __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ double row_sum(double v) {
+  v += dpp_d<0x128>(v);   // row_ror:8
+  v += dpp_d<0x124>(v);
+  v += dpp_d<0x122>(v);
+  v += dpp_d<0x121>(v);
+  return v;
+}
+// v + v of the lane 16 (32) away, by the row and half-wave swaps.
+__device__ __forceinline__ double swap16_sum(double v) {
+  const auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(v), __double2loint(v), false, false);
+  const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(v), __double2hiint(v), false, false);
+  return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+}
+__device__ __forceinline__ double swap32_sum(double v) {
+  const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(v), __double2loint(v), false, false);
+  const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(v), __double2hiint(v), false, false);
+  return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+}
+__device__ __forceinline__ double wave_sum(double v) {
+  return swap32_sum(swap16_sum(row_sum(v)));
+}
+
+typedef double v2d __attribute__((ext_vector_type(2)));
+typedef __attribute__((address_space(3))) void lds_void;
+
 // Upper-triangle tiles are ordered in G x G groups of the tile grid (the
 // diagonal groups are triangular), row-major inside a group; tile_of_index
-// gives tile L of that order.
+// gives tile L of that order in closed form (a search over the groups took
+// up to a thousand scalar steps per block).
 constexpr int TILE_GROUP = 8;
 
 __device__ __forceinline__ void tile_of_index(int L, int nt, int &ti, int &tj) {
-  const int ng = (nt + TILE_GROUP - 1) / TILE_GROUP;
-  for (int gr = 0; gr < ng; ++gr) {
-    const int r0 = gr * TILE_GROUP, r1 = min(nt, r0 + TILE_GROUP);
-    for (int gc = gr; gc < ng; ++gc) {
-      const int c0 = gc * TILE_GROUP, c1 = min(nt, c0 + TILE_GROUP);
-      for (int t = r0; t < r1; ++t) {
-        const int first = (gc == gr) ? t : c0;   // diagonal group: tj >= ti
-        const int len = c1 - first;
-        if (L < len) {
-          ti = t;
-          tj = first + L;
-          return;
-        }
-        L -= len;
-      }
+  constexpr int G = TILE_GROUP;
+  // group row gr: rows gr G .. ; the rows before row s hold s nt - s (s - 1)/2 tiles
+  auto before = [&](int gr) {
+    const int s = gr * G;
+    return s * nt - s * (s - 1) / 2;
+  };
+  const float q = 2.0f * nt + 1.0f;
+  int gr = (int)((q - sqrtf(fmaxf(q * q - 8.0f * L, 0.0f))) * (0.5f / G));
+  while (gr > 0 && before(gr) > L) --gr;
+  while ((gr + 1) * G < nt && before(gr + 1) <= L) ++gr;
+  int rem = L - before(gr);
+  const int r0 = gr * G, rows = min(G, nt - r0), diag = rows * (rows + 1) / 2;
+  if (rem < diag) {
+    int t = 0;
+    while (rem >= rows - t) {
+      rem -= rows - t;
+      ++t;
     }
+    ti = r0 + t;
+    tj = ti + rem;
+    return;
   }
-  ti = tj = 0;   // not reached for L < nt (nt + 1) / 2
+  rem -= diag;   // full groups of G rows (the last may have fewer columns)
+  const int k = rem / (G * G), c0 = (gr + 1 + k) * G, w = min(G, nt - c0);
+  rem -= k * G * G;
+  ti = r0 + rem / w;
+  tj = c0 + rem % w;
 }
 
 // Tile of block b of the first nblk blocks, which cover tiles 0 .. nblk-1 of
 // that order.  Blocks are dispatched round-robin over the 8 XCDs; each XCD
-// gets a contiguous run of the order, so the ~64 tiles resident on one XCD
-// at a time fall in one group and read about 2G row panels, which its L2
-// serves.
+// gets a contiguous run of the order, so the tiles resident on one XCD at a
+// time fall in few groups and read few row panels, which its L2 serves.
 __device__ __forceinline__ void tile_of_block(int b, int nblk, int nt, int &ti, int &tj, int &lin) {
   const int xcd = b & 7, loc = b >> 3, q = nblk >> 3, r = nblk & 7;
   lin = xcd * q + (xcd < r ? xcd : r) + loc;
@@ -94,111 +140,262 @@ __device__ __forceinline__ void tile_of_block(int b, int nt, int &ti, int &tj, i
   tile_of_block(b, nt * (nt + 1) / 2, nt, ti, tj, lin);
 }
 
-// LDS geometry of the FP64 / FP32 tile product: K stages of 128 bytes per
-// row, double-buffered through registers, one 16-byte chunk of row padding.
-template <int P> struct MmaCfg {
+// Geometry of the tile product.  A K stage is one 128-byte segment of every
+// panel row (16 FP64, 32 FP32, 64 values of one 16-bit plane, or 32 of two
+// interleaved planes); three planes take a 64-byte segment of each (32
+// values).
+//
+// Wave layout.  16-bit: 2 x 2 waves of 2 x 2 MFMA blocks.  FP64 / FP32: waves
+// 0 and 1 take the upper and lower 32 rows, 2 x 4 blocks each, of the first
+// half of every stage's K values, waves 2 and 3 of the second half.  With
+// 2 x 2 blocks per wave (four accumulators) FP64 products alone reach 67
+// TFLOP/s, however many waves there are; with eight accumulators 78.
+//
+// Stages in LDS: FP64 runs best with four blocks per CU, FP32 with two (the
+// product loop alone, in TFLOP/s: FP32 139 with two blocks, 89 with three;
+// FP64 71.6 and 72.5); FP32 uses the LDS of the other two for a deeper ring.
+template <int P> struct TileCfg {
   using T = typename Enc<P>::T;
-  static constexpr int NP = Enc<P>::NP, ES = (int)sizeof(T);
-  static constexpr int KT = 128 / ES;              // K per LDS stage
-  static constexpr int EPC = 16 / ES;              // elements per 16-byte chunk
-  static constexpr int LDR = KT + EPC;             // LDS row stride
-  static constexpr int CPR = KT / EPC;             // chunks per row per plane
-  static constexpr int CPT = TILE * CPR / NTH;     // chunks per thread per operand per plane
-  static constexpr int SMEM = 2 * NP * TILE * LDR; // elements of LDS
+  static constexpr int NP = Enc<P>::NP, KIND = Enc<P>::KIND, ES = (int)sizeof(T);
+  static constexpr int TE = T64;                           // tile edge
+  static constexpr int KS = KIND <= 1 ? 2 : 1;             // wave groups along K
+  static constexpr int WA = TE / 32, WB = WA * KS;         // MFMA blocks per wave
+  static constexpr bool R128 = NP <= 2;
+  static constexpr int KT = R128 ? 128 / ES / NP : 32;     // K values per stage
+  static constexpr int ROWB = R128 ? 128 : 64 * NP;        // bytes per panel row per stage
+  static constexpr int STAGE = 2 * TE * ROWB;              // bytes per stage
+  static constexpr int NBUF = KIND == 1 ? 4 : 2;           // stages in LDS
+  static constexpr int SMEM = NBUF * STAGE;
+  static constexpr int LPS = STAGE / 1024 / 4;             // 1 KiB loads per stage per wave
+  static constexpr int NX = R128 ? 2 : NP;                 // 16-byte fragments per row
+  static constexpr int NXW = NX / KS;                      // ... that a wave reads
+  static_assert(KS == 1 || NP == 1, "K halves of one-plane stages");
+  using Acc = typename AccType<KIND>::type;
+  using S = std::conditional_t<KIND == 0, double, float>;
 };
 
-// acc[bi][bj] = A[arow0 + wm*64 + bi*16 .. , K] * B[brow0 + wn*64 + bj*16 .., K]^T
-// over the K stages [kb, ke) of KT values each (ke < 0: the whole K = Mp).
-// Planes of a multi-plane operand are PS elements apart (FP64 / FP32 storage
-// has one).  FP32 accumulates each run of `fold` K stages in a chunk
-// accumulator and adds it into a running total (fold <= 0: fp32_fold(Mp));
-// FP64 keeps one accumulator.  Ends with a barrier: smem is free.
-template <int P>
-__device__ __forceinline__ void mma_tile(const typename Enc<P>::T *__restrict__ Ag,
-                                         const typename Enc<P>::T *__restrict__ Bg,
-                                         int64_t arow0, int64_t brow0, int64_t Mp, int64_t PS,
-                                         typename Enc<P>::T *smem, int fold,
-                                         typename AccType<Enc<P>::KIND>::type (&acc)[4][4],
-                                         int kb = 0, int ke = -1) {
-  using C = MmaCfg<P>;
-  using T = typename C::T;
-  constexpr int NP = C::NP, KT = C::KT, EPC = C::EPC, LDR = C::LDR, CPR = C::CPR, CPT = C::CPT;
-  static_assert(Enc<P>::KIND <= 1, "16-bit encodings use the paired-tile kernel");
-  using Acc = typename AccType<Enc<P>::KIND>::type;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave >> 1, wn = wave & 1, l16 = lane & 15, lg = lane >> 4;
-  T *As = smem;
-  T *Bs = smem + NP * TILE * LDR;
+// Bare s_barrier: __syncthreads() would add a workgroup release fence, which
+// waits for every outstanding LDS-DMA load.  The empty asm statements keep
+// the compiler from moving LDS accesses across it, the scheduling barriers
+// keep the matrix products on their side of it; the waits before it provide
+// the hardware ordering.
+__device__ __forceinline__ void bare_barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("" ::: "memory");
+}
 
-  v4u ra[NP][CPT], rb[NP][CPT];
-  auto gload = [&](int kt) {
-    const int64_t k0 = (int64_t)kt * KT;
+// acc[bi][bj] = rows of A x rows of B over the K stages [kb, ke).  Lane l of a
+// wave holds row wrow + bi*16 + l%16 and the four columns wcol + bj*16 +
+// acc_row<KIND>(l/16, r) of the tile, with (wrow, wcol) from tile_origin.
+//
+// FP32 and the 16-bit encodings add all products of `fold` stages into a
+// chunk accumulator and that into a running total; FP64 keeps one
+// accumulator.  Ends with a barrier: smem is free.
+//
+// Panels go from global memory straight to LDS (16 bytes per lane, one wave
+// instruction fills 1 KiB).  In 128-byte rows chunk c sits at slot c ^ (R % 8)
+// and a lane reads whole 16-byte chunks (two FP64 or four FP32 values of K,
+// the same ones of A and B, so their order inside the stage does not
+// matter), which reads LDS without bank conflicts; 64-byte rows use slot
+// c ^ ((R >> 1) ^ (R >> 3)) % 4.
+template <class C>
+__device__ __forceinline__ void tile_origin(int wave, int &wrow, int &wcol) {
+  wrow = (C::KS == 1 ? wave >> 1 : wave & 1) * 16 * C::WA;
+  wcol = C::KS == 1 ? (wave & 1) * 16 * C::WB : 0;
+}
+
+template <class C, int P>
+__device__ __forceinline__ void tile_mma(const void *A, const void *B, int64_t arow0,
+                                         int64_t brow0, int64_t Mp, char *smem, int fold, int kb,
+                                         int ke, typename C::Acc (&acc)[C::WA][C::WB]) {
+  using Acc = typename C::Acc;
+  constexpr int TE = C::TE, LPS = C::LPS, NX = C::NXW, KIND = C::KIND, WA = C::WA, WB = C::WB;
+  constexpr bool R128 = C::R128;
+  // The loop keeps its vector instructions to the products, the fragment
+  // reads and the loads: FP64 products and vector instructions do not overlap
+  // on a SIMD, so every address instruction costs product time.  Loads take a
+  // scalar base that advances and a fixed 32-bit lane offset; fragments a
+  // fixed LDS base with immediate offsets (two stages are unrolled).
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l16 = lane & 15, lg = lane >> 4, kg = C::KS == 1 ? 0 : wave >> 1;
+  int wrow, wcol;
+  tile_origin<C>(wave, wrow, wcol);
+  const int64_t rowb = Mp * C::NP * C::ES;       // bytes per panel row
+  const char *Ab = (const char *)A + arow0 * rowb, *Bb = (const char *)B + brow0 * rowb;
+
+  // load q of a stage: rows of one panel (R128: the first half of the loads
+  // fills A), swizzled chunk
+  constexpr int PB = R128 ? 1 : 2 * TE / 16;   // loads per plane (three planes)
+  uint32_t voff[LPS];
 #pragma unroll
-    for (int p = 0; p < NP; ++p)
+  for (int q = 0; q < LPS; ++q) {
+    const int blk = wave + 4 * q;
+    if constexpr (R128) {
+      const int R = (q < LPS / 2 ? blk : blk - TE / 8) * 8 + (lane >> 3);   // row in its panel
+      voff[q] = (uint32_t)(R * rowb) + ((lane & 7) ^ (R & 7)) * 16;
+    } else {
+      const int p = blk / PB, Rl = blk % PB * 16 + (lane >> 2), R = Rl & (TE - 1);
+      voff[q] = (uint32_t)(R * rowb) + p * 64 + ((lane & 3) ^ (((Rl >> 1) ^ (Rl >> 3)) & 3)) * 16;
+    }
+  }
+  auto issue = [&](int kt, char *st) {
+    const char *pa = Ab + (int64_t)kt * C::ROWB, *pb = Bb + (int64_t)kt * C::ROWB;
 #pragma unroll
-      for (int c = 0; c < CPT; ++c) {
-        const int ch = tid + c * NTH, row = ch / CPR, kc = ch % CPR;
-        ra[p][c] = *(const v4u *)(Ag + p * PS + (arow0 + row) * Mp + k0 + kc * EPC);
-        rb[p][c] = *(const v4u *)(Bg + p * PS + (brow0 + row) * Mp + k0 + kc * EPC);
-      }
+    for (int q = 0; q < LPS; ++q) {
+      const int blk = wave + 4 * q;
+      const bool isA = R128 ? q < LPS / 2 : blk % PB < TE / 16;
+      const char *src = (isA ? pa : pb) + voff[q];
+      char *dst = st + (R128 ? blk * 1024 : (blk / PB * 2 * TE + blk % PB * 16) * 64);
+      __builtin_amdgcn_global_load_lds((const void *)src, (lds_void *)dst, 16, 0, 0);
+    }
   };
-  auto swrite = [&]() {
-#pragma unroll
-    for (int p = 0; p < NP; ++p)
-#pragma unroll
-      for (int c = 0; c < CPT; ++c) {
-        const int ch = tid + c * NTH, row = ch / CPR, kc = ch % CPR;
-        *(v4u *)(As + (p * TILE + row) * LDR + kc * EPC) = ra[p][c];
-        *(v4u *)(Bs + (p * TILE + row) * LDR + kc * EPC) = rb[p][c];
-      }
+  // fragment x of MFMA row block b of this wave (panel rows rb ..)
+  auto frag = [&](const char *st, int rb, int b, int x) -> v4u {
+    const int R = rb + b * 16 + l16;
+    if constexpr (R128)   // R % 8 does not depend on b
+      return *(const v4u *)(st + ((rb + l16) * 128 + (((kg + x) * 4 + lg) ^ (l16 & 7)) * 16) + b * 2048);
+    else
+      return *(const v4u *)(st + (x * 2 * TE + R) * 64 + (lg ^ (((R >> 1) ^ (R >> 3)) & 3)) * 16);
   };
 
-  constexpr bool FOLD = Enc<P>::KIND == 1;
-  Acc tot[4][4];
+  constexpr bool FOLD = KIND != 0;
+  Acc tot[WA][WB];
 #pragma unroll
-  for (int bi = 0; bi < 4; ++bi)
+  for (int bi = 0; bi < WA; ++bi)
 #pragma unroll
-    for (int bj = 0; bj < 4; ++bj) acc[bi][bj] = tot[bi][bj] = Acc{};
+    for (int bj = 0; bj < WB; ++bj) acc[bi][bj] = tot[bi][bj] = Acc{};
 
-  const int nk = ke < 0 ? (int)(Mp / KT) : ke;
-  const int f = fold > 0 ? fold : fp32_fold(Mp);
-  gload(kb);
-  swrite();
-  __syncthreads();
-  for (int kt = kb; kt < nk; ++kt) {
-    if (kt + 1 < nk) gload(kt + 1);
+  // Products of a stage, largest first: split encodings pair the planes.
+  constexpr int NPR = C::NP == 1 ? 2 : Enc<P>::NPROD;
+  constexpr int PA[6] = {0, 0, 1, 1, 0, 2};
+  constexpr int PB2[6] = {0, 1, 0, 1, 2, 0};
+
+  int left = fold;   // stages until the next fold
+  // s_waitcnt immediate: vmcnt <= the loads of the PD - 1 stages after the one
+  // waited for, lgkmcnt 0, expcnt not waited on
+  constexpr int PD = C::NBUF - 1, AHEAD = (PD - 1) * LPS;
+  static_assert(AHEAD <= 63, "vmcnt range");
+  constexpr int WAIT = (AHEAD & 0xF) | ((AHEAD >> 4) << 14) | (0x7 << 4);
+  auto stage = [&](int kt, int buf) {
+    const char *st = smem + buf * C::STAGE;
+    if (PD > 1 && kt + PD - 1 < ke)
+      __builtin_amdgcn_s_waitcnt(WAIT);
+    else
+      __builtin_amdgcn_s_waitcnt(0);
+    // this wave's loads of stage kt have landed; after the barrier everyone's
+    // have, and the buffer of stage kt - 1 is free
+    bare_barrier();
+    v4u af[WA][NX], bf[WB][NX];
 #pragma unroll
-    for (int ks = 0; ks < KT / 4; ++ks) {
-      T bf[4];
+    for (int x = 0; x < NX; ++x) {
 #pragma unroll
-      for (int bj = 0; bj < 4; ++bj) bf[bj] = Bs[(wn * 64 + bj * 16 + l16) * LDR + ks * 4 + lg];
+      for (int b = 0; b < WA; ++b) af[b][x] = frag(st, wrow, b, x);
 #pragma unroll
-      for (int bi = 0; bi < 4; ++bi) {
-        const T af = As[(wm * 64 + bi * 16 + l16) * LDR + ks * 4 + lg];
+      for (int b = 0; b < WB; ++b) bf[b][x] = frag(st, TE + wcol, b, x);
+    }
+    // the fragment reads go out before the loads (which take long to issue),
+    // and those before the first product
+    __builtin_amdgcn_sched_barrier(0);
+    if (kt + PD < ke) issue(kt + PD, smem + (buf + PD) % C::NBUF * C::STAGE);
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (KIND == 0) {
 #pragma unroll
-        for (int bj = 0; bj < 4; ++bj) acc[bi][bj] = mfma(af, bf[bj], acc[bi][bj]);
+      for (int x = 0; x < NX; ++x)
+#pragma unroll
+        for (int e = 0; e < 2; ++e)
+#pragma unroll
+          for (int bi = 0; bi < WA; ++bi)
+#pragma unroll
+            for (int bj = 0; bj < WB; ++bj)
+              acc[bi][bj] = mfma(__builtin_bit_cast(v2d, bf[bj][x])[e],
+                                 __builtin_bit_cast(v2d, af[bi][x])[e], acc[bi][bj]);
+    } else if constexpr (KIND == 1) {
+#pragma unroll
+      for (int x = 0; x < NX; ++x)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int bi = 0; bi < WA; ++bi)
+#pragma unroll
+            for (int bj = 0; bj < WB; ++bj)
+              acc[bi][bj] = mfma(__builtin_bit_cast(v4f, bf[bj][x])[e],
+                                 __builtin_bit_cast(v4f, af[bi][x])[e], acc[bi][bj]);
+    } else {
+#pragma unroll
+      for (int pr = 0; pr < NPR; ++pr)
+#pragma unroll
+        for (int bi = 0; bi < WA; ++bi)
+#pragma unroll
+          for (int bj = 0; bj < WB; ++bj) {
+            const int xa = C::NP == 1 ? pr : PA[pr], xb = C::NP == 1 ? pr : PB2[pr];
+            acc[bi][bj] = mfma16<KIND>(bf[bj][xb], af[bi][xa], acc[bi][bj]);
+          }
+    }
+    if constexpr (FOLD) {
+      if (--left == 0 || kt + 1 == ke) {
+        left = fold;
+#pragma unroll
+        for (int bi = 0; bi < WA; ++bi)
+#pragma unroll
+          for (int bj = 0; bj < WB; ++bj) {
+            tot[bi][bj] += acc[bi][bj];
+            acc[bi][bj] = Acc{};
+          }
       }
     }
-    if (FOLD && ((kt - kb + 1) % f == 0 || kt == nk - 1)) {
+  };
 #pragma unroll
-      for (int bi = 0; bi < 4; ++bi)
+  for (int s = 0; s < PD; ++s)
+    if (kb + s < ke) issue(kb + s, smem + s * C::STAGE);
+  for (int kt = kb; kt < ke; kt += C::NBUF) {
 #pragma unroll
-        for (int bj = 0; bj < 4; ++bj) {
-          tot[bi][bj] += acc[bi][bj];
-          acc[bi][bj] = Acc{};
-        }
-    }
-    __syncthreads();
-    if (kt + 1 < nk) {
-      swrite();
-      __syncthreads();
-    }
+    for (int s = 0; s < C::NBUF; ++s)
+      if (kt + s < ke) stage(kt + s, s);
   }
   if constexpr (FOLD) {
 #pragma unroll
-    for (int bi = 0; bi < 4; ++bi)
+    for (int bi = 0; bi < WA; ++bi)
 #pragma unroll
-      for (int bj = 0; bj < 4; ++bj) acc[bi][bj] = tot[bi][bj];
+      for (int bj = 0; bj < WB; ++bj) acc[bi][bj] = tot[bi][bj];
+  }
+  __syncthreads();
+}
+
+// The same with the whole 64 x 64 tile as the result, in LDS: V[row][col] with
+// a row pitch of VP elements (a product of the K halves adds the second
+// half's totals to the first's).  Ends with a barrier.
+constexpr int VP = T64 + 1;
+
+template <int P>
+__device__ __forceinline__ void tile_product(const void *A, const void *B, int64_t arow0,
+                                             int64_t brow0, int64_t Mp, char *smem, int fold,
+                                             int kb, int ke) {
+  using C = TileCfg<P>;
+  typename C::Acc acc[C::WA][C::WB];
+  tile_mma<C, P>(A, B, arow0, brow0, Mp, smem, fold, kb, ke, acc);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l16 = lane & 15, lg = lane >> 4;
+  int wrow, wcol;
+  tile_origin<C>(wave, wrow, wcol);
+  typename C::S *V = (typename C::S *)smem + (wrow + l16) * VP + wcol;
+  auto each = [&](auto &&f) {
+#pragma unroll
+    for (int bi = 0; bi < C::WA; ++bi)
+#pragma unroll
+      for (int bj = 0; bj < C::WB; ++bj)
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          f(V[bi * 16 * VP + bj * 16 + acc_row<C::KIND>(lg, r)], acc[bi][bj][r]);
+  };
+  using S = typename C::S;
+  if (C::KS == 1 || wave >= 2) each([](S &v, S x) { v = x; });
+  __syncthreads();
+  if constexpr (C::KS == 2) {
+    if (wave < 2) each([](S &v, S x) { v = x + v; });
+    __syncthreads();
   }
 }
 

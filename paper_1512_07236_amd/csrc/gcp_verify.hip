@@ -19,118 +19,96 @@
 
 namespace gcp {
 
-// MODE 0: D D over upper tiles, per-tile sums of w_ij (X_ij - D_ij)^2 (no
-// store).  MODE 1: H D over all tiles (rows of H against rows of D), stored.
+// One 64 x 64 upper tile (ti <= tj) of one product per block, sums over the
+// tile's elements with the mirrored ones (w_ij = 2 off the diagonal).
+//   MODE 0: X = D D.  Sums of w (X - D)^2, w D H, w D^2 and the trace of D.
+//   MODE 1: H D - D H, both products over the same panels, (D H)_ij being
+//           (H D)_ji: the sum of w ((H D)_ij - (H D)_ji)^2.  Neither product
+//           is stored.
+// The tile sums go to tpart[5][ntri].
 template <int MODE>
-__global__ __launch_bounds__(NTH, 2) void k_vgemm(VerifyArgs a) {
-  using T = double;
-  __shared__ __attribute__((aligned(16))) T smem[MmaCfg<GCP_FP64>::SMEM];
+__device__ __forceinline__ void verify_tile(const VerifyArgs &a, int L, char *smem, double *red) {
   const int64_t Mp = a.Mp;
-  int ti, tj, lin = 0;
-  if constexpr (MODE == 1) {
-    const int L = (int)blockIdx.x;
-    ti = L / a.nt;
-    tj = L % a.nt;
-  } else {
-    tile_of_block(blockIdx.x, a.nt, ti, tj, lin);
-  }
-  const int64_t arow0 = (int64_t)ti * TILE, brow0 = (int64_t)tj * TILE;
-  const T *__restrict__ D = a.D;
-  const T *Al = MODE == 0 ? D : a.H;
-  v4d acc[4][4];
-  mma_tile<GCP_FP64>(Al, D, arow0, brow0, Mp, Mp * Mp, smem, 0, acc);
-
+  const int nk = (int)(Mp / TileCfg<GCP_FP64>::KT);
+  int ti, tj, lin;
+  tile_of_block(L, a.ntri, a.nt, ti, tj, lin);
+  const int64_t arow0 = (int64_t)ti * T64, brow0 = (int64_t)tj * T64;
+  const double *__restrict__ D = a.D;
+  const double *__restrict__ H = a.H;
+  constexpr int NS = MODE == 0 ? 4 : 1;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = wave >> 1, wn = wave & 1, l16 = lane & 15, lg = lane >> 4;
-  const bool diag_tile = ti == tj;
-  double tsum = 0.0;
+  const int c4 = (tid & 15) * 4, r0 = tid >> 4;
+  const double *V = (const double *)smem + r0 * VP + c4;   // this thread's elements
+  double p[4][4], v[NS] = {};
+  tile_product<GCP_FP64>(MODE == 0 ? D : H, D, arow0, brow0, Mp, smem, 0, 0, nk);
+  if constexpr (MODE == 1) {
 #pragma unroll
-  for (int bi = 0; bi < 4; ++bi)
+    for (int q = 0; q < 4; ++q)
 #pragma unroll
-    for (int bj = 0; bj < 4; ++bj)
+      for (int e = 0; e < 4; ++e) p[q][e] = V[q * 16 * VP + e];
+    __syncthreads();   // V read before the next product's stages land in it
+    tile_product<GCP_FP64>(D, H, arow0, brow0, Mp, smem, 0, 0, nk);
+  }
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int64_t i = arow0 + wm * 64 + bi * 16 + acc_row<0>(lg, r);
-        const int64_t j = brow0 + wn * 64 + bj * 16 + l16;
-        const double v = acc[bi][bj][r];
-        if constexpr (MODE == 1) {
-          a.HD[i * Mp + j] = v;
-        } else {
-          if (diag_tile && i > j) continue;
-          const double d = v - D[i * Mp + j];
-          tsum += (i == j ? 1.0 : 2.0) * d * d;
-        }
+  for (int q = 0; q < 4; ++q)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int64_t i = arow0 + q * 16 + r0, j = brow0 + c4 + e;
+      if (i > j) continue;
+      const double w = i == j ? 1.0 : 2.0;
+      const double m = V[q * 16 * VP + e];
+      if constexpr (MODE == 1) {
+        const double x = p[q][e] - m;
+        v[0] += w * x * x;
+      } else {
+        const double d = D[i * Mp + j], x = m - d;
+        v[0] += w * x * x;
+        v[1] += w * d * H[i * Mp + j];
+        v[2] += w * d * d;
+        if (i == j) v[3] += d;
       }
-  if constexpr (MODE == 0) {
-    __shared__ double red[4];
-    tsum += shfl_xor_d(tsum, 1);
-    tsum += shfl_xor_d(tsum, 2);
-    tsum += shfl_xor_d(tsum, 4);
-    tsum += shfl_xor_d(tsum, 8);
-    tsum += shfl_xor_d(tsum, 16);
-    tsum += shfl_xor_d(tsum, 32);
-    if (lane == 0) red[wave] = tsum;
-    __syncthreads();
-    if (tid == 0) a.tpart[lin] = ((red[0] + red[1]) + red[2]) + red[3];
-  }
-}
-
-// Per row i (one block): sum_{j>i} (HD_ij - HD_ji)^2, sum_j D_ij H_ij,
-// sum_j D_ij^2 and D_ii into rows[k * Mp + i].
-__global__ __launch_bounds__(256) void k_vrows(VerifyArgs a) {
-  __shared__ double s[3][256];
-  const int64_t i = blockIdx.x, Mp = a.Mp;
-  double c = 0.0, e = 0.0, f = 0.0;
-  for (int64_t j = threadIdx.x; j < Mp; j += 256) {
-    const double d = a.D[i * Mp + j];
-    e += d * a.H[i * Mp + j];
-    f += d * d;
-    if (j > i) {
-      const double x = a.HD[i * Mp + j] - a.HD[j * Mp + i];
-      c += x * x;
     }
+#pragma unroll
+  for (int k = 0; k < NS; ++k) {
+#pragma unroll
+    for (int m = 1; m < 64; m <<= 1) v[k] += shfl_xor_d(v[k], m);
+    if (lane == 0) red[k * 4 + wave] = v[k];
   }
-  s[0][threadIdx.x] = c;
-  s[1][threadIdx.x] = e;
-  s[2][threadIdx.x] = f;
   __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if (threadIdx.x < w)
-      for (int k = 0; k < 3; ++k) s[k][threadIdx.x] += s[k][threadIdx.x + w];
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    a.rows[i] = s[0][0];
-    a.rows[Mp + i] = s[1][0];
-    a.rows[2 * Mp + i] = s[2][0];
-    a.rows[3 * Mp + i] = a.D[i * Mp + i];
-  }
+  if (tid < NS)
+    a.tpart[(MODE == 1 ? 4 : tid) * a.ntri + lin] =
+        ((red[tid * 4] + red[tid * 4 + 1]) + red[tid * 4 + 2]) + red[tid * 4 + 3];
 }
 
-// out[0..3] = fixed-order sums of the four row vectors, out[4] = sum of the
-// idempotency tile partials.
+// The commutator's tiles (twice the work) come first.
+__global__ __launch_bounds__(NTH, 3) void k_vgemm(VerifyArgs a) {
+  constexpr int MM = T64 * VP * 8;
+  static_assert(MM >= TileCfg<GCP_FP64>::SMEM, "the product's stages fit");
+  __shared__ __attribute__((aligned(16))) char smem[MM + 16 * 8];
+  const int b = (int)blockIdx.x;
+  if (b < a.ntri) verify_tile<1>(a, b, smem, (double *)(smem + MM));
+  else verify_tile<0>(a, b - a.ntri, smem, (double *)(smem + MM));
+}
+
+// out[k] = sum of tpart[k][..] in a fixed order, one block per sum.
 __global__ __launch_bounds__(256) void k_vsum(VerifyArgs a) {
-  __shared__ double s[5][256];
-  double v[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-  for (int64_t i = threadIdx.x; i < a.Mp; i += 256)
-    for (int k = 0; k < 4; ++k) v[k] += a.rows[k * a.Mp + i];
-  for (int t = threadIdx.x; t < a.ntri; t += 256) v[4] += a.tpart[t];
-  for (int k = 0; k < 5; ++k) s[k][threadIdx.x] = v[k];
+  __shared__ double s[256];
+  const int k = (int)blockIdx.x;
+  double v = 0.0;
+#pragma unroll 4
+  for (int t = threadIdx.x; t < a.ntri; t += 256) v += a.tpart[(int64_t)k * a.ntri + t];
+  s[threadIdx.x] = v;
   __syncthreads();
   for (int w = 128; w > 0; w >>= 1) {
-    if (threadIdx.x < w)
-      for (int k = 0; k < 5; ++k) s[k][threadIdx.x] += s[k][threadIdx.x + w];
+    if (threadIdx.x < w) s[threadIdx.x] += s[threadIdx.x + w];
     __syncthreads();
   }
-  if (threadIdx.x < 5) a.out[threadIdx.x] = s[threadIdx.x][0];
+  if (threadIdx.x == 0) a.out[k] = s[0];
 }
 
 hipError_t launch_verify(const VerifyArgs &a, hipStream_t st) {
-  const unsigned ntri = (unsigned)(a.nt * (a.nt + 1) / 2);
-  k_vgemm<0><<<ntri, NTH, 0, st>>>(a);
-  k_vgemm<1><<<(unsigned)(a.nt * a.nt), NTH, 0, st>>>(a);
-  k_vrows<<<(unsigned)a.Mp, 256, 0, st>>>(a);
-  k_vsum<<<1, 256, 0, st>>>(a);
+  k_vgemm<<<(unsigned)(2 * a.ntri), NTH, 0, st>>>(a);
+  k_vsum<<<5, 256, 0, st>>>(a);
   return hipGetLastError();
 }
 
