@@ -238,9 +238,9 @@ int gcp_purify(gcp_ctx *ctx, void *D, int32_t dtype, int64_t ldd, gcp_result *ou
  * guess and hole option is supported.
  *   - Each update, D' = a D + b D^2 + e D^3 with (a, b, e) functions of
  *     c = (T2 - T3)/(T1 - T2) (eq. (hpcp3), or eqs. (pm1a)/(pm1b) for PMCP),
- *     is differentiated including the dependence of c on D; this costs two
- *     symmetric and two general M x M products per update (about three
- *     times the forward).
+ *     is differentiated including the dependence of c on D; this costs four
+ *     products over the upper triangle per update (twice the forward; five
+ *     for PMCP).
  *   - The initial guess is differentiated through mu = Tr(H)/M and the
  *     slope beta: beta(mu) of eqs. (dmguess),(pmcpguess) or of the
  *     fixed-alpha guess of eq. (hpcpguess), with emin/emax held fixed (also

@@ -129,8 +129,11 @@ struct gcp_ctx {
   int n_switch[3] = {-1, -1, -1};   // update at which the schedule entered phase k
   int bwd_p = -1;           // updates covered by the stored iterates (-1: none)
   void *bG[2] = {nullptr, nullptr};
-  void *bX2 = nullptr, *bAT = nullptr, *bCT = nullptr;
-  double *btpart = nullptr; // per-tile partial sums of kappa (2 ntri + nt^2)
+  void *bS = nullptr, *bT = nullptr;
+  void *bws = nullptr;      // partial tiles of the split tiles, and their counters
+  unsigned *bcnt = nullptr;
+  int b_nfull = 0, b_nsplit = 2;   // whole tiles of a launch, splits of the others
+  double *btpart = nullptr; // per-tile partial sums of kappa (3 ntri)
   double *bvec = nullptr;   // 2 Mp row scratch + kappa + 2 sums
   // verification workspace (allocated by the first gcp_verify)
   double *vD = nullptr, *vH = nullptr, *vaux = nullptr;
@@ -173,7 +176,7 @@ static void free_all(gcp_ctx *c) {
                   c->counter, c->rcnt, c->sc, c->hist, c->D0p, c->dg0, c->rD0, c->d20};
   for (void *p : ptrs)
     if (p) (void)hipFree(p);
-  void *bptrs[] = {c->bG[0], c->bG[1], c->bX2, c->bAT, c->bCT, c->btpart, c->bvec, c->split_ws,
+  void *bptrs[] = {c->bG[0], c->bG[1], c->bS, c->bT, c->bws, c->bcnt, c->btpart, c->bvec, c->split_ws,
                    c->split_cnt, c->vD, c->vH, c->vaux, c->Xc};
   for (void *p : bptrs)
     if (p) (void)hipFree(p);
@@ -298,6 +301,30 @@ static void init_prec_cfg(gcp_ctx *c, int k) {
 }
 
 
+// Whole and split tiles of the adjoint's launches: the tiles of a last partial
+// round over the CUs are split as the forward's (init_prec_cfg), each of
+// their two products over half of the splits.
+static void init_bwd_cfg(gcp_ctx *c) {
+  int cus = 0;
+  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess ||
+      cus <= 0)
+    cus = 256;
+  const int nt = (int)(c->Mp / 64), ntiles = nt * (nt + 1) / 2, tail = ntiles % cus;
+  const int nk = (int)(c->Mp * elem_size(c->opt.bwd_precision) / 128);
+  const double t_part = c->opt.bwd_precision == GCP_FP64 ? 1.2 : 0.6;
+  c->b_nfull = ntiles;
+  double best = 0.5 * 2 * nk;
+  for (int S = 2; tail > 0 && S <= 16; S += 2) {
+    if (2 * nk / S < 4 || (ntiles > cus && tail * S > cus)) break;
+    const double t = 0.5 * 2 * nk * ((tail * S + cus - 1) / cus) / S + 2.0 + t_part * S;
+    if (t < best) {
+      best = t;
+      c->b_nfull = ntiles - tail;
+      c->b_nsplit = S;
+    }
+  }
+}
+
 extern "C" int gcp_options_default(gcp_options *opt) {
   if (!opt) return GCP_ERR_INVALID_ARG;
   std::memset(opt, 0, sizeof(*opt));
@@ -401,6 +428,7 @@ static void setup_ctx(gcp_ctx *c, int64_t M, const gcp_options &o, void *stream)
     init_prec_cfg(c, k);
     if (c->pc[k].ntpart > c->ntpart) c->ntpart = c->pc[k].ntpart;
   }
+  if (o.keep_iterates) init_bwd_cfg(c);
 }
 
 // Largest workspace of partial tiles, and most arrival counters, of any phase.
@@ -456,11 +484,14 @@ static void for_each_buffer(gcp_ctx *c, bool one_shot, F &&f) {
     const size_t bb = Mp * Mp * (size_t)elem_size(c->opt.bwd_precision);
     f(&c->bG[0], bb);
     f(&c->bG[1], bb);
-    f(&c->bX2, bb);
-    f(&c->bAT, bb);
-    f(&c->bCT, bb);
-    const size_t nt = Mp / 64;
-    f((void **)&c->btpart, (nt * (nt + 1) + nt * nt) * sizeof(double));
+    f(&c->bS, bb);
+    f(&c->bT, bb);
+    const size_t nt = Mp / 64, ntri = nt * (nt + 1) / 2, tail = ntri - (size_t)c->b_nfull;
+    f((void **)&c->btpart, 3 * ntri * sizeof(double));
+    if (tail > 0) {
+      f(&c->bws, tail * (size_t)c->b_nsplit * 64 * 64 * (size_t)elem_size(c->opt.bwd_precision));
+      f((void **)&c->bcnt, tail * sizeof(unsigned));
+    }
     f((void **)&c->bvec, (2 * Mp + 8) * sizeof(double));
   }
 }
@@ -498,7 +529,9 @@ extern "C" int gcp_create(gcp_ctx **out, int64_t M, const gcp_options *opt, void
     return GCP_ERR_NO_MEMORY;
   }
   const size_t vec = (size_t)c->Mp * sizeof(double);
-  if ((c->split_cnt && hipMemsetAsync(c->split_cnt, 0, (size_t)split_counters(c) * sizeof(unsigned),
+  const size_t btail = (size_t)(c->Mp / 64) * (c->Mp / 64 + 1) / 2 - (size_t)c->b_nfull;
+  if ((c->bcnt && hipMemsetAsync(c->bcnt, 0, btail * sizeof(unsigned), c->stream) != hipSuccess) ||
+      (c->split_cnt && hipMemsetAsync(c->split_cnt, 0, (size_t)split_counters(c) * sizeof(unsigned),
                                      c->stream) != hipSuccess) ||
       hipMemsetAsync(c->rcnt, 0, (size_t)c->nred * sizeof(unsigned), c->stream) != hipSuccess ||
       hipMemsetAsync(c->counter, 0, sizeof(unsigned), c->stream) != hipSuccess ||
@@ -1177,18 +1210,14 @@ extern "C" int gcp_backward(gcp_ctx *c, const void *dLdD, int64_t ldg, void *dLd
   double flops = 0.0, mflops = 0.0;
   const double Md = (double)c->M, tile_fl = nominal_tile_flops(c);
   const int nt = (int)(c->Mp / 64), ntri = nt * (nt + 1) / 2;
-  auto gemm = [&](BwdArgs &a) -> int {
+  auto gemm = [&](BwdArgs &a, int mode) -> int {
     if (prof) HIPCHK(c, hipEventRecord(c->events[2 * nlaunch], c->stream));
-    HIPCHK(c, launch_bwd_gemm(bprec, a, c->stream));
+    HIPCHK(c, launch_bwd(bprec, a, mode, c->stream));
     if (prof) HIPCHK(c, hipEventRecord(c->events[2 * nlaunch + 1], c->stream));
     ++nlaunch;
-    if (a.mode == 1) {
-      flops += 4.0 * Md * Md * Md;
-      mflops += 2.0 * c->nt_nominal * c->nt_nominal * tile_fl;
-    } else {
-      flops += Md * Md * (Md + 1.0);
-      mflops += c->nt_nominal * (c->nt_nominal + 1) / 2 * tile_fl;
-    }
+    const double products = mode == BWD_X2 ? 1.0 : 2.0;   // upper tiles of each
+    flops += products * Md * Md * (Md + 1.0);
+    mflops += products * c->nt_nominal * (c->nt_nominal + 1) / 2 * tile_fl;
     return GCP_OK;
   };
 
@@ -1198,9 +1227,13 @@ extern "C" int gcp_backward(gcp_ctx *c, const void *dLdD, int64_t ldg, void *dLd
   BwdArgs a{};
   a.Mp = c->Mp;
   a.nt = nt;
-  a.X2 = c->bX2;
-  a.AT = c->bAT;
-  a.CT = c->bCT;
+  a.fold = fp32_fold(c->Mp);
+  a.nfull = c->b_nfull;
+  a.nsplit = c->b_nsplit;
+  a.ws = c->bws;
+  a.cnt = c->bcnt;
+  a.S = c->bS;
+  a.T = c->bT;
   a.kappa = kappa;
   a.tpart = c->btpart;
   // iterates: all kept (slot n = D_n), or recomputed segment by segment from
@@ -1226,23 +1259,15 @@ extern "C" int gcp_backward(gcp_ctx *c, const void *dLdD, int64_t ldg, void *dLd
     a.G = c->bG[cur];
     a.c = cn;
     a.inv_t12 = 1.0 / t12;
-    a.need_x3 = de != 0.0;
-    // X2 = D D and the partial sums of <G, D^2> and <G, D>
-    a.mode = 0;
-    a.out0 = c->bX2;
-    int st = gemm(a);
+    a.out = c->bG[1 - cur];
+    int st = gemm(a, BWD_PAIR);
     if (st != GCP_OK) return st;
-    // AT = D G, CT = X2 G (and the partial sums of <G, D^3> = <X2, AT>)
-    a.mode = 1;
-    a.out0 = c->bAT;
-    a.out1 = c->bCT;
-    st = gemm(a);
-    if (st != GCP_OK) return st;
-    HIPCHK(c, launch_bwd_kappa(c->btpart, ntri, nt * nt, da, db, de, kappa, c->stream));
-    // Gbar_n
-    a.mode = 2;
-    a.out0 = c->bG[1 - cur];
-    st = gemm(a);
+    if (de != 0.0) {
+      st = gemm(a, BWD_X2);
+      if (st != GCP_OK) return st;
+    }
+    HIPCHK(c, launch_bwd_kappa(c->btpart, ntri, da, db, de, kappa, c->stream));
+    st = gemm(a, BWD_STEP);
     if (st != GCP_OK) return st;
     cur = 1 - cur;
   }

@@ -13,19 +13,22 @@
 // (Frobenius products; a', b', e' from update_coef_derivs; <Gbar', D^3> =
 // <D^2, D Gbar'>, needed only when e' != 0, i.e. for PMCP).
 //
-// One adjoint step is three launches of 64 x 64 MFMA tile products, all of
-// the A * B^T row-panel form of the forward (every operand is symmetric
-// except AT and CT, which are only ever read along their rows):
-//   mode 0 (upper tiles)  X2 = D D           epilogue: per-tile sums of
-//                                            w_ij Gbar'_ij X2_ij and w_ij Gbar'_ij D_ij
-//   mode 1 (all tiles)    AT = D Gbar'  and  CT = X2 Gbar'   (one launch;
-//                                            PMCP: per-tile sums of X2 o AT)
-//   mode 2 (upper tiles)  E  = D (Gbar' D)   epilogue: Gbar_n from Gbar', AT,
-//                                            AT^T, CT, CT^T, E, D and X2
-// with AT + AT^T = D Gbar' + Gbar' D and CT + CT^T = D^2 Gbar' + Gbar' D^2.
-// Algorithmic cost per step: two symmetric products (M^3 each, upper-triangle
-// output) and two general ones (2 M^3 each).  kappa is reduced on the device
-// in a fixed order, so the whole backward is bitwise reproducible.
+// One adjoint step is two launches of 64 x 64 MFMA tile products over upper
+// tiles, two products per tile, all of the A * B^T row-panel form of the
+// forward:
+//   k_bpair   D_i G_j and D_j G_i, i.e. both tiles of A = D Gbar' of a mirrored
+//             pair: stores S = A + A^T and T = A^T, and sums <A, D> = <Gbar', D^2>
+//             and <Gbar', D> (both = 1/2 <S, .> by symmetry)
+//   k_bstep   D_i T_j + S_i D_j = D^2 Gbar' + (D Gbar' D + Gbar' D^2), one
+//             accumulator; epilogue: Gbar_n from Gbar', S, D and the product
+// with S = D Gbar' + Gbar' D.  The term -3 kappa D^2 / (T1 - T2) is linear in
+// a third product D D, which k_badd folds into the first one by adding a
+// multiple of D to T once kappa is known.  That is 4 M^3 flops per step; with
+// D^2 formed for itself, D Gbar' and D^2 Gbar' as general products and D
+// Gbar' D it was 6 M^3.  PMCP alone needs D^2: k_bx2 forms its tiles for the
+// sum <Gbar', D^3> = 1/2 <S, D^2> and does not store them.
+// kappa is reduced on the device in a fixed order, so the whole backward is
+// bitwise reproducible.
 //
 // The initial guess D_0 = theta I + beta (mu I - H), mu = Tr(H)/M.  With a
 // fixed slope rule (eqs. (dmguess),(pmcpguess), or eq. (hpcpguess) with a
@@ -46,206 +49,274 @@
 
 namespace gcp {
 
-// All tiles of the nt x nt grid, in groups of TILE_GROUP tile rows,
-// column-major inside a group: consecutive blocks share the right-hand
-// (column) panel and cycle over the group's row panels.
-__device__ __forceinline__ void full_tile_of_block(int L, int nt, int &ti, int &tj) {
-  const int gr = L / (TILE_GROUP * nt);
-  const int r0 = gr * TILE_GROUP, rows = min(TILE_GROUP, nt - r0);
-  const int rem = L - gr * TILE_GROUP * nt;
-  ti = r0 + rem % rows;
-  tj = rem / rows;
-}
-
-// Contiguous run of [0, total) for the XCD that block b is dispatched to.
-__device__ __forceinline__ int xcd_linear(int b, int total) {
-  const int xcd = b & 7, loc = b >> 3, q = total >> 3, r = total & 7;
-  return xcd * q + (xcd < r ? xcd : r) + loc;
-}
-
 template <int P> struct BwdCfg {
-  static constexpr int W = T64 * VP * 8;     // FP64 staging of a tile
-  static constexpr int MM = TileCfg<P>::SMEM > W ? TileCfg<P>::SMEM : W;
+  using S = typename TileCfg<P>::S;
+  static constexpr int V = T64 * VP * (int)sizeof(S);
+  static constexpr int MM = TileCfg<P>::SMEM > V ? TileCfg<P>::SMEM : V;
   static constexpr int SMEM = MM + 8 * 8;    // and two sums per wave
-  static constexpr int BLOCKS = Enc<P>::KIND == 0 ? 3 : 2;   // per CU, as k_tile
+  static constexpr int BLOCKS = Enc<P>::KIND == 0 ? 4 : 2;   // per CU, as k_tile
 };
 
-// 64 x 64 tiles, one per block; thread tid works on columns 4 (tid % 16) .. +3
-// of rows 16 q + tid / 16 of the tile, so that the inputs are read, and the
-// result and its mirror (through LDS) written, as rows of 64 elements.
-template <int P, int MODE>
-__global__ __launch_bounds__(NTH, BwdCfg<P>::BLOCKS) void k_bgemm(BwdArgs a) {
-  using E = Enc<P>;
-  using T = typename E::T;
-  typedef T v4t __attribute__((ext_vector_type(4)));
+// Tile of this block, and for a tile of the last partial round its split: the
+// two products of such a tile are nsplit/2 blocks each (nsplit even).
+struct BwdTile {
+  int ti, tj, lin, split;
+};
+__device__ __forceinline__ BwdTile bwd_tile(const BwdArgs &a) {
+  BwdTile t{0, 0, 0, -1};
+  const int u = (int)blockIdx.x - a.nfull;
+  if (u < 0) {
+    tile_of_block(blockIdx.x, a.nfull, a.nt, t.ti, t.tj, t.lin);
+  } else {
+    const int ntail = ((int)gridDim.x - a.nfull) / a.nsplit;
+    t.split = u / ntail;
+    t.lin = a.nfull + u % ntail;
+    tile_of_index(t.lin, a.nt, t.ti, t.tj);
+  }
+  return t;
+}
+
+// Thread tid works on columns 4 (tid % 16) .. +3 of rows 16 q + tid / 16 of
+// the tile, so that inputs are read and results written as rows of 64
+// elements; mirrored tiles go through LDS.
+template <int P> struct BwdThread {
+  using T = typename Enc<P>::T;
   using S = typename TileCfg<P>::S;
-  static_assert(E::NP == 1, "the adjoint uses single-plane FP64 / FP32 storage");
+  typedef T v4t __attribute__((ext_vector_type(4)));
+  int c4, r0;
+  char *smem;
+  __device__ explicit BwdThread(char *s) : c4((threadIdx.x & 15) * 4), r0(threadIdx.x >> 4), smem(s) {}
+  __device__ __forceinline__ void take(S (&v)[4][4]) const {   // own elements of the tile in LDS
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[q][e] = ((const S *)smem)[(q * 16 + r0) * VP + c4 + e];
+  }
+  __device__ __forceinline__ void put(const S (&v)[4][4]) const {
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) ((S *)smem)[(q * 16 + r0) * VP + c4 + e] = v[q][e];
+    __syncthreads();
+  }
+  __device__ __forceinline__ void take_mirror(S (&v)[4][4]) const {
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[q][e] = ((const S *)smem)[(c4 + e) * VP + q * 16 + r0];
+  }
+  __device__ __forceinline__ void store(T *O, int64_t i0, int64_t j0, int64_t Mp,
+                                        const S (&v)[4][4]) const {
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      *(v4t *)(O + (i0 + q * 16 + r0) * Mp + j0 + c4) = v4t{v[q][0], v[q][1], v[q][2], v[q][3]};
+  }
+};
 
-  __shared__ __attribute__((aligned(16))) char smem[BwdCfg<P>::SMEM];
-  double *W = (double *)smem, *red = (double *)(smem + BwdCfg<P>::MM);
+// Sums of x and y over the tile into tpart[lin] and tpart[ntri + lin].
+__device__ __forceinline__ void tile_sums(const BwdArgs &a, int lin, double x, double y, double *red) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, ntri = a.nt * (a.nt + 1) / 2;
+  x = wave_sum(x);
+  y = wave_sum(y);
+  if (lane == 0) {
+    red[wave] = x;
+    red[4 + wave] = y;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    a.tpart[lin] = ((red[0] + red[1]) + red[2]) + red[3];
+    a.tpart[ntri + lin] = ((red[4] + red[5]) + red[6]) + red[7];
+  }
+}
 
+template <int P>
+__global__ __launch_bounds__(NTH, BwdCfg<P>::BLOCKS) void k_bpair(BwdArgs a) {
+  using B = BwdCfg<P>;
+  using T = typename Enc<P>::T;
+  using S = typename B::S;
+  typedef T v4t __attribute__((ext_vector_type(4)));
+  __shared__ __attribute__((aligned(16))) char smem[B::SMEM];
   const int64_t Mp = a.Mp;
-  int ti, tj, lin = 0, which = 0;
-  if constexpr (MODE == 1) {
-    const int nfull = a.nt * a.nt;
-    int L = xcd_linear(blockIdx.x, 2 * nfull);
-    which = L >= nfull;
-    full_tile_of_block(L - which * nfull, a.nt, ti, tj);
+  const BwdTile t = bwd_tile(a);
+  const int64_t i0 = (int64_t)t.ti * T64, j0 = (int64_t)t.tj * T64;
+  const int nk = (int)(Mp / TileCfg<P>::KT), half = a.nsplit / 2;
+  const bool dtile = t.ti == t.tj;
+  const BwdThread<P> me(smem);
+  S p[4][4], m[4][4];   // A(i, j), and A(j, i) read as its transpose
+  if (t.split < 0) {
+    tile_product<P>(a.D, a.G, i0, j0, Mp, smem, a.fold, 0, nk);
+    me.take(p);
+    if (!dtile) {
+      __syncthreads();   // read by all before the next product's stages land in it
+      tile_product<P>(a.D, a.G, j0, i0, Mp, smem, a.fold, 0, nk);
+    }
   } else {
-    tile_of_block(blockIdx.x, a.nt, ti, tj, lin);
+    const int which = t.split >= half, s = t.split - which * half;
+    tile_product<P>(a.D, a.G, which ? j0 : i0, which ? i0 : j0, Mp, smem, a.fold, s * nk / half,
+                    (s + 1) * nk / half);
+    const int64_t ps = (int64_t)((int)gridDim.x - a.nfull) / a.nsplit * (T64 * T64);
+    S *w = (S *)a.ws + (int64_t)(t.lin - a.nfull) * (T64 * T64) + me.r0 * T64 + me.c4;
+    if (!publish_split((const S *)smem + me.r0 * VP + me.c4, w + t.split * ps,
+                       a.cnt + (t.lin - a.nfull), a.nsplit, smem))
+      return;
+    double v[4][4];
+    add_partials(w + half * ps, ps, half, v);
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) p[q][e] = (S)v[q][e];
+    me.put(p);   // A(j, i), as a whole product leaves it
+    add_partials(w, ps, half, v);
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) p[q][e] = (S)v[q][e];
   }
-  const int64_t arow0 = (int64_t)ti * T64, brow0 = (int64_t)tj * T64;
+  me.take_mirror(m);
+  S s[4][4];
+  double sd = 0.0, gd = 0.0;
   const T *__restrict__ D = (const T *)a.D;
-  const T *__restrict__ X2 = (const T *)a.X2;
   const T *__restrict__ G = (const T *)a.G;
-  const T *__restrict__ AT = (const T *)a.AT;
-  const T *__restrict__ CT = (const T *)a.CT;
-  const T *Al, *Bl;
-  if constexpr (MODE == 0) {
-    Al = D;
-    Bl = D;
-  } else if constexpr (MODE == 1) {
-    Al = which ? X2 : D;
-    Bl = G;
-  } else {
-    Al = D;
-    Bl = AT;
-  }
-
-  tile_product<P>(Al, Bl, arow0, brow0, Mp, smem, fp32_fold(Mp), 0,
-                  (int)(Mp / TileCfg<P>::KT));
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int c4 = (tid & 15) * 4, r0 = tid >> 4;
-  const S *V = (const S *)smem + r0 * VP + c4;   // this thread's elements
-  const int64_t o0 = (arow0 + r0) * Mp + brow0 + c4;
-  const int64_t m0 = (brow0 + r0) * Mp + arow0 + c4;   // in the mirrored tile
-
-  if constexpr (MODE == 1) {
-    T *__restrict__ O = (T *)(which ? a.out1 : a.out0);
-    const bool x3 = a.need_x3 && !which;   // block-uniform
-    double xsum = 0.0;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int64_t o = o0 + q * 16 * Mp;
-      v4t ov;
+  for (int q = 0; q < 4; ++q) {
+    const int64_t o = (i0 + q * 16 + me.r0) * Mp + j0 + me.c4;
+    const v4t dv = *(const v4t *)(D + o), gv = *(const v4t *)(G + o);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) ov[e] = V[q * 16 * VP + e];
-      if (x3) {
-        const v4t xv = *(const v4t *)(X2 + o);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) xsum += (double)xv[e] * (double)ov[e];
-      }
-      *(v4t *)(O + o) = ov;
+    for (int e = 0; e < 4; ++e) {
+      const double x = (double)p[q][e] + (double)m[q][e];
+      s[q][e] = (S)x;
+      sd += x * (double)dv[e];
+      gd += (double)gv[e] * (double)dv[e];
     }
-    if (x3) {
-#pragma unroll
-      for (int m = 1; m < 64; m <<= 1) xsum += shfl_xor_d(xsum, m);
-      if (lane == 0) red[wave] = xsum;
-      __syncthreads();
-      if (tid == 0) {
-        const int ntri = a.nt * (a.nt + 1) / 2;
-        a.tpart[2 * ntri + ti * a.nt + tj] = ((red[0] + red[1]) + red[2]) + red[3];
-      }
-    }
-    return;
   }
+  T *To = (T *)a.T, *So = (T *)a.S;
+  me.store(To, i0, j0, Mp, m);
+  me.store(So, i0, j0, Mp, s);
+  if (!dtile) {
+    S x[4][4];
+    me.put(p);
+    me.take_mirror(x);
+    me.store(To, j0, i0, Mp, x);
+    me.put(s);
+    me.take_mirror(x);
+    me.store(So, j0, i0, Mp, x);
+  }
+  tile_sums(a, t.lin, dtile ? 0.5 * sd : sd, dtile ? gd : 2.0 * gd, (double *)(smem + B::MM));
+}
 
-  const bool dtile = (ti == tj);
-  T *__restrict__ O = (T *)a.out0;
-  double tsum = 0.0, dsum = 0.0;
-  const double kappa = MODE == 2 ? *a.kappa : 0.0;
+// T += *kappa w D (the D^2 term of the update's kappa part).
+template <int P>
+__global__ __launch_bounds__(256) void k_badd(const void *D, void *T, const double *kappa, double w,
+                                              int64_t n4) {
+  using TB = typename Enc<P>::T;
+  typedef TB v4t __attribute__((ext_vector_type(4)));
+  const double f = *kappa * w;
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n4; i += (int64_t)gridDim.x * 256) {
+    const v4t d = ((const v4t *)D)[i];
+    v4t t = ((const v4t *)T)[i];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) t[e] = (TB)((double)t[e] + f * (double)d[e]);
+    ((v4t *)T)[i] = t;
+  }
+}
+
+template <int P>
+__global__ __launch_bounds__(NTH, BwdCfg<P>::BLOCKS) void k_bstep(BwdArgs a) {
+  using B = BwdCfg<P>;
+  using T = typename Enc<P>::T;
+  using S = typename B::S;
+  typedef T v4t __attribute__((ext_vector_type(4)));
+  __shared__ __attribute__((aligned(16))) char smem[B::SMEM];
+  const int64_t Mp = a.Mp;
+  const BwdTile t = bwd_tile(a);
+  const int64_t i0 = (int64_t)t.ti * T64, j0 = (int64_t)t.tj * T64;
+  const int nk = (int)(Mp / TileCfg<P>::KT), half = a.nsplit / 2;
+  const bool dtile = t.ti == t.tj;
+  const BwdThread<P> me(smem);
   double v[4][4];
+  S p[4][4];
+  if (t.split < 0) {
+    tile_product<P>(a.D, a.T, i0, j0, Mp, smem, a.fold, 0, nk);
+    me.take(p);
+    __syncthreads();   // read by all before the next product's stages land in it
+    tile_product<P>(a.S, a.D, i0, j0, Mp, smem, a.fold, 0, nk);
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+        v[q][e] = (double)p[q][e] + (double)((const S *)smem)[(q * 16 + me.r0) * VP + me.c4 + e];
+  } else {
+    const int which = t.split >= half, s = t.split - which * half;
+    tile_product<P>(which ? a.S : a.D, which ? a.D : a.T, i0, j0, Mp, smem, a.fold, s * nk / half,
+                    (s + 1) * nk / half);
+    const int64_t ps = (int64_t)((int)gridDim.x - a.nfull) / a.nsplit * (T64 * T64);
+    S *w = (S *)a.ws + (int64_t)(t.lin - a.nfull) * (T64 * T64) + me.r0 * T64 + me.c4;
+    if (!publish_split((const S *)smem + me.r0 * VP + me.c4, w + t.split * ps,
+                       a.cnt + (t.lin - a.nfull), a.nsplit, smem))
+      return;
+    add_partials(w, ps, a.nsplit, v);
+  }
+  const T *__restrict__ D = (const T *)a.D;
+  const T *__restrict__ G = (const T *)a.G;
+  const T *__restrict__ Sm = (const T *)a.S;
+  const double k = *a.kappa * a.inv_t12, kd = k * (2.0 + 2.0 * a.c), ki = -k * a.c;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int row = q * 16 + me.r0;
+    const int64_t o = (i0 + row) * Mp + j0 + me.c4;
+    const v4t dv = *(const v4t *)(D + o), gv = *(const v4t *)(G + o), sv = *(const v4t *)(Sm + o);
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      p[q][e] = (S)(a.a * (double)gv[e] + a.b * (double)sv[e] + a.e * v[q][e] + kd * (double)dv[e] +
+                    (dtile && row == me.c4 + e ? ki : 0.0));
+  }
+  T *O = (T *)a.out;
+  if (!dtile) me.store(O, i0, j0, Mp, p);
+  me.put(p);
+  // mirrored tile; a diagonal tile is written whole, its lower half from the
+  // upper one
+  S x[4][4];
 #pragma unroll
   for (int q = 0; q < 4; ++q)
 #pragma unroll
-    for (int e = 0; e < 4; ++e) v[q][e] = (double)V[q * 16 * VP + e];
-  if constexpr (MODE == 2) {
-    // b AT^T + e CT^T + e E: the transposes from rows of the mirrored tile
-    double t[4][4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const v4t at = *(const v4t *)(AT + m0 + q * 16 * Mp), ct = *(const v4t *)(CT + m0 + q * 16 * Mp);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) t[q][e] = a.b * (double)at[e] + a.e * (double)ct[e];
-    }
-    __syncthreads();   // V read by all
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) W[(q * 16 + r0) * VP + c4 + e] = t[q][e];
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) v[q][e] = W[(c4 + e) * VP + q * 16 + r0] + a.e * v[q][e];
-  }
-  __syncthreads();
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int row = q * 16 + r0;
-    const int64_t o = o0 + q * 16 * Mp;
-    const v4t dv = *(const v4t *)(D + o), gv = *(const v4t *)(G + o);
-    v4t ov;
-    if constexpr (MODE == 0) {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int c = c4 + e;
-        const T x = (T)v[q][e];
-        ov[e] = x;
-        if (dtile && row > c) continue;   // covered by the mirror of (j, i)
-        const double wg = ((dtile && row == c) ? 1.0 : 2.0) * (double)gv[e];
-        tsum += wg * (double)x;
-        dsum += wg * (double)dv[e];
-      }
-    } else {
-      const v4t xv = *(const v4t *)(X2 + o), av = *(const v4t *)(AT + o), cv = *(const v4t *)(CT + o);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const double d = (double)dv[e], x2 = (double)xv[e];
-        const double one = (dtile && row == c4 + e) ? 1.0 : 0.0;
-        const double gc = ((2.0 * d - 3.0 * x2) - a.c * (one - 2.0 * d)) * a.inv_t12;
-        ov[e] = (T)(a.a * (double)gv[e] + a.b * (double)av[e] + a.e * (double)cv[e] + v[q][e] +
-                    kappa * gc);
-      }
-    }
-#pragma unroll
-    for (int e = 0; e < 4; ++e) ((T *)smem)[row * VP + c4 + e] = ov[e];
-    if (!dtile) *(v4t *)(O + o) = ov;
-  }
-  __syncthreads();
-  // mirrored tile, from LDS; a diagonal tile is written whole from here, its
-  // lower half from the upper one
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int row = q * 16 + r0;
-    v4t ov;
-#pragma unroll
     for (int e = 0; e < 4; ++e) {
-      const int c = c4 + e;
+      const int row = q * 16 + me.r0, c = me.c4 + e;
       const bool up = dtile && row < c;
-      ov[e] = ((const T *)smem)[(up ? row : c) * VP + (up ? c : row)];
+      x[q][e] = ((const S *)smem)[(up ? row : c) * VP + (up ? c : row)];
     }
-    *(v4t *)(O + m0 + q * 16 * Mp) = ov;
-  }
+  me.store(O, j0, i0, Mp, x);
+}
 
-  if constexpr (MODE == 0) {
+// PMCP: tiles of X2 = D D, not stored, for 1/2 <S, D^2> into tpart[2 ntri ..).
+template <int P>
+__global__ __launch_bounds__(NTH, BwdCfg<P>::BLOCKS) void k_bx2(BwdArgs a) {
+  using B = BwdCfg<P>;
+  using T = typename Enc<P>::T;
+  using S = typename B::S;
+  typedef T v4t __attribute__((ext_vector_type(4)));
+  __shared__ __attribute__((aligned(16))) char smem[B::SMEM];
+  const int64_t Mp = a.Mp;
+  int ti, tj, lin;
+  tile_of_block(blockIdx.x, a.nt, ti, tj, lin);
+  const int64_t i0 = (int64_t)ti * T64, j0 = (int64_t)tj * T64;
+  tile_product<P>(a.D, a.D, i0, j0, Mp, smem, a.fold, 0, (int)(Mp / TileCfg<P>::KT));
+  const BwdThread<P> me(smem);
+  S v[4][4];
+  me.take(v);
+  double x = 0.0;
 #pragma unroll
-    for (int m = 1; m < 64; m <<= 1) {
-      tsum += shfl_xor_d(tsum, m);
-      dsum += shfl_xor_d(dsum, m);
-    }
-    if (lane == 0) {
-      red[wave] = tsum;
-      red[4 + wave] = dsum;
-    }
-    __syncthreads();
-    if (tid == 0) {
-      const int ntri = a.nt * (a.nt + 1) / 2;
-      a.tpart[lin] = ((red[0] + red[1]) + red[2]) + red[3];
-      a.tpart[ntri + lin] = ((red[4] + red[5]) + red[6]) + red[7];
-    }
+  for (int q = 0; q < 4; ++q) {
+    const v4t sv = *(const v4t *)((const T *)a.S + (i0 + q * 16 + me.r0) * Mp + j0 + me.c4);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) x += (double)sv[e] * (double)v[q][e];
   }
+  x = wave_sum(ti == tj ? 0.5 * x : x);
+  double *red = (double *)(smem + B::MM);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = x;
+  __syncthreads();
+  if (threadIdx.x == 0)
+    a.tpart[a.nt * (a.nt + 1) + lin] = ((red[0] + red[1]) + red[2]) + red[3];
 }
 
 // Sum of tpart[t0 .. t1) in a fixed order by the 256 threads of one block.
@@ -265,12 +336,12 @@ __device__ double block_sum(const double *tpart, int t0, int t1, double *s) {
 
 // kappa = da <G, D> + db <G, D^2> + de <G, D^3> from the per-tile sums, in a
 // fixed order (one block).
-__global__ __launch_bounds__(256) void k_bkappa(const double *tpart, int ntri, int nfull,
-                                                double da, double db, double de, double *kappa) {
+__global__ __launch_bounds__(256) void k_bkappa(const double *tpart, int ntri, double da,
+                                                double db, double de, double *kappa) {
   __shared__ double s[256];
   const double sx2 = block_sum(tpart, 0, ntri, s);
   const double sd = block_sum(tpart, ntri, 2 * ntri, s);
-  const double sx3 = de != 0.0 ? block_sum(tpart, 2 * ntri, 2 * ntri + nfull, s) : 0.0;
+  const double sx3 = de != 0.0 ? block_sum(tpart, 2 * ntri, 3 * ntri, s) : 0.0;
   if (threadIdx.x == 0) *kappa = da * sd + db * sx2 + de * sx3;
 }
 
@@ -434,26 +505,32 @@ hipError_t launch_bwd_load(int bprec, const void *g, int64_t ldg, int dtype, int
 }
 
 template <int P>
-static hipError_t bgemm_p(const BwdArgs &a, hipStream_t st) {
-  const unsigned ntri = (unsigned)(a.nt * (a.nt + 1) / 2);
-  switch (a.mode) {
-    case 0: k_bgemm<P, 0><<<ntri, NTH, 0, st>>>(a); break;
-    case 1: k_bgemm<P, 1><<<(unsigned)(2 * a.nt * a.nt), NTH, 0, st>>>(a); break;
-    case 2: k_bgemm<P, 2><<<ntri, NTH, 0, st>>>(a); break;
+static hipError_t bwd_step(const BwdArgs &a, int mode, hipStream_t st) {
+  const int ntri = a.nt * (a.nt + 1) / 2;
+  const unsigned grid = (unsigned)(a.nfull + (ntri - a.nfull) * a.nsplit);
+  const int64_t n4 = a.Mp * a.Mp / 4;
+  switch (mode) {
+    case BWD_PAIR: k_bpair<P><<<grid, NTH, 0, st>>>(a); break;
+    case BWD_X2: k_bx2<P><<<(unsigned)ntri, NTH, 0, st>>>(a); break;
+    case BWD_STEP:
+      k_badd<P><<<(unsigned)(n4 / 1024 + 1 > 4096 ? 4096 : n4 / 1024 + 1), 256, 0, st>>>(
+          a.D, a.T, a.kappa, -3.0 * a.inv_t12 / a.e, n4);
+      k_bstep<P><<<grid, NTH, 0, st>>>(a);
+      break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
 
-hipError_t launch_bwd_gemm(int bprec, const BwdArgs &a, hipStream_t st) {
-  if (bprec == GCP_FP64) return bgemm_p<GCP_FP64>(a, st);
-  if (bprec == GCP_FP32) return bgemm_p<GCP_FP32>(a, st);
+hipError_t launch_bwd(int bprec, const BwdArgs &a, int mode, hipStream_t st) {
+  if (bprec == GCP_FP64) return bwd_step<GCP_FP64>(a, mode, st);
+  if (bprec == GCP_FP32) return bwd_step<GCP_FP32>(a, mode, st);
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_bwd_kappa(const double *tpart, int ntri, int nfull, double da, double db,
-                            double de, double *kappa, hipStream_t st) {
-  k_bkappa<<<1, 256, 0, st>>>(tpart, ntri, nfull, da, db, de, kappa);
+hipError_t launch_bwd_kappa(const double *tpart, int ntri, double da, double db, double de,
+                            double *kappa, hipStream_t st) {
+  k_bkappa<<<1, 256, 0, st>>>(tpart, ntri, da, db, de, kappa);
   return hipGetLastError();
 }
 

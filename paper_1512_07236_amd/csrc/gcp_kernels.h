@@ -158,23 +158,24 @@ struct OutArgs {
 // row-major in the adjoint's storage type (FP64 or FP32).
 struct BwdArgs {
   const void *D;       // D_n
-  const void *X2;      // D_n^2                     (modes 1, 2)
   const void *G;       // Gbar_{n+1} = dL/dD_{n+1}
-  const void *AT;      // D_n Gbar_{n+1}            (mode 2)
-  const void *CT;      // D_n^2 Gbar_{n+1}          (mode 2)
-  void *out0;          // mode 0: X2; mode 1: AT; mode 2: Gbar_n
-  void *out1;          // mode 1: CT
+  void *S, *T;         // D G + G D, and G D (BWD_PAIR writes, BWD_STEP reads)
+  void *out;           // Gbar_n (BWD_STEP)
   int64_t Mp;
-  int nt;
-  int mode;            // 0: X2 = D D; 1: AT = D G and CT = X2 G; 2: E = D G D + combine
-  int need_x3;         // mode 1: also the per-tile sums of X2 o AT (<G, D^3>; e' != 0)
+  int nt;              // Mp / 64
+  int fold;            // fold period of the FP32 products, in K stages
+  // Blocks [0, nfull) compute whole tiles; each remaining tile is split over
+  // nsplit (even) blocks, half of them for each of its two products, which
+  // meet in ws (arrival counters cnt, self-resetting)
+  int nfull, nsplit;
+  void *ws;
+  unsigned *cnt;
   double a, b, e;      // D_{n+1} = a D + b D^2 + e D^3 at c_n (update_coefs)
   double c, inv_t12;   // c_n, 1 / (T1 - T2)_n
-  const double *kappa; // device scalar (mode 2)
-  double *tpart;       // per-tile sums: [0, ntri) w_ij G_ij X2_ij and [ntri, 2 ntri)
-                       // w_ij G_ij D_ij over upper tiles (mode 0), [2 ntri, 2 ntri + nt^2)
-                       // X2 o AT over all tiles (mode 1, need_x3)
+  const double *kappa; // device scalar (BWD_STEP)
+  double *tpart;       // per-tile sums [3][ntri]: <G, D^2>, <G, D>, <G, D^3> (BWD_X2)
 };
+enum { BWD_PAIR = 0, BWD_X2 = 1, BWD_STEP = 2 };
 
 struct BwdInitArgs {
   const void *G0;      // Gbar_0 (Mp x Mp)
@@ -204,9 +205,9 @@ hipError_t launch_bwd_store(int fprec, int bprec, const void *planes, const doub
                             int64_t Mp, void *out, hipStream_t st);
 hipError_t launch_bwd_load(int bprec, const void *g, int64_t ldg, int dtype, int64_t M,
                            int64_t Mp, void *G, hipStream_t st);
-hipError_t launch_bwd_gemm(int bprec, const BwdArgs &a, hipStream_t st);
-hipError_t launch_bwd_kappa(const double *tpart, int ntri, int nfull, double da, double db,
-                            double de, double *kappa, hipStream_t st);
+hipError_t launch_bwd(int bprec, const BwdArgs &a, int mode, hipStream_t st);
+hipError_t launch_bwd_kappa(const double *tpart, int ntri, double da, double db, double de,
+                            double *kappa, hipStream_t st);
 hipError_t launch_bwd_init(int bprec, const BwdInitArgs &a, hipStream_t st);
 
 hipError_t launch_gemm(int prec, const GemmArgs &g, hipStream_t st);

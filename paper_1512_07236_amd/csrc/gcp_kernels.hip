@@ -413,52 +413,6 @@ template <int P> struct TileKernel {
   static constexpr int BLOCKS = C::KIND == 0 ? 4 : C::KIND == 1 ? 2 : 3;   // per CU
 };
 
-// v[u][e] = the sum of the n partial tiles w, w + ps, .. at QC rows of this
-// thread, which blocks on other XCDs have written in this launch: stored and
-// loaded at agent scope, 8 bytes at a time.  (Plain accesses between
-// __threadfence() calls write back and invalidate a whole L2 per block:
-// measured 65 us instead of 30 per FP16X3 product at M = 1000.)
-template <class S, int QC>
-__device__ __forceinline__ void add_partials(const S *w, int64_t ps, int n, double (&v)[QC][4]) {
-  typedef S v4s __attribute__((ext_vector_type(4)));
-  constexpr int NW = (int)sizeof(v4s) / 8;
-  union Pack {
-    uint64_t u[NW];
-    v4s x;
-  };
-#pragma unroll
-  for (int q = 0; q < QC; ++q)
-#pragma unroll
-    for (int e = 0; e < 4; ++e) v[q][e] = 0.0;
-#pragma unroll 2
-  for (int s = 0; s < n; ++s)
-#pragma unroll
-    for (int q = 0; q < QC; ++q) {
-      const S *p = w + s * ps + q * 16 * T64;
-      Pack t;
-#pragma unroll
-      for (int k = 0; k < NW; ++k)
-        t.u[k] = __hip_atomic_load((const uint64_t *)p + k, __ATOMIC_RELAXED,
-                                   __HIP_MEMORY_SCOPE_AGENT);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) v[q][e] += (double)t.x[e];
-    }
-}
-
-template <class S>
-__device__ __forceinline__ void publish4(S *p, S a, S b, S c, S d) {
-  typedef S v4s __attribute__((ext_vector_type(4)));
-  constexpr int NW = (int)sizeof(v4s) / 8;
-  union Pack {
-    uint64_t u[NW];
-    v4s x;
-  } t;
-  t.x = v4s{a, b, c, d};
-#pragma unroll
-  for (int k = 0; k < NW; ++k)
-    __hip_atomic_store((uint64_t *)p + k, t.u[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
 template <int P>
 __global__ __launch_bounds__(NTH, (TileKernel<P>::BLOCKS)) void k_tile(GemmArgs g) {
   using C = TileCfg<P>;
@@ -485,22 +439,9 @@ __global__ __launch_bounds__(NTH, (TileKernel<P>::BLOCKS)) void k_tile(GemmArgs 
   const S *V = (const S *)smem + r0 * VP + c4;
   const int64_t ps = (int64_t)ntail * (T64 * T64);
   const S *w0 = (const S *)g.ws + (int64_t)(lin - g.nfull) * (T64 * T64) + r0 * T64 + c4;
-  if (split >= 0) {
-    S *w = (S *)w0 + split * ps;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const S *v = V + q * 16 * VP;
-      publish4(w + q * 16 * T64, v[0], v[1], v[2], v[3]);
-    }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // out before the counter moves
-    __syncthreads();
-    unsigned *cnt = g.cnt + (lin - g.nfull), *last = (unsigned *)smem;
-    if (tid == 0) *last = atomicAdd(cnt, 1u) == (unsigned)g.nsplit - 1;
-    __syncthreads();
-    if (!*last) return;
-    __syncthreads();   // flag read by all before the epilogue reuses smem
-    if (tid == 0) *cnt = 0u;   // ready for the next launch
-  }
+  if (split >= 0 &&
+      !publish_split(V, (S *)w0 + split * ps, g.cnt + (lin - g.nfull), g.nsplit, smem))
+    return;
   constexpr int QC = FinCfg<P>::QC;
   finish_any<P>(g, ti, tj, lin, [&](int q0, double (&v)[QC][4]) {
     if (split >= 0) {

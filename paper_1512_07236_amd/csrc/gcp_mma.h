@@ -399,4 +399,73 @@ __device__ __forceinline__ void tile_product(const void *A, const void *B, int64
   }
 }
 
+// v[u][e] = the sum of the n partial tiles w, w + ps, .. at QC rows of this
+// thread, which blocks on other XCDs have written in this launch: stored and
+// loaded at agent scope, 8 bytes at a time.  (Plain accesses between
+// __threadfence() calls write back and invalidate a whole L2 per block:
+// measured 65 us instead of 30 per FP16X3 product at M = 1000.)
+template <class S, int QC>
+__device__ __forceinline__ void add_partials(const S *w, int64_t ps, int n, double (&v)[QC][4]) {
+  typedef S v4s __attribute__((ext_vector_type(4)));
+  constexpr int NW = (int)sizeof(v4s) / 8;
+  union Pack {
+    uint64_t u[NW];
+    v4s x;
+  };
+#pragma unroll
+  for (int q = 0; q < QC; ++q)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[q][e] = 0.0;
+#pragma unroll 2
+  for (int s = 0; s < n; ++s)
+#pragma unroll
+    for (int q = 0; q < QC; ++q) {
+      const S *p = w + s * ps + q * 16 * T64;
+      Pack t;
+#pragma unroll
+      for (int k = 0; k < NW; ++k)
+        t.u[k] = __hip_atomic_load((const uint64_t *)p + k, __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) v[q][e] += (double)t.x[e];
+    }
+}
+
+template <class S>
+__device__ __forceinline__ void publish4(S *p, S a, S b, S c, S d) {
+  typedef S v4s __attribute__((ext_vector_type(4)));
+  constexpr int NW = (int)sizeof(v4s) / 8;
+  union Pack {
+    uint64_t u[NW];
+    v4s x;
+  } t;
+  t.x = v4s{a, b, c, d};
+#pragma unroll
+  for (int k = 0; k < NW; ++k)
+    __hip_atomic_store((uint64_t *)p + k, t.u[k], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// One split of a tile: publishes this thread's elements of V (its own base in
+// a 64 x 64 LDS tile) to w (its own base in the split's partial tile) and
+// counts the split.  True in the block that completes the tile, where all
+// partials may be read and smem is free.
+template <class S>
+__device__ __forceinline__ bool publish_split(const S *V, S *w, unsigned *cnt, int nsplit,
+                                              char *smem) {
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const S *v = V + q * 16 * VP;
+    publish4(w + q * 16 * T64, v[0], v[1], v[2], v[3]);
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // out before the counter moves
+  __syncthreads();
+  unsigned *last = (unsigned *)smem;
+  if (threadIdx.x == 0) *last = atomicAdd(cnt, 1u) == (unsigned)nsplit - 1;
+  __syncthreads();
+  if (!*last) return false;
+  __syncthreads();   // flag read by all before smem is used again
+  if (threadIdx.x == 0) *cnt = 0u;   // ready for the next launch
+  return true;
+}
+
 }  // namespace gcp
