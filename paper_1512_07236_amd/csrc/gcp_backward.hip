@@ -369,28 +369,30 @@ __global__ __launch_bounds__(256) void k_bstore(const void *planes, const double
   ((TB *)out)[i * Mp + j] = (TB)x;
 }
 
-// G = (g + g^T)/2 of the caller's M x M gradient over 64 x 64 tiles of the
-// padded matrix (zero outside M x M).
+// G = (g + g^T)/2 of the caller's M x M matrix over the padded matrix (zero
+// outside M x M).  Bound by HBM; M = 3000, FP64: 137 -> 31 us against reading
+// 16 consecutive elements per thread of every tile and its mirror.
 template <int PB>
 __global__ __launch_bounds__(256) void k_bload(const void *g, int64_t ldg, int dtype, int64_t M,
                                                int64_t Mp, void *G) {
   using TB = typename Enc<PB>::T;
-  __shared__ double hs[64][65], ht[64][65];
-  const int64_t I = (int64_t)blockIdx.y * 64, J = (int64_t)blockIdx.x * 64;
-  const int tid = threadIdx.x, row = tid >> 2, c0 = (tid & 3) * 16;
-  auto ld = [&](int64_t r, int64_t c) -> double {
-    if (r >= M || c >= M) return 0.0;
-    return dtype == GCP_DTYPE_F64 ? ((const double *)g)[r * ldg + c]
-                                  : (double)((const float *)g)[r * ldg + c];
-  };
-  for (int c = 0; c < 16; ++c) {
-    hs[row][c0 + c] = ld(I + row, J + c0 + c);
-    ht[row][c0 + c] = ld(J + row, I + c0 + c);
-  }
-  __syncthreads();
-  for (int c = 0; c < 16; ++c) {
-    const int64_t i = I + row, j = J + c0 + c;
-    ((TB *)G)[i * Mp + j] = (TB)(0.5 * (hs[row][c0 + c] + ht[c0 + c][row]));
+  __shared__ double ta[64][65], tb[64][65];
+  double ha[16], hb[16];
+  const SymPair p =
+      dtype == GCP_DTYPE_F64
+          ? sym_pair(blockIdx.x, M,
+                     [&](int64_t r, int64_t c) { return ((const double *)g)[r * ldg + c]; }, ha, hb,
+                     ta, tb)
+          : sym_pair(blockIdx.x, M,
+                     [&](int64_t r, int64_t c) { return (double)((const float *)g)[r * ldg + c]; },
+                     ha, hb, ta, tb);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  TB *__restrict__ O = (TB *)G;
+#pragma unroll
+  for (int q = 0; q < 16; ++q) {
+    const int r = 4 * q + wave;
+    O[(p.I + r) * Mp + p.J + lane] = (TB)(0.5 * (ha[q] + tb[lane][r]));
+    if (!p.diag) O[(p.J + r) * Mp + p.I + lane] = (TB)(0.5 * (hb[q] + ta[lane][r]));
   }
 }
 
@@ -494,7 +496,8 @@ hipError_t launch_bwd_store(int fprec, int bprec, const void *planes, const doub
 
 hipError_t launch_bwd_load(int bprec, const void *g, int64_t ldg, int dtype, int64_t M,
                            int64_t Mp, void *G, hipStream_t st) {
-  const dim3 grid((unsigned)(Mp / 64), (unsigned)(Mp / 64));
+  const int64_t nt = Mp / 64;
+  const unsigned grid = (unsigned)(nt * (nt + 1) / 2);
   if (bprec == GCP_FP64)
     k_bload<GCP_FP64><<<grid, 256, 0, st>>>(g, ldg, dtype, M, Mp, G);
   else if (bprec == GCP_FP32)

@@ -229,7 +229,7 @@ hipError_t launch_zero(void *p, int64_t nwords, hipStream_t st);
 hipError_t launch_hstats(const double *H, int64_t ldh, int64_t M, double *lo, double *hi,
                          double *hd, double *out, hipStream_t st);
 // out[0] = || (H + H^T)/2 - mu I ||_F^2 over M x M (fixed order); scratch holds
-// (Mp/64)^2 block partials.
+// one partial per pair of mirrored 64 x 64 tiles.
 hipError_t launch_hdev(const double *H, int64_t ldh, int64_t M, int64_t Mp, double mu,
                        double *scratch, double *out, hipStream_t st);
 

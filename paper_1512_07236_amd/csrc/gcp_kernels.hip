@@ -1101,34 +1101,29 @@ __global__ __launch_bounds__(256) void k_hfinal(const double *lo, const double *
 }
 
 // ||(H + H^T)/2 - mu I||_F^2 (the alpha search of the hole-particle guess):
-// 64 x 64 tiles, one partial per tile, then a fixed-order sum.
+// one partial per mirrored pair of 64 x 64 tiles, then a fixed-order sum.
+// M = 1500: 35 -> 7 us against uncoalesced reads of every tile and its mirror.
 __global__ __launch_bounds__(256) void k_hdev(const double *__restrict__ H, int64_t ldh, int64_t M,
                                               double mu, double *part) {
-  __shared__ double hs[64][65], ht[64][65], red[256];
-  const int64_t I = (int64_t)blockIdx.y * 64, J = (int64_t)blockIdx.x * 64;
-  const int tid = threadIdx.x, row = tid >> 2, c0 = (tid & 3) * 16;
-  for (int c = 0; c < 16; ++c) {
-    const int64_t gi = I + row, gj = J + c0 + c;
-    hs[row][c0 + c] = (gi < M && gj < M) ? H[gi * ldh + gj] : 0.0;
-    const int64_t ti = J + row, tj = I + c0 + c;
-    ht[row][c0 + c] = (ti < M && tj < M) ? H[ti * ldh + tj] : 0.0;
-  }
-  __syncthreads();
+  __shared__ double ta[64][65], tb[64][65], red[4];
+  double ha[16], hb[16];
+  const SymPair p = sym_pair(
+      blockIdx.x, M, [&](int64_t r, int64_t c) { return H[r * ldh + c]; }, ha, hb, ta, tb);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   double s = 0.0;
-  for (int c = 0; c < 16; ++c) {
-    const int64_t i = I + row, j = J + c0 + c;
+#pragma unroll
+  for (int q = 0; q < 16; ++q) {
+    const int r = 4 * q + wave;
+    const int64_t i = p.I + r, j = p.J + lane;
     if (i < M && j < M) {
-      const double x = 0.5 * (hs[row][c0 + c] + ht[c0 + c][row]) - (i == j ? mu : 0.0);
+      const double x = 0.5 * (ha[q] + tb[lane][r]) - (i == j ? mu : 0.0);
       s += x * x;
     }
   }
-  red[tid] = s;
+  s = wave_sum(p.diag ? s : 2.0 * s);
+  if (lane == 0) red[wave] = s;
   __syncthreads();
-  for (int w = 128; w > 0; w >>= 1) {
-    if (tid < w) red[tid] += red[tid + w];
-    __syncthreads();
-  }
-  if (tid == 0) part[(int64_t)blockIdx.y * gridDim.x + blockIdx.x] = red[0];
+  if (threadIdx.x == 0) part[blockIdx.x] = ((red[0] + red[1]) + red[2]) + red[3];
 }
 
 __global__ __launch_bounds__(256) void k_hdev_sum(const double *part, int n, double *out) {
@@ -1182,9 +1177,7 @@ __device__ __forceinline__ void init_tile(const InitArgs &a, int64_t I, int64_t 
       a.rD[i] = x - E::dec(op);
     }
     // row sum of D0 o D0 over the tile's 64 columns (fixed order)
-    double rs = xm * xm;
-#pragma unroll
-    for (int m = 1; m < 64; m <<= 1) rs += __shfl_xor(rs, m, 64);
+    const double rs = wave_sum(xm * xm);
     if (lane == 0) a.part[(J >> 6) * a.Mp + i] = rs;
   }
 }
@@ -1192,39 +1185,12 @@ __device__ __forceinline__ void init_tile(const InitArgs &a, int64_t I, int64_t 
 template <int P>
 __global__ __launch_bounds__(256) void k_init(InitArgs a) {
   __shared__ double ta[64][65], tb[64][65];
-  // block L -> (u, v), v <= u, of the row-major lower triangle
-  const int64_t L = blockIdx.x;
-  int64_t u = (int64_t)((sqrt(8.0 * (double)L + 1.0) - 1.0) * 0.5);
-  while (u * (u + 1) / 2 > L) --u;
-  while ((u + 1) * (u + 2) / 2 <= L) ++u;
-  const int64_t v = L - u * (u + 1) / 2;
-  const int64_t I = v * 64, J = u * 64;
-  const bool diag = u == v;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  // ha[q] = H[I+r][J+lane], hb[q] = H[J+r][I+lane]; a wave reads 64
-  // consecutive elements (512 bytes) of one row per load
   double ha[16], hb[16];
-#pragma unroll
-  for (int q = 0; q < 16; ++q) {
-    const int r = 4 * q + wave;
-    const int64_t gi = I + r, gj = J + lane;
-    ha[q] = (gi < a.M && gj < a.M) ? a.H[gi * a.ldh + gj] : 0.0;
-    const int64_t ti = J + r, tj = I + lane;
-    hb[q] = (!diag && ti < a.M && tj < a.M) ? a.H[ti * a.ldh + tj] : 0.0;
-  }
-#pragma unroll
-  for (int q = 0; q < 16; ++q) {
-    const int r = 4 * q + wave;
-    ta[r][lane] = ha[q];
-    tb[r][lane] = hb[q];
-  }
-  __syncthreads();
-  if (diag) {
-    init_tile<P>(a, I, J, ha, ta, wave, lane);
-  } else {
-    init_tile<P>(a, I, J, ha, tb, wave, lane);
-    init_tile<P>(a, J, I, hb, ta, wave, lane);
-  }
+  const SymPair p = sym_pair(
+      blockIdx.x, a.M, [&](int64_t r, int64_t c) { return a.H[r * a.ldh + c]; }, ha, hb, ta, tb);
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  init_tile<P>(a, p.I, p.J, ha, tb, wave, lane);
+  if (!p.diag) init_tile<P>(a, p.J, p.I, hb, ta, wave, lane);
 }
 
 // -------------------------------------------------------------- reductions
@@ -1458,9 +1424,9 @@ hipError_t launch_hstats(const double *H, int64_t ldh, int64_t M, double *lo, do
 
 hipError_t launch_hdev(const double *H, int64_t ldh, int64_t M, int64_t Mp, double mu,
                        double *scratch, double *out, hipStream_t st) {
-  const unsigned nb = (unsigned)(Mp / 64);
-  k_hdev<<<dim3(nb, nb), 256, 0, st>>>(H, ldh, M, mu, scratch);
-  k_hdev_sum<<<1, 256, 0, st>>>(scratch, (int)(nb * nb), out);
+  const int64_t nt = Mp / 64, np = nt * (nt + 1) / 2;
+  k_hdev<<<(unsigned)np, 256, 0, st>>>(H, ldh, M, mu, scratch);
+  k_hdev_sum<<<1, 256, 0, st>>>(scratch, (int)np, out);
   return hipGetLastError();
 }
 

@@ -90,6 +90,48 @@ __device__ __forceinline__ double wave_sum(double v) {
 typedef double v2d __attribute__((ext_vector_type(2)));
 typedef __attribute__((address_space(3))) void lds_void;
 
+// A symmetrised matrix (A + A^T)/2 is formed by one block of 256 threads per
+// mirrored pair (I, J), (J, I), I <= J, of 64 x 64 tiles: each tile of A is
+// read once, a wave taking 64 consecutive elements of a row per load, and the
+// transposed operand comes from LDS.  Block L of the nt (nt + 1)/2 pairs.
+// ha[q] = A[I + r][J + lane] and hb[q] = A[J + r][I + lane] with r = 4q +
+// wave; ta and tb hold the two tiles ([r][lane]).
+// ld(r, c) is called with r and c clamped to the M x M matrix and its value
+// dropped outside it, so that all 32 loads of a thread are in flight
+// together (loads under a condition go out one by one).
+struct SymPair {
+  int64_t I, J;
+  bool diag;
+};
+template <class LD>
+__device__ __forceinline__ SymPair sym_pair(int64_t L, int64_t M, LD &&ld, double (&ha)[16],
+                                            double (&hb)[16], double (*ta)[T64 + 1],
+                                            double (*tb)[T64 + 1]) {
+  int64_t u = (int64_t)((sqrt(8.0 * (double)L + 1.0) - 1.0) * 0.5);
+  while (u * (u + 1) / 2 > L) --u;
+  while ((u + 1) * (u + 2) / 2 <= L) ++u;
+  const int64_t v = L - u * (u + 1) / 2;
+  const SymPair p{v * 64, u * 64, u == v};
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int64_t cJ = p.J + lane, cI = p.I + lane, last = M - 1;
+#pragma unroll
+  for (int q = 0; q < 16; ++q) {
+    const int r = 4 * q + wave;
+    ha[q] = ld(p.I + r < M ? p.I + r : last, cJ < M ? cJ : last);
+    hb[q] = ld(p.J + r < M ? p.J + r : last, cI < M ? cI : last);
+  }
+#pragma unroll
+  for (int q = 0; q < 16; ++q) {
+    const int r = 4 * q + wave;
+    if (p.I + r >= M || cJ >= M) ha[q] = 0.0;
+    if (p.J + r >= M || cI >= M) hb[q] = 0.0;
+    ta[r][lane] = ha[q];
+    tb[r][lane] = hb[q];
+  }
+  __syncthreads();
+  return p;
+}
+
 // Upper-triangle tiles are ordered in G x G groups of the tile grid (the
 // diagonal groups are triangular), row-major inside a group; tile_of_index
 // gives tile L of that order in closed form (a search over the groups took
