@@ -824,7 +824,8 @@ __global__ __launch_bounds__(NTH16, 1) void k_gemm16(GemmArgs g) {
   const bool tvalid = tjj >= ti, dtile = tjj == ti;
   const int br = x >> 4, bc = x & 15;
   const int64_t i0 = arow0 + br * 8;
-  constexpr double S = 1.0 / (E::SC * E::SC);
+  // elements are kept in the stored units SC x (SC a power of two)
+  constexpr double SC = E::SC, INV = 1.0 / SC;
   T *__restrict__ Og = (T *)g.out;
   double a_coef = 0.0, b_coef = 0.0, e_coef = 0.0;
   if (g.mode == 1) update_coefs(g.method, g.coef[0], a_coef, b_coef, e_coef);
@@ -864,41 +865,43 @@ __global__ __launch_bounds__(NTH16, 1) void k_gemm16(GemmArgs g) {
         T dp[NP], op[NP];
 #pragma unroll
         for (int p = 0; p < NP; ++p) dp[p] = (uint16_t)(dv[p][e >> 1] >> (16 * (e & 1)));
-        const double v = (double)vr[e] * S;
+        const double v = (double)vr[e] * INV;   // SC times the product
         double prod, diff;
         if constexpr (MODE == 0) {
           double Dm, x2;
           if (DK != 0 && i == j) {
-            Dm = vrow[2 * TILE + br * 8 + r];
-            x2 = vrow[3 * TILE + br * 8 + r];
+            Dm = SC * vrow[2 * TILE + br * 8 + r];
+            x2 = SC * vrow[3 * TILE + br * 8 + r];
           } else {
-            Dm = E::dec(dp);
+            Dm = E::dec_s(dp);
             x2 = v + Dm * (vrow[br * 8 + r] + vcol[th * TILE + bc * 8 + e]);
           }
-          E::enc(x2, op);
-          const double x2m = (DK != 0 && i == j) ? x2 : E::dec(op);
-          if (DK != 0 && i == j) g.s2[i] = x2 - E::dec(op);
+          E::enc_s(x2, op);
+          const double x2m = (DK != 0 && i == j) ? x2 : E::dec_s(op);
+          if (DK != 0 && i == j) g.s2[i] = INV * (x2 - E::dec_s(op));
           prod = x2m * Dm;
           diff = x2m - Dm;
         } else {
-          double Dm, dn;
+          double Dm, dn, dx = 0.0;
           if (DK != 0 && i == j) {
-            Dm = vrow[2 * TILE + br * 8 + r];
-            dn = a_coef * Dm + b_coef * vrow[3 * TILE + br * 8 + r] + e_coef * vrow[4 * TILE + br * 8 + r];
+            const double d = vrow[2 * TILE + br * 8 + r];
+            dx = a_coef * d + b_coef * vrow[3 * TILE + br * 8 + r] + e_coef * vrow[4 * TILE + br * 8 + r];
+            Dm = SC * d;
+            dn = SC * dx;
           } else {
             T xp[NP];
 #pragma unroll
             for (int p = 0; p < NP; ++p) xp[p] = (uint16_t)(xv[p][e >> 1] >> (16 * (e & 1)));
-            Dm = E::dec(dp);
-            const double X2m = E::dec(xp);
+            Dm = E::dec_s(dp);
+            const double X2m = E::dec_s(xp);
             const double x3 = v + X2m * vcol[th * TILE + bc * 8 + e] + vrow[TILE + br * 8 + r] * Dm;
             dn = a_coef * Dm + b_coef * X2m + e_coef * x3;
           }
-          E::enc(dn, op);
-          const double dnm = (DK != 0 && i == j) ? dn : E::dec(op);
+          E::enc_s(dn, op);
+          const double dnm = (DK != 0 && i == j) ? dn : E::dec_s(op);
           if (DK != 0 && i == j) {
-            g.dg_new[i] = dn;
-            g.rD_new[i] = dn - E::dec(op);
+            g.dg_new[i] = dx;
+            g.rD_new[i] = INV * (dn - E::dec_s(op));
           }
           prod = dnm * dnm;
           diff = dnm - Dm;
@@ -909,9 +912,9 @@ __global__ __launch_bounds__(NTH16, 1) void k_gemm16(GemmArgs g) {
         rsum[r] += prod;
         if (DK == 0 || i != j) {
           csum[e] += prod;
-          tsum += 2.0 * diff * diff;
-        } else {
           tsum += diff * diff;
+        } else {
+          tsum += 0.5 * diff * diff;   // off-diagonal elements count twice, below
         }
       }
 #pragma unroll
@@ -984,27 +987,14 @@ __global__ __launch_bounds__(NTH16, 1) void k_gemm16(GemmArgs g) {
   // row sums: the 16 threads of a block row (lanes differing in bits 0..3)
 #pragma unroll
   for (int r = 0; r < 8; ++r) {
-    double v = rsum[r];
-    v += shfl_xor_d(v, 1);
-    v += shfl_xor_d(v, 2);
-    v += shfl_xor_d(v, 4);
-    v += shfl_xor_d(v, 8);
-    rsum[r] = v;
+    rsum[r] = row_sum(rsum[r]);
   }
   // column sums: the 4 block rows of a wave (bits 4..5), then the tile's waves
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
-    double v = csum[e];
-    v += shfl_xor_d(v, 16);
-    v += shfl_xor_d(v, 32);
-    csum[e] = v;
+    csum[e] = swap32_sum(swap16_sum(csum[e]));
   }
-  tsum += shfl_xor_d(tsum, 1);
-  tsum += shfl_xor_d(tsum, 2);
-  tsum += shfl_xor_d(tsum, 4);
-  tsum += shfl_xor_d(tsum, 8);
-  tsum += shfl_xor_d(tsum, 16);
-  tsum += shfl_xor_d(tsum, 32);
+  tsum = wave_sum(tsum);
   const int wt = x >> 6;   // wave within the tile
   if ((x & 15) == 0) {
 #pragma unroll
@@ -1017,10 +1007,11 @@ __global__ __launch_bounds__(NTH16, 1) void k_gemm16(GemmArgs g) {
   if (lane == 0) tp[th * WPT + wt] = tsum;
   __syncthreads();
   if (x < TILE && tvalid) {
-    const double rs = rp[th * TILE + x];
+    const double rs = INV * INV * rp[th * TILE + x];
     double cs = 0.0;
 #pragma unroll
     for (int w = 0; w < WPT; ++w) cs += cpart[(th * WPT + w) * TILE + x];
+    cs *= INV * INV;
     if (!dtile) {
       g.part[(int64_t)tjj * Mp + arow0 + x] = rs;
       g.part[(int64_t)ti * Mp + (int64_t)tjj * TILE + x] = cs;
@@ -1032,7 +1023,7 @@ __global__ __launch_bounds__(NTH16, 1) void k_gemm16(GemmArgs g) {
     double t = 0.0;
 #pragma unroll
     for (int w = 0; w < WPT; ++w) t += tp[tid * WPT + w];
-    g.tpart[2 * lin + tid] = t;
+    g.tpart[2 * lin + tid] = 2.0 * INV * INV * t;
   }
 }
 

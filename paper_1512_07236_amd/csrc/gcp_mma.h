@@ -53,8 +53,6 @@ __device__ __forceinline__ v4f mfma16(v4u a, v4u b, v4f c) {
                                                   __builtin_bit_cast(v8h, b), c, 0, 0, 0);
 }
 
-__device__ __forceinline__ double shfl_xor_d(double v, int m) { return __shfl_xor(v, m, 64); }
-
 // Sums over lanes in a fixed order, by rotations inside the rows of 16 lanes
 // (DPP) and swaps of rows and half waves: no LDS round trip per step, as a
 // general shuffle takes.  row_sum leaves the sum of its row of 16 lanes in

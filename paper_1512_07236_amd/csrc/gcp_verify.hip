@@ -70,8 +70,7 @@ __device__ __forceinline__ void verify_tile(const VerifyArgs &a, int L, char *sm
     }
 #pragma unroll
   for (int k = 0; k < NS; ++k) {
-#pragma unroll
-    for (int m = 1; m < 64; m <<= 1) v[k] += shfl_xor_d(v[k], m);
+    v[k] = wave_sum(v[k]);
     if (lane == 0) red[k * 4 + wave] = v[k];
   }
   __syncthreads();
