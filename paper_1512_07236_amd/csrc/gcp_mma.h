@@ -204,7 +204,7 @@ template <int P> struct TileCfg {
   static constexpr int KT = R128 ? 128 / ES / NP : 32;     // K values per stage
   static constexpr int ROWB = R128 ? 128 : 64 * NP;        // bytes per panel row per stage
   static constexpr int STAGE = 2 * TE * ROWB;              // bytes per stage
-  static constexpr int NBUF = KIND == 1 ? 4 : 2;           // stages in LDS
+  static constexpr int NBUF = KIND == 1 ? 4 : KIND >= 2 && NP <= 2 ? 3 : 2;   // stages in LDS
   static constexpr int SMEM = NBUF * STAGE;
   static constexpr int LPS = STAGE / 1024 / 4;             // 1 KiB loads per stage per wave
   static constexpr int NX = R128 ? 2 : NP;                 // 16-byte fragments per row
