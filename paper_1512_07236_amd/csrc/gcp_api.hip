@@ -72,6 +72,7 @@ struct gcp_ctx {
   gcp_options opt{};
   hipStream_t stream = nullptr;
   int device = 0;
+  int cus = 256;   // compute units
   // operand planes: D (double-buffered) and X2
   void *Dp[2] = {nullptr, nullptr};
   void *X2p = nullptr;
@@ -100,7 +101,7 @@ struct gcp_ctx {
   void *split_ws = nullptr;   // partial tiles of the K-split units
   unsigned *split_cnt = nullptr;   // their arrival counters
   unsigned *counter = nullptr;
-  unsigned *rcnt = nullptr;   // tiles done per 64-row block (tile kernels)
+  unsigned *rcnt = nullptr;   // tiles done per row block (tile kernels)
   Scalars *sc = nullptr;    // device
   Scalars *sc_host = nullptr;  // pinned
   double *hist = nullptr;   // device, (max_iter + 1) x 9
@@ -193,19 +194,24 @@ static void free_all(gcp_ctx *c) {
   c->events.clear();
 }
 
-// Product kernel of an encoding at size M.  FP64 and FP32 products run as 64 x
-// 64 tiles at every size.  The 16-bit pair kernel needs about 200 pairs of
-// 128 x 128 tiles to fill the chip (one block per CU); below that 64 x 64
-// tiles are faster.  Measured per product, 64 x 64 tiles / pairs, in us:
-//   FP16X3  M = 512: 22 / 56   1000: 29 / 72   2048: 53 / 137   3000: 127 / 126
-//   BF16X6  M = 512: 23 / 62   1000: 34 / 80   2048: 80 / 157   3000: 210 / 233
-// (at M = 3584 one round of 210 pairs takes little longer than the 156 of
-// M = 3000, while tiles grow with M^3.)  The ksplit option is the pair
-// kernel's.
+// Product kernel of an encoding at size M.
+//   32 x 32 tiles where 64 x 64 ones would leave most CUs idle: per product,
+//   32 x 32 / 64 x 64 tiles, in us:
+//     FP64    M = 256: 14 / 23   520: 22 / 32   900: 38 / 43   1200: 58 / 70   1500: 97 / 82
+//     FP32    M = 256: 13 / 20   520: 19 / 22   900: 29 / 29   1000: 38 / 34
+//     FP16X3  M = 256: 13 / 17   520: 18 / 22   900: 24 / 25   1000: 30 / 27
+//     BF16X6  M = 256: 15 / 21   520: 20 / 24   900: 33 / 32   1000: 42 / 36
+//   64 x 64 tiles above.  FP64 and FP32 keep them at every size.  The 16-bit
+//   pair kernel needs about 200 pairs of 128 x 128 tiles to fill the chip (one
+//   block per CU); 64 x 64 tiles / pairs, in us:
+//     FP16X3  M = 1000: 28 / 72   2048: 50 / 137   3000: 115 / 126   3500: 153 / 150
+//     BF16X6  M = 1000: 36 / 80   2048: 78 / 157   3000: 210 / 233   3584: 360 / 275
+//   (one round of 210 pairs, M = 3584, takes little longer than the 156 of
+//   M = 3000, while tiles grow with M^3).  The ksplit option is the pair
+//   kernel's.
 static int product_path(int prec, int64_t M, const gcp_options &o) {
-  if (elem_size(prec) != 2) return PATH_T64;
-  if (o.ksplit >= 2 || M > 3008) return PATH_PAIR;
-  return PATH_T64;
+  if (elem_size(prec) == 2 && (o.ksplit >= 2 || M > 3008)) return PATH_PAIR;
+  return M <= (prec == GCP_FP64 ? 1280 : 896) ? PATH_T32 : PATH_T64;
 }
 
 // Fold period of a product's FP32 accumulator over nk K stages, in stages:
@@ -223,16 +229,27 @@ static void init_prec_cfg(gcp_ctx *c, int k) {
   gcp_ctx::PrecCfg &q = c->pc[k];
   const int prec = q.prec;
   const int np = plane_count(prec);
-  int cus = 0;
-  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess ||
-      cus <= 0)
-    cus = 256;
+  const int cus = c->cus;
   // K stages: 128 bytes of a row, or 32 values of three planes
   const int nk = elem_size(prec) != 2 ? (int)(c->Mp * elem_size(prec) / 128)
                  : np <= 2            ? (int)(c->Mp * np / 64)
                                       : (int)(c->Mp / 32);
   q.nsplit = 1;
   q.ntail = 0;
+  if (q.path == PATH_T32) {
+    const int nt = (int)(c->Mp / 32);
+    q.ntpart = nt * (nt + 1) / 2;
+    q.nfull = q.ntpart;
+    // Every wave takes a quarter of the stages and folds each of them (with
+    // every second: the same time within 2 %, and the error of D 10 to 30 %
+    // larger in FP32, FP16X3 and BF16X6).  The coarse encodings fold every
+    // second: their error is that of the operands (BF16X3, M = 640: 8.8e-6
+    // either way).
+    q.fold = fold_period(c, prec, nk / 4.0);
+    const bool coarse = prec == GCP_BF16 || prec == GCP_FP16 || prec == GCP_BF16X3;
+    if (c->opt.fold_every <= 0 && coarse && q.fold < 2) q.fold = 2;
+    return;
+  }
   if (q.path == PATH_T64) {
     // Tiles are equal units of work.  Those of a last partial round over the
     // CUs (all of them when there are fewer than one round) would leave most
@@ -241,9 +258,8 @@ static void init_prec_cfg(gcp_ctx *c, int k) {
     // time: a K stage takes about 0.5 us in a block that is alone on its CU
     // (0.8 us with six products), and a split costs 2 us plus, per partial
     // tile, 1.2 us (FP64) or 0.6 us to publish and add.  Measured per product
-    // with 1 / 3 / 6 splits: FP64 M = 256 23 / 24 / 27, M = 512 32 / 29 / 33,
-    // M = 1536 115 / 87 / 95, M = 2048 197 / 160 / 152 us; FP16X3 M = 1000
-    // 31 / 29 / 36 us.  Up to GCP_STATIC_MAX_M the partials stay within 13 MB,
+    // with 1 / 3 / 6 splits: FP64 M = 1536 115 / 87 / 95, M = 2048 197 / 160 /
+    // 152 us; FP16X3 M = 1000 31 / 29 / 36 us.  Up to GCP_STATIC_MAX_M the partials stay within 13 MB,
     // for the static workspace of gcp_purify_static.
     const int nt = (int)(c->Mp / 64), ntiles = nt * (nt + 1) / 2, tail = ntiles % cus;
     const size_t unit = 64 * 64 * (size_t)(prec == GCP_FP64 ? 8 : 4);
@@ -305,10 +321,7 @@ static void init_prec_cfg(gcp_ctx *c, int k) {
 // round over the CUs are split as the forward's (init_prec_cfg), each of
 // their two products over half of the splits.
 static void init_bwd_cfg(gcp_ctx *c) {
-  int cus = 0;
-  if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess ||
-      cus <= 0)
-    cus = 256;
+  const int cus = c->cus;
   const int nt = (int)(c->Mp / 64), ntiles = nt * (nt + 1) / 2, tail = ntiles % cus;
   const int nk = (int)(c->Mp * elem_size(c->opt.bwd_precision) / 128);
   const double t_part = c->opt.bwd_precision == GCP_FP64 ? 1.2 : 0.6;
@@ -400,6 +413,9 @@ static void setup_ctx(gcp_ctx *c, int64_t M, const gcp_options &o, void *stream)
   c->opt = o;
   c->stream = (hipStream_t)stream;
   (void)hipGetDevice(&c->device);
+  if (hipDeviceGetAttribute(&c->cus, hipDeviceAttributeMultiprocessorCount, c->device) !=
+          hipSuccess || c->cus <= 0)
+    c->cus = 256;
   // the schedule's phases: an encoding that repeats the previous one adds none
   c->pc[0].prec = o.precision;
   c->pc[0].enter_ddbar = INFINITY;
@@ -451,7 +467,9 @@ template <class F>
 static void for_each_buffer(gcp_ctx *c, bool one_shot, F &&f) {
   const size_t Mp = (size_t)c->Mp;
   const size_t vec = Mp * sizeof(double);
-  const size_t nslots_max = Mp / 64;   // the initial guess uses 64-wide column slots
+  size_t nslots_max = Mp / 64;   // column slots of the initial guess and the 64-wide tiles
+  for (int k = 0; k < c->nprec; ++k)
+    if (c->pc[k].path == PATH_T32) nslots_max = Mp / 32;
   const size_t pb = plane_bytes(c);
   f(&c->Dp[0], pb);
   f(&c->Dp[1], pb);
@@ -471,12 +489,12 @@ static void for_each_buffer(gcp_ctx *c, bool one_shot, F &&f) {
   }
   f((void **)&c->part, nslots_max * vec);
   f((void **)&c->tpart, (size_t)c->ntpart * sizeof(double));
-  f((void **)&c->bpart, (size_t)2 * c->nred * sizeof(double));
+  f((void **)&c->bpart, (size_t)2 * 2 * c->nred * sizeof(double));   // row blocks of 32 or 64
   f((void **)&c->hvec, 3 * vec);
   f((void **)&c->counter, sizeof(unsigned));
   f((void **)&c->sc, sizeof(Scalars));
   f((void **)&c->hist, (size_t)(c->opt.max_iter + 1) * GCP_HIST_COLS * sizeof(double));
-  f((void **)&c->rcnt, (size_t)c->nred * sizeof(unsigned));
+  f((void **)&c->rcnt, (size_t)2 * c->nred * sizeof(unsigned));
   if (split_ws_bytes(c) > 0) f(&c->split_ws, split_ws_bytes(c));
   if (split_counters(c) > 0) f((void **)&c->split_cnt, (size_t)split_counters(c) * sizeof(unsigned));
   if (c->nprec > 1) f(&c->Xc, pb);
@@ -533,7 +551,7 @@ extern "C" int gcp_create(gcp_ctx **out, int64_t M, const gcp_options *opt, void
   if ((c->bcnt && hipMemsetAsync(c->bcnt, 0, btail * sizeof(unsigned), c->stream) != hipSuccess) ||
       (c->split_cnt && hipMemsetAsync(c->split_cnt, 0, (size_t)split_counters(c) * sizeof(unsigned),
                                      c->stream) != hipSuccess) ||
-      hipMemsetAsync(c->rcnt, 0, (size_t)c->nred * sizeof(unsigned), c->stream) != hipSuccess ||
+      hipMemsetAsync(c->rcnt, 0, (size_t)2 * c->nred * sizeof(unsigned), c->stream) != hipSuccess ||
       hipMemsetAsync(c->counter, 0, sizeof(unsigned), c->stream) != hipSuccess ||
       hipMemsetAsync(c->s2, 0, vec, c->stream) != hipSuccess ||
       hipStreamSynchronize(c->stream) != hipSuccess) {
@@ -640,6 +658,7 @@ static void setup_gemm(gcp_ctx *c, GemmArgs &g, int pi) {
   g.Mp = c->Mp;
   g.nt = (int)(c->Mp / 128);
   g.path = q.path;
+  g.cus = c->cus;
   g.fold = q.fold;
   g.nfull = q.nfull;
   g.nsplit = q.nsplit;
@@ -1477,7 +1496,7 @@ extern "C" int gcp_purify_static(const double *H, int64_t ldh, int64_t M, int64_
   // the array keeps the previous call's contents: the arrival counters and
   // the X2 diagonal residuals must start at zero
   if (launch_zero(c.split_cnt, split_counters(&c), c.stream) != hipSuccess ||
-      launch_zero(c.rcnt, c.nred, c.stream) != hipSuccess ||
+      launch_zero(c.rcnt, 2 * c.nred, c.stream) != hipSuccess ||
       launch_zero(c.counter, 1, c.stream) != hipSuccess ||
       launch_zero(c.s2, 2 * c.Mp, c.stream) != hipSuccess) {
     g_create_error = "gcp_purify_static: clearing the workspace failed";

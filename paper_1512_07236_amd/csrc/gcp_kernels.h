@@ -84,7 +84,7 @@ struct RedArgs {
   const double *extra;
   double *bpart;
   unsigned *counter;
-  unsigned *rcnt;      // tiles done per 64-row block (tile kernels; self-resetting)
+  unsigned *rcnt;      // tiles done per row block (tile kernels; self-resetting)
   const double *tpart;
   int ntiles;
   int iter, max_iter;
@@ -98,9 +98,10 @@ struct RedArgs {
   double *hist;
 };
 
-// Product kernels: one 64 x 64 tile per block, with the reduction that follows
-// it (every encoding), or pairs of 128 x 128 tiles (16-bit).
-enum { PATH_T64 = 0, PATH_PAIR = 1 };
+// Product kernels: one 32 x 32 or 64 x 64 tile per block, with the reduction
+// that follows the product (every encoding), or pairs of 128 x 128 tiles
+// (16-bit).
+enum { PATH_T64 = 0, PATH_PAIR = 1, PATH_T32 = 2 };
 
 struct GemmArgs {
   const void *A;       // left operand planes (rows of D or X2)
@@ -109,6 +110,7 @@ struct GemmArgs {
   int64_t Mp;          // padded size (a multiple of the path's tile edge)
   int nt;              // Mp / 128 (PATH_PAIR)
   int path;            // PATH_*
+  int cus;             // compute units of the GPU
   int mode;            // 0: X2 = D D, 1: D_{n+1} = (1-2c) D + (2+2c) X2 - 2 X2 D
   int fold;            // fold period of the main accumulator, in K stages
   // Blocks [0, nfull) compute whole units (tiles, or tile pairs); the
@@ -130,7 +132,7 @@ struct GemmArgs {
   double *rD_new;      // its residual                    (mode 1)
   double *part;        // row sums [column tile][Mp]
   double *tpart;       // tile sums [ntiles]
-  RedArgs red;         // PATH_T64: the reduction that follows the product
+  RedArgs red;         // PATH_T32, PATH_T64: the reduction that follows the product
   const double *coef;  // coef[0] = c_n (mode 1)
   // non-NULL: the launch does nothing once *status is non-zero (the solve
   // has stopped; later launches of a batch enqueued ahead are void)

@@ -112,38 +112,43 @@ __device__ void scalar_step(const RedArgs &a, double sum_out, double sum_extra,
 }
 
 // ------------------------------------------------- epilogue of one tile
-// The epilogues work on 64 x 64 tiles (ti <= tj) of the output with 256
-// threads: thread tid holds columns 4 (tid % 16) .. +3 of the rows
-// 16 q + tid / 16, q = 0..3, so that a row of the tile is one contiguous
-// access of 16 lanes.  The encoded results also go to LDS, from which the
-// mirrored tile is written as rows.
-template <int P> struct FinCfg {
+// The epilogues work on TE x TE tiles (64 or 32; ti <= tj) of the output with
+// 256 threads: TE/4 lanes take a row, 4 columns each, so that it is one
+// contiguous access; thread tid holds the rows RP q + tid / (TE/4), q < NQ.
+// The encoded results also go to LDS, from which the mirrored tile is written
+// as rows.
+template <int P, int TE> struct FinCfg {
   using T = typename Enc<P>::T;
-  static constexpr int QC = sizeof(T) == 8 ? 2 : 4;   // rows of a thread taken together
-  static constexpr int V = Enc<P>::NP * T64 * VP * (int)sizeof(T);   // encoded results
-  static constexpr int SUMS = (V + 15) / 16 * 16;                    // then FP64 sums
-  static constexpr int SMEM_FIN = SUMS + (T64 + 4 * T64 + 4) * 8;
-  static constexpr int SMEM_RED = 8 * 64 * 8;                        // finish_rows
+  static constexpr int RP = 1024 / TE, NQ = TE / RP;
+  static constexpr int QC = sizeof(T) == 8 && NQ > 2 ? 2 : NQ;   // rows of a thread taken together
+  static constexpr int VP = TE + 1;                   // LDS row pitch (elements)
+  static constexpr int V = Enc<P>::NP * TE * VP * (int)sizeof(T);   // encoded results
+  static constexpr int SUMS = (V + 15) / 16 * 16;                   // then FP64 sums
+  static constexpr int SMEM_FIN = SUMS + (TE + 4 * TE + 4) * 8;
+  static constexpr int SMEM_RED = 8 * 64 * 8;                       // finish_rows
   static constexpr int SMEM = SMEM_FIN > SMEM_RED ? SMEM_FIN : SMEM_RED;
 };
 
-// Row block R (64 rows) is complete when all nt64 tiles that touch it have
-// stored their row sums.  The block that completes it adds the slots (wave q
-// the slots s = q (mod 4) in ascending order, then the four wave sums), and
+// Row block R (TE rows) is complete when all nt tiles that touch it have
+// stored their row sums.  The block that completes it adds the slots (the
+// q-th of its 256/TE groups of threads the slots s = q (mod 256/TE) in
+// ascending order, then the group sums in order), and
 // the block that completes the last row block adds the block sums and the
 // tile sums in a fixed order and runs the scalar step: the sums do not depend
 // on the order in which blocks finish.  Sums that cross blocks inside the
 // launch are stored and loaded at agent scope (the XCDs' L2s are not coherent
 // for plain accesses) and are out before the counters move.
-__device__ __forceinline__ void finish_rows(const RedArgs &a, int ti, int tj, int nt64,
+template <int TE>
+__device__ __forceinline__ void finish_rows(const RedArgs &a, int ti, int tj, int nt,
                                             double *sm) {
-  const int tid = threadIdx.x, lane = tid & 63, q = tid >> 6;
+  constexpr int NG = 256 / TE;
+  const int tid = threadIdx.x, lane = tid & 63, row = tid % TE, q = tid / TE;
   int *flag = (int *)sm;
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   __syncthreads();
   if (tid == 0) {
-    int f = atomicAdd(a.rcnt + ti, 1u) == (unsigned)nt64 - 1 ? 1 : 0;
-    if (tj != ti && atomicAdd(a.rcnt + tj, 1u) == (unsigned)nt64 - 1) f |= 2;
+    int f = atomicAdd(a.rcnt + ti, 1u) == (unsigned)nt - 1 ? 1 : 0;
+    if (tj != ti && atomicAdd(a.rcnt + tj, 1u) == (unsigned)nt - 1) f |= 2;
     *flag = f;
   }
   __syncthreads();
@@ -153,25 +158,29 @@ __device__ __forceinline__ void finish_rows(const RedArgs &a, int ti, int tj, in
   for (int h = 0; h < 2; ++h) {
     if (!((f >> h) & 1)) continue;   // block-uniform
     const int R = h ? tj : ti;
-    const int64_t i = (int64_t)R * 64 + lane;
+    const int64_t i = (int64_t)R * TE + row;
     double w = 0.0;
 #pragma unroll 8
-    for (int s = q; s < nt64; s += 4) w += ld_agent(a.part + (int64_t)s * a.Mp + i);
+    for (int s = q; s < nt; s += NG) w += ld_agent(a.part + (int64_t)s * a.Mp + i);
     __syncthreads();
-    sm[q * 64 + lane] = w;
+    sm[tid] = w;
     __syncthreads();
-    if (q == 0) {
-      double v = ((sm[lane] + sm[64 + lane]) + sm[128 + lane]) + sm[192 + lane];
-      a.out[i] = v;
-      double e = a.extra ? ld_agent(a.extra + i) : 0.0;
+    if (tid < 64) {   // whole wave; lanes past the block's rows add nothing
+      double v = 0.0, x = 0.0;
+      if (tid < TE) {
+#pragma unroll
+        for (int k = 0; k < NG; ++k) v += sm[k * TE + tid];
+        a.out[i] = v;
+        if (a.extra) x = ld_agent(a.extra + i);
+      }
       v = wave_sum(v);
-      e = wave_sum(e);
-      if (lane == 0) {
+      x = wave_sum(x);
+      if (tid == 0) {
         st_agent(a.bpart + 2 * R, v);
-        st_agent(a.bpart + 2 * R + 1, e);
+        st_agent(a.bpart + 2 * R + 1, x);
         a.rcnt[R] = 0u;   // ready for the next launch
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        flag[2 * 256] = atomicAdd(a.counter, 1u) == (unsigned)nt64 - 1;
+        flag[2 * 256] = atomicAdd(a.counter, 1u) == (unsigned)nt - 1;
       }
     }
     __syncthreads();
@@ -179,7 +188,7 @@ __device__ __forceinline__ void finish_rows(const RedArgs &a, int ti, int tj, in
   }
   if (!last) return;
   double b1 = 0.0, b2 = 0.0, b3 = 0.0;
-  for (int b = tid; b < nt64; b += 256) {
+  for (int b = tid; b < nt; b += 256) {
     b1 += ld_agent(a.bpart + 2 * b);
     b2 += ld_agent(a.bpart + 2 * b + 1);
   }
@@ -190,9 +199,10 @@ __device__ __forceinline__ void finish_rows(const RedArgs &a, int ti, int tj, in
   b3 = wave_sum(b3);
   __syncthreads();
   if (lane == 0) {
-    sm[q] = b1;
-    sm[4 + q] = b2;
-    sm[8 + q] = b3;
+    const int wave = tid >> 6;
+    sm[wave] = b1;
+    sm[4 + wave] = b2;
+    sm[8 + wave] = b3;
   }
   __syncthreads();
   if (tid != 0) return;
@@ -212,22 +222,23 @@ __device__ __forceinline__ void finish_rows(const RedArgs &a, int ti, int tj, in
 // Bound by the chain of memory round trips, and for many tiles by vector
 // instructions (about 100 per element before the diagonal cases and the
 // scalings went, 40 now).
-template <int P, int MODE, bool DT, class V>
+template <int P, int TE, int MODE, bool DT, class V>
 __device__ __forceinline__ void finish_tile(const GemmArgs &g, int ti, int tj, int lin, V &&vload,
                                             char *smem) {
   using E = Enc<P>;
   using T = typename E::T;
   typedef T v4t __attribute__((ext_vector_type(4)));
-  constexpr int NP = E::NP;
+  using F = FinCfg<P, TE>;
+  constexpr int NP = E::NP, RP = F::RP, NQ = F::NQ, QC = F::QC, VP = F::VP, LR = TE / 4;
   constexpr double SC = E::SC, INV = 1.0 / SC;
-  const int64_t Mp = g.Mp, i0 = (int64_t)ti * T64, j0 = (int64_t)tj * T64;
+  const int64_t Mp = g.Mp, i0 = (int64_t)ti * TE, j0 = (int64_t)tj * TE;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int c4 = (tid & 15) * 4, r0 = tid >> 4;
+  const int c4 = tid % LR * 4, r0 = tid / LR;
   const T *__restrict__ Ag = (const T *)g.A;
   const T *__restrict__ Bg = (const T *)g.B;
   T *__restrict__ Og = (T *)g.out;
   T *Vt = (T *)smem;
-  double rDj[4], colacc[4] = {}, rowacc[4], tacc = 0.0;
+  double rDj[4], colacc[4] = {}, rowacc[NQ], tacc = 0.0;
 #pragma unroll
   for (int e = 0; e < 4; ++e) rDj[e] = g.rD[j0 + c4 + e];
   double a_coef = 0.0, b_coef = 0.0, e_coef = 0.0;
@@ -235,14 +246,13 @@ __device__ __forceinline__ void finish_tile(const GemmArgs &g, int ti, int tj, i
   // the inputs of QC rows are loaded together, before any of their stores (the
   // compiler cannot tell the output from the inputs); four FP64 rows would
   // not fit the registers of four blocks per CU
-  constexpr int QC = FinCfg<P>::QC;
 #pragma unroll
-  for (int q0 = 0; q0 < 4; q0 += QC) {
+  for (int q0 = 0; q0 < NQ; q0 += QC) {
     v4t dv[QC][NP], xv[QC][NP];
     double ri[QC], dgi[QC], d2i[QC], d3i[QC];   // (the last three: the diagonal, DT)
 #pragma unroll
     for (int u = 0; u < QC; ++u) {
-      const int64_t i = i0 + (q0 + u) * 16 + r0;
+      const int64_t i = i0 + (q0 + u) * RP + r0;
 #pragma unroll
       for (int p = 0; p < NP; ++p) {
         dv[u][p] = *(const v4t *)(Bg + eoff<P>(i, j0 + c4, p, Mp));
@@ -259,7 +269,7 @@ __device__ __forceinline__ void finish_tile(const GemmArgs &g, int ti, int tj, i
     vload(q0, v);
 #pragma unroll
     for (int u = 0; u < QC; ++u) {
-      const int q = q0 + u, row = q * 16 + r0;
+      const int q = q0 + u, row = q * RP + r0;
       const int64_t i = i0 + row;
       v4t ov[NP];
       double rs = 0.0;
@@ -312,7 +322,7 @@ __device__ __forceinline__ void finish_tile(const GemmArgs &g, int ti, int tj, i
 #pragma unroll
         for (int p = 0; p < NP; ++p) {
           ov[p][e] = op[p];
-          Vt[(p * T64 + row) * VP + c4 + e] = op[p];
+          Vt[(p * TE + row) * VP + c4 + e] = op[p];
         }
         if (lower) continue;   // covered by the mirror of (j, i)
         rs += prod;
@@ -330,18 +340,20 @@ __device__ __forceinline__ void finish_tile(const GemmArgs &g, int ti, int tj, i
       }
     }
   }
-  double *rp = (double *)(smem + FinCfg<P>::SUMS);   // [64] row sums
-  double *cp = rp + T64;                             // [4 waves][64] column sums
-  double *tp = cp + 4 * T64;                         // [4 waves]
+  double *rp = (double *)(smem + F::SUMS);   // [TE] row sums
+  double *cp = rp + TE;                      // [4 waves][TE] column sums
+  double *tp = cp + 4 * TE;                  // [4 waves]
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const double x = row_sum(rowacc[q]);
-    if ((lane & 15) == 0) rp[q * 16 + r0] = x;
+  for (int q = 0; q < NQ; ++q) {
+    const double x = TE == 64 ? row_sum(rowacc[q]) : sum8(rowacc[q]);
+    if (lane % LR == 0) rp[q * RP + r0] = x;
   }
 #pragma unroll
   for (int e = 0; e < 4; ++e) {
-    const double x = swap32_sum(swap16_sum(colacc[e]));
-    if (lane < 16) cp[wave * T64 + c4 + e] = x;
+    double x = colacc[e];
+    if (TE == 32) x += dpp_d<0x128>(x);   // row_ror:8
+    x = swap32_sum(swap16_sum(x));
+    if (lane < LR) cp[wave * TE + c4 + e] = x;
   }
   tacc = wave_sum(tacc);
   if (lane == 0) tp[wave] = tacc;
@@ -349,8 +361,8 @@ __device__ __forceinline__ void finish_tile(const GemmArgs &g, int ti, int tj, i
   // mirrored tile: row j0 + row, columns i0 + c4 .. +3.  A diagonal tile is
   // written whole from here, its lower half from the upper one.
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int row = q * 16 + r0;
+  for (int q = 0; q < NQ; ++q) {
+    const int row = q * RP + r0;
 #pragma unroll
     for (int p = 0; p < NP; ++p) {
       v4t w;
@@ -358,15 +370,15 @@ __device__ __forceinline__ void finish_tile(const GemmArgs &g, int ti, int tj, i
       for (int e = 0; e < 4; ++e) {
         const int c = c4 + e;
         const bool up = DT && row < c;
-        w[e] = Vt[(p * T64 + (up ? row : c)) * VP + (up ? c : row)];
+        w[e] = Vt[(p * TE + (up ? row : c)) * VP + (up ? c : row)];
       }
       *(v4t *)(Og + eoff<P>(j0 + row, i0 + c4, p, Mp)) = w;
     }
   }
-  if (tid < T64) {
+  if (tid < TE) {
     constexpr double I2 = INV * INV;
     const double rs = I2 * rp[tid];
-    const double cs = I2 * (((cp[tid] + cp[T64 + tid]) + cp[2 * T64 + tid]) + cp[3 * T64 + tid]);
+    const double cs = I2 * (((cp[tid] + cp[TE + tid]) + cp[2 * TE + tid]) + cp[3 * TE + tid]);
     if constexpr (!DT) {
       st_agent(g.part + (int64_t)tj * Mp + i0 + tid, rs);
       st_agent(g.part + (int64_t)ti * Mp + j0 + tid, cs);
@@ -378,17 +390,17 @@ __device__ __forceinline__ void finish_tile(const GemmArgs &g, int ti, int tj, i
   }
 }
 
-template <int P, class V>
+template <int P, int TE, class V>
 __device__ __forceinline__ void finish_any(const GemmArgs &g, int ti, int tj, int lin, V &&vload,
                                            char *smem) {
   if (g.mode == 0) {
-    if (ti != tj) finish_tile<P, 0, false>(g, ti, tj, lin, vload, smem);
-    else finish_tile<P, 0, true>(g, ti, tj, lin, vload, smem);
+    if (ti != tj) finish_tile<P, TE, 0, false>(g, ti, tj, lin, vload, smem);
+    else finish_tile<P, TE, 0, true>(g, ti, tj, lin, vload, smem);
   } else {
-    if (ti != tj) finish_tile<P, 1, false>(g, ti, tj, lin, vload, smem);
-    else finish_tile<P, 1, true>(g, ti, tj, lin, vload, smem);
+    if (ti != tj) finish_tile<P, TE, 1, false>(g, ti, tj, lin, vload, smem);
+    else finish_tile<P, TE, 1, true>(g, ti, tj, lin, vload, smem);
   }
-  finish_rows(g.red, ti, tj, (int)(g.Mp / T64), (double *)smem);
+  finish_rows<TE>(g.red, ti, tj, (int)(g.Mp / TE), (double *)smem);
 }
 
 // ---------------------------------------------------- tile product kernel
@@ -402,14 +414,14 @@ __device__ __forceinline__ void finish_any(const GemmArgs &g, int ti, int tj, in
 // Small tiles keep several blocks on a CU, so that the epilogue of one runs
 // under the products of the others, and fill the chip at small M.  Per
 // product, against 128 x 128 tiles of one block's 64 x 64 waves (16-bit:
-// pairs) followed by a reduction launch, in us: FP64 M = 256 55 -> 23,
-// M = 2048 310 -> 152, M = 4096 1360 -> 997; FP32 M = 4096 670 -> 575; FP16X3
-// M = 1000 80 -> 29, M = 2048 145 -> 53.
+// pairs) followed by a reduction launch, in us: FP64 M = 2048 310 -> 152,
+// M = 4096 1360 -> 997; FP32 M = 4096 670 -> 575; FP16X3 M = 1000 80 -> 28,
+// M = 2048 145 -> 50.
 template <int P> struct TileKernel {
   using C = TileCfg<P>;
   static constexpr int VS = T64 * VP * (int)sizeof(typename C::S);
   static constexpr int MM = C::SMEM > VS ? C::SMEM : VS;
-  static constexpr int SMEM = FinCfg<P>::SMEM > MM ? FinCfg<P>::SMEM : MM;
+  static constexpr int SMEM = FinCfg<P, T64>::SMEM > MM ? FinCfg<P, T64>::SMEM : MM;
   static constexpr int BLOCKS = C::KIND == 0 ? 4 : C::KIND == 1 ? 2 : 3;   // per CU
 };
 
@@ -442,8 +454,8 @@ __global__ __launch_bounds__(NTH, (TileKernel<P>::BLOCKS)) void k_tile(GemmArgs 
   if (split >= 0 &&
       !publish_split(V, (S *)w0 + split * ps, g.cnt + (lin - g.nfull), g.nsplit, smem))
     return;
-  constexpr int QC = FinCfg<P>::QC;
-  finish_any<P>(g, ti, tj, lin, [&](int q0, double (&v)[QC][4]) {
+  constexpr int QC = FinCfg<P, T64>::QC;
+  finish_any<P, T64>(g, ti, tj, lin, [&](int q0, double (&v)[QC][4]) {
     if (split >= 0) {
       add_partials(w0 + q0 * 16 * T64, ps, g.nsplit, v);
       return;
@@ -458,6 +470,27 @@ __global__ __launch_bounds__(NTH, (TileKernel<P>::BLOCKS)) void k_tile(GemmArgs 
       static_assert(QC == 4, "all rows at once");
       __syncthreads();
     }
+  }, smem);
+}
+
+// One 32 x 32 upper tile per block (small_product), for products whose 64 x
+// 64 tiles would leave most CUs idle behind the K loops of few blocks: at
+// M = 256 the ten 64 x 64 tiles of an FP64 product spend 10 of their 19 us
+// there; with 36 tiles, each on four independent waves, the product takes 14
+// us instead of 23.
+template <int P, int NB>
+__global__ __launch_bounds__(NTH) void k_small(GemmArgs g) {
+  constexpr int TE = 32;
+  __shared__ __attribute__((aligned(16))) char smem[SmallCfg<P, NB>::SMEM];
+  static_assert(SmallCfg<P, NB>::SMEM >= FinCfg<P, TE>::SMEM, "the epilogue fits");
+  if (g.status && *g.status != 0) return;   // the solve has stopped
+  int ti, tj, lin;
+  tile_of_block(blockIdx.x, (int)gridDim.x, (int)(g.Mp / TE), ti, tj, lin);
+  double x[4];
+  small_product<P, NB>(g.A, g.B, (int64_t)ti * TE, (int64_t)tj * TE, g.Mp, smem, g.fold, x);
+  finish_any<P, TE>(g, ti, tj, lin, [&](int, double (&v)[1][4]) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[0][e] = x[e];
   }, smem);
 }
 
@@ -1351,6 +1384,14 @@ hipError_t launch_convert(int pa, int pb, const void *in, const double *diag, vo
 // ---------------------------------------------------------------- dispatch
 template <int P>
 static hipError_t launch_gemm_p(const GemmArgs &g, hipStream_t st) {
+  if (g.path == PATH_T32) {
+    const int nt = (int)(g.Mp / 32);
+    const unsigned n = (unsigned)(nt * (nt + 1) / 2);
+    // deep rings (one block per CU) while there is one tile per CU
+    if ((int)n <= g.cus) k_small<P, Enc<P>::NP == 3 ? 3 : 4><<<n, NTH, 0, st>>>(g);
+    else k_small<P, 2><<<n, NTH, 0, st>>>(g);
+    return hipGetLastError();
+  }
   const int nt = (int)(g.Mp / T64), ntail = nt * (nt + 1) / 2 - g.nfull;
   if constexpr (Enc<P>::KIND >= 2) {
     if (g.path == PATH_PAIR) {

@@ -81,6 +81,13 @@ __device__ __forceinline__ double swap32_sum(double v) {
   const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(v), __double2hiint(v), false, false);
   return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
 }
+// sum of the aligned group of 8 lanes, in every lane of it
+__device__ __forceinline__ double sum8(double v) {
+  v += dpp_d<0xB1>(v);    // quad_perm [1, 0, 3, 2]
+  v += dpp_d<0x4E>(v);    // quad_perm [2, 3, 0, 1]
+  v += dpp_d<0x141>(v);   // row_half_mirror
+  return v;
+}
 __device__ __forceinline__ double wave_sum(double v) {
   return swap32_sum(swap16_sum(row_sum(v)));
 }
@@ -506,6 +513,159 @@ __device__ __forceinline__ bool publish_split(const S *V, S *w, unsigned *cnt, i
   __syncthreads();   // flag read by all before smem is used again
   if (threadIdx.x == 0) *cnt = 0u;   // ready for the next launch
   return true;
+}
+
+// ------------------------------------------------------ 32 x 32 tiles
+// For products of few tiles: a 32 x 32 tile per block, whose four waves take
+// every fourth K stage of the whole tile (2 x 2 MFMA blocks each) through LDS
+// rings of their own, without barriers; their totals are added in FP64.
+template <int P, int NB_> struct SmallCfg {
+  using C = TileCfg<P>;
+  using Acc = typename C::Acc;
+  using S = typename C::S;
+  static constexpr int TE = 32, NB = NB_, PD = NB - 1;   // stages in a wave's ring, ahead
+  static constexpr int STAGE = 2 * TE * C::ROWB;         // bytes
+  static constexpr int LPS = STAGE / 1024;               // loads per stage
+  static constexpr int RING = NB * STAGE;
+  static constexpr int SMEM = 4 * RING;
+  static_assert(PD * LPS <= 63 && RING >= TE * (TE + 1) * (int)sizeof(S), "vmcnt range, result fits");
+};
+
+// v[e] = element (row, c4 + e) of the tile at (arow0, brow0) for row = tid / 8
+// and c4 = 4 (tid % 8).  Ends with a barrier: smem is free.
+template <int P, int NB>
+__device__ __forceinline__ void small_product(const void *A, const void *B, int64_t arow0,
+                                              int64_t brow0, int64_t Mp, char *smem, int fold,
+                                              double (&v)[4]) {
+  using C = TileCfg<P>;
+  using Z = SmallCfg<P, NB>;
+  using Acc = typename C::Acc;
+  using S = typename C::S;
+  constexpr int KIND = C::KIND, NX = C::NX, LPS = Z::LPS, PD = Z::PD, TE = Z::TE;
+  constexpr bool R128 = C::R128;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l16 = lane & 15, lg = lane >> 4, nk = (int)(Mp / C::KT);
+  const int64_t rowb = Mp * C::NP * C::ES;
+  const char *Ab = (const char *)A + arow0 * rowb, *Bb = (const char *)B + brow0 * rowb;
+  char *ring = smem + wave * Z::RING;
+  // 128-byte rows: 8 rows per load; 64-byte rows of a plane: 16
+  constexpr int RPL = R128 ? 8 : 16, LPA = TE / RPL;   // rows per load, loads per panel (and plane)
+  uint32_t voff[LPS];
+#pragma unroll
+  for (int q = 0; q < LPS; ++q) {
+    const int p = q / (2 * LPA), R = q % LPA * RPL + (R128 ? lane >> 3 : lane >> 2);
+    voff[q] = (uint32_t)(R * rowb) +
+              (R128 ? ((lane & 7) ^ (R & 7)) * 16
+                    : p * 64 + ((lane & 3) ^ (((R >> 1) ^ (R >> 3)) & 3)) * 16);
+  }
+  auto issue = [&](int kt, char *st) {
+    const char *pa = Ab + (int64_t)kt * C::ROWB, *pb = Bb + (int64_t)kt * C::ROWB;
+#pragma unroll
+    for (int q = 0; q < LPS; ++q)
+      __builtin_amdgcn_global_load_lds((const void *)((q % (2 * LPA) < LPA ? pa : pb) + voff[q]),
+                                       (lds_void *)(st + q * 1024), 16, 0, 0);
+  };
+  auto frag = [&](const char *st, int pan, int b, int x) -> v4u {   // panel 0: A, 1: B
+    const int R = b * 16 + l16;
+    if constexpr (R128)
+      return *(const v4u *)(st + (pan * TE + R) * 128 + ((x * 4 + lg) ^ (R & 7)) * 16);
+    else
+      return *(const v4u *)(st + ((x * 2 + pan) * TE + R) * 64 +
+                            (lg ^ (((R >> 1) ^ (R >> 3)) & 3)) * 16);
+  };
+  Acc acc[2][2], tot[2][2];
+#pragma unroll
+  for (int bi = 0; bi < 2; ++bi)
+#pragma unroll
+    for (int bj = 0; bj < 2; ++bj) acc[bi][bj] = tot[bi][bj] = Acc{};
+  constexpr int NPR = C::NP == 1 ? 2 : Enc<P>::NPROD;
+  constexpr int PA[6] = {0, 0, 1, 1, 0, 2};
+  constexpr int PB2[6] = {0, 1, 0, 1, 2, 0};
+  constexpr int AHEAD = (PD - 1) * LPS;
+  constexpr int WAIT = (AHEAD & 0xF) | ((AHEAD >> 4) << 14) | (0x7 << 4);
+  int left = fold;
+#pragma unroll
+  for (int s = 0; s < PD; ++s)
+    if (wave + 4 * s < nk) issue(wave + 4 * s, ring + s * Z::STAGE);
+  int buf = 0;
+  for (int kt = wave; kt < nk; kt += 4) {
+    if (PD > 1 && kt + 4 * (PD - 1) < nk)
+      __builtin_amdgcn_s_waitcnt(WAIT);
+    else
+      __builtin_amdgcn_s_waitcnt(0);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    const char *st = ring + buf * Z::STAGE;
+    v4u af[2][NX], bf[2][NX];
+#pragma unroll
+    for (int x = 0; x < NX; ++x)
+#pragma unroll
+      for (int b = 0; b < 2; ++b) {
+        af[b][x] = frag(st, 0, b, x);
+        bf[b][x] = frag(st, 1, b, x);
+      }
+    __builtin_amdgcn_sched_barrier(0);
+    // the buffer of the previous stage: its fragments have been used
+    if (kt + 4 * PD < nk) issue(kt + 4 * PD, ring + (buf + PD) % NB * Z::STAGE);
+    __builtin_amdgcn_sched_barrier(0);
+    buf = buf + 1 == NB ? 0 : buf + 1;
+    if constexpr (KIND <= 1) {
+      constexpr int NE = KIND == 0 ? 2 : 4;
+      typedef S vs __attribute__((ext_vector_type(NE)));
+#pragma unroll
+      for (int x = 0; x < NX; ++x)
+#pragma unroll
+        for (int e = 0; e < NE; ++e)
+#pragma unroll
+          for (int bi = 0; bi < 2; ++bi)
+#pragma unroll
+            for (int bj = 0; bj < 2; ++bj)
+              acc[bi][bj] = mfma(__builtin_bit_cast(vs, bf[bj][x])[e],
+                                 __builtin_bit_cast(vs, af[bi][x])[e], acc[bi][bj]);
+    } else {
+#pragma unroll
+      for (int pr = 0; pr < NPR; ++pr)
+#pragma unroll
+        for (int bi = 0; bi < 2; ++bi)
+#pragma unroll
+          for (int bj = 0; bj < 2; ++bj) {
+            const int xa = C::NP == 1 ? pr : PA[pr], xb = C::NP == 1 ? pr : PB2[pr];
+            acc[bi][bj] = mfma16<KIND>(bf[bj][xb], af[bi][xa], acc[bi][bj]);
+          }
+    }
+    if constexpr (KIND != 0) {
+      if (--left == 0 || kt + 4 >= nk) {
+        left = fold;
+#pragma unroll
+        for (int bi = 0; bi < 2; ++bi)
+#pragma unroll
+          for (int bj = 0; bj < 2; ++bj) {
+            tot[bi][bj] += acc[bi][bj];
+            acc[bi][bj] = Acc{};
+          }
+      }
+    }
+  }
+  // every wave leaves its totals in its own ring
+  S *V = (S *)ring + l16 * (TE + 1);
+#pragma unroll
+  for (int bi = 0; bi < 2; ++bi)
+#pragma unroll
+    for (int bj = 0; bj < 2; ++bj)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        V[bi * 16 * (TE + 1) + bj * 16 + acc_row<KIND>(lg, r)] =
+            KIND == 0 ? acc[bi][bj][r] : tot[bi][bj][r];
+  __syncthreads();
+  const int o = (tid >> 3) * (TE + 1) + (tid & 7) * 4;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    v[e] = 0.0;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) v[e] += (double)((const S *)(smem + w * Z::RING))[o + e];
+  }
+  __syncthreads();
 }
 
 }  // namespace gcp
