@@ -143,12 +143,15 @@ typedef struct {
                               (bitwise the same iterates), storing k iterates at a time:
                               memory p/k + k matrices instead of p, for two extra
                               products per update in the backward. */
-    int32_t sync_every;    /* gcp_purify enqueues this many updates between host checks of
-                              the termination decision (default 4; 1 = check after every
-                              D^2).  Each update's decision is taken on the device before c_n
-                              is formed, and launches enqueued past the stop do nothing, so
-                              the iterates and the history do not depend on it.  A precision
-                              schedule checks after every update until it has switched. */
+    int32_t sync_every;    /* gcp_purify runs at most this many updates ahead of the last
+                              termination decision that the host has seen (default 4, of
+                              which it uses two; 1 = see each update's before the next is
+                              enqueued; gcp_purify_static reads the decision after every
+                              sync_every updates).  Each update's decision is taken on the
+                              device before c_n is formed, and launches enqueued past the
+                              stop do nothing, so the iterates and the history do not
+                              depend on it.  A precision schedule checks after every update
+                              until it has switched. */
     int32_t ksplit;        /* 16-bit encodings: split the K range of every tile pair over
                               ksplit blocks (2..64), whose FP32 totals the last of them
                               adds in FP64, in split order: the chunked accumulation is
@@ -186,7 +189,8 @@ typedef struct {
     double gemm_ms;      /* summed device time of the matrix-product launches (profile=1) */
     int32_t gemm_launches; /* number of matrix-product launches that did work: 2p, or
                               2p + 1 when the stop needed the square of D_p */
-    int32_t host_syncs;  /* host synchronisations of the iteration loop (gcp_purify) */
+    int32_t host_syncs;  /* times the loop of gcp_purify let the device run dry to read a
+                            decision (one at its end, and each check of a schedule) */
     double gemm_flops;   /* algorithmic flops of those launches (M^3 per product,
                             upper-triangle output; split products not counted) */
     double mfma_flops;   /* flops issued to the matrix cores, counted as whole 128x128

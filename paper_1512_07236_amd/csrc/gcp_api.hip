@@ -103,7 +103,11 @@ struct gcp_ctx {
   unsigned *counter = nullptr;
   unsigned *rcnt = nullptr;   // tiles done per row block (tile kernels)
   Scalars *sc = nullptr;    // device
-  Scalars *sc_host = nullptr;  // pinned
+  Scalars *sc_host = nullptr;  // host copy
+  Scalars *post = nullptr;     // sc_host when it is pinned: reductions post to it
+  double *hist_pin = nullptr;  // pinned staging of the history (behind sc_host)
+  uint32_t seq = 0;            // number of the last reduction enqueued
+  void *arena = nullptr;       // one allocation for the small buffers
   double *hist = nullptr;   // device, (max_iter + 1) x 9
   std::vector<double> hist_host;
   int hist_rows = 0;
@@ -120,7 +124,8 @@ struct gcp_ctx {
   // reverse mode: stored iterates D_0 .. D_{p-1} (adjoint type, Mp x Mp each),
   // or with checkpoint_every = k >= 2 the forward state at every k-th step
   // (operand planes + dg, rD, d2) and k recomputed iterates at a time
-  std::vector<void *> slots;
+  std::vector<void *> slots, slot_chunks;   // iterates; the allocations they lie in
+  std::vector<void *> large;                // separately allocated buffers
   struct Ckpt {
     void *planes = nullptr;
     double *vec = nullptr;   // dg, rD, d2 (3 Mp)
@@ -171,28 +176,7 @@ static size_t plane_bytes(const gcp_ctx *c) {
   return b;
 }
 
-static void free_all(gcp_ctx *c) {
-  void *ptrs[] = {c->Dp[0], c->Dp[1], c->X2p, c->dg[0], c->dg[1], c->rD[0], c->rD[1],
-                  c->d2[0], c->d2[1], c->s2, c->d3, c->part, c->tpart, c->bpart, c->hvec,
-                  c->counter, c->rcnt, c->sc, c->hist, c->D0p, c->dg0, c->rD0, c->d20};
-  for (void *p : ptrs)
-    if (p) (void)hipFree(p);
-  void *bptrs[] = {c->bG[0], c->bG[1], c->bS, c->bT, c->bws, c->bcnt, c->btpart, c->bvec, c->split_ws,
-                   c->split_cnt, c->vD, c->vH, c->vaux, c->Xc};
-  for (void *p : bptrs)
-    if (p) (void)hipFree(p);
-  for (void *p : c->slots)
-    if (p) (void)hipFree(p);
-  c->slots.clear();
-  for (auto &k : c->ckpts) {
-    if (k.planes) (void)hipFree(k.planes);
-    if (k.vec) (void)hipFree(k.vec);
-  }
-  c->ckpts.clear();
-  if (c->sc_host) (void)hipHostFree(c->sc_host);
-  for (hipEvent_t e : c->events) (void)hipEventDestroy(e);
-  c->events.clear();
-}
+static void free_slots(gcp_ctx *c);
 
 // Product kernel of an encoding at size M.
 //   32 x 32 tiles where 64 x 64 ones would leave most CUs idle: per product,
@@ -514,6 +498,26 @@ static void for_each_buffer(gcp_ctx *c, bool one_shot, F &&f) {
   }
 }
 
+static_assert(sizeof(Scalars) <= 256, "the pinned block holds the scalars first");
+constexpr size_t kArenaMax = (size_t)64 << 20;
+
+static void free_all(gcp_ctx *c) {
+  if (c->arena) (void)hipFree(c->arena);
+  for (void *p : c->large) (void)hipFree(p);
+  c->large.clear();
+  for (void *p : {(void *)c->vD, (void *)c->vH, (void *)c->vaux})
+    if (p) (void)hipFree(p);
+  free_slots(c);
+  for (auto &k : c->ckpts) {
+    if (k.planes) (void)hipFree(k.planes);
+    if (k.vec) (void)hipFree(k.vec);
+  }
+  c->ckpts.clear();
+  if (c->sc_host) (void)hipHostFree(c->sc_host);
+  for (hipEvent_t e : c->events) (void)hipEventDestroy(e);
+  c->events.clear();
+}
+
 extern "C" int gcp_create(gcp_ctx **out, int64_t M, const gcp_options *opt, void *stream) {
   if (!out) {
     g_create_error = "gcp_create: ctx pointer is NULL";
@@ -530,16 +534,42 @@ extern "C" int gcp_create(gcp_ctx **out, int64_t M, const gcp_options *opt, void
     return GCP_ERR_NO_MEMORY;
   }
   setup_ctx(c, M, o, stream);
+  // buffers up to kArenaMax come from one allocation (thirty of them cost 0.1
+  // to 0.2 ms to allocate and 0.1 to 1.6 ms to free), larger ones are separate
   bool ok = true;
+  size_t small = 0;
+  for_each_buffer(c, false, [&](void **, size_t bytes) {
+    if (bytes <= kArenaMax) small += (bytes + 255) / 256 * 256;
+  });
+  ok = hipMalloc(&c->arena, small) == hipSuccess;
+  if (!ok) c->arena = nullptr;
+  size_t off = 0;
   for_each_buffer(c, false, [&](void **p, size_t bytes) {
     if (!ok) return;
-    if (hipMalloc(p, bytes) != hipSuccess) {
-      ok = false;
-      *p = nullptr;
+    if (bytes <= kArenaMax) {
+      *p = (char *)c->arena + off;
+      off += (bytes + 255) / 256 * 256;
+      return;
     }
+    void *q = nullptr;
+    if (hipMalloc(&q, bytes) != hipSuccess) {
+      ok = false;
+      return;
+    }
+    *p = q;
+    c->large.push_back(q);
   });
-  if (ok && hipHostMalloc((void **)&c->sc_host, sizeof(Scalars), hipHostMallocDefault) != hipSuccess)
+  // the host copy of the scalars and, when short, of the history
+  const size_t hist_bytes = (size_t)(o.max_iter + 1) * GCP_HIST_COLS * sizeof(double);
+  const bool pin_hist = o.max_iter <= 1000;
+  if (ok && hipHostMalloc((void **)&c->sc_host, 256 + (pin_hist ? hist_bytes : 0),
+                          hipHostMallocDefault) != hipSuccess)
     ok = false;
+  if (ok) {
+    std::memset((void *)c->sc_host, 0, sizeof(Scalars));
+    c->post = c->sc_host;
+    if (pin_hist) c->hist_pin = (double *)((char *)c->sc_host + 256);
+  }
   if (!ok) {
     free_all(c);
     delete c;
@@ -603,12 +633,51 @@ static RedArgs reduction(const gcp_ctx *c, int nslots, int mode, double *out, co
   a.recheck = recheck ? 1 : 0;
   a.sc = c->sc;
   a.hist = c->hist;
+  a.post = c->post;
   return a;
+}
+
+// Numbers a reduction and says what it posts; returns its number.
+static uint32_t number(gcp_ctx *c, RedArgs &a, int what) {
+  a.seq = ++c->seq;
+  a.what = what;
+  return a.seq;
 }
 
 static int build_guess(gcp_ctx *c, const double *H, int64_t ldh, double theta, double beta,
                        double mu);
 static int first_traces(gcp_ctx *c);
+
+// Waits until reduction number seq has posted to c->post or, in the loop of a
+// solve, one before it has stopped it (later ones then do nothing).  Polling
+// pinned memory takes 6 us from launch to answer, a copy and a stream
+// synchronisation 14; without a pinned copy (gcp_purify_static) that is what
+// happens here.
+static int wait_scalars(gcp_ctx *c, uint32_t seq, bool in_loop = false) {
+  if (!c->post) {
+    HIPCHK(c, hipMemcpyAsync(c->sc_host, c->sc, sizeof(Scalars), hipMemcpyDeviceToHost, c->stream));
+    HIPCHK(c, hipStreamSynchronize(c->stream));
+    return GCP_OK;
+  }
+  auto reached = [&] {
+    const uint32_t at = __atomic_load_n(&c->post->seq, __ATOMIC_ACQUIRE);
+    return (int32_t)(at - seq) >= 0 ||
+           (in_loop && __atomic_load_n(&c->post->status, __ATOMIC_ACQUIRE) != 0);
+  };
+  for (uint32_t spin = 1; !reached(); ++spin) {
+    __builtin_ia32_pause();
+    if (spin % 8192 != 0) continue;
+    // every 0.2 ms or so: is the stream still at work?
+    const hipError_t e = hipStreamQuery(c->stream);
+    if (e == hipErrorNotReady) continue;
+    if (e != hipSuccess || !reached()) {
+      c->err.set("waiting for a reduction", e != hipSuccess ? hipGetErrorString(e)
+                                                            : "the stream is done without it");
+      return GCP_ERR_HIP;
+    }
+  }
+  return GCP_OK;
+}
 
 // Rounding floor of |Tr(D Dbar)| for encoding pc[k] (unless the caller gave
 // one).  One update leaves an off-diagonal error of relative size
@@ -689,9 +758,9 @@ extern "C" int gcp_init(gcp_ctx *c, const double *H, int64_t ldh, int64_t N, dou
   }
   const size_t vec = (size_t)c->Mp * sizeof(double);
   double *lo = c->hvec, *hi = c->hvec + c->Mp, *hd = c->hvec + 2 * c->Mp;
-  HIPCHK(c, launch_hstats(H, ldh, c->M, lo, hi, hd, c->sc->hstat, c->stream));
-  HIPCHK(c, hipMemcpyAsync(c->sc_host, c->sc, sizeof(Scalars), hipMemcpyDeviceToHost, c->stream));
-  HIPCHK(c, hipStreamSynchronize(c->stream));
+  HIPCHK(c, launch_hstats(H, ldh, c->M, lo, hi, hd, c->sc->hstat, c->post, ++c->seq, c->stream));
+  int rc = wait_scalars(c, c->seq);
+  if (rc != GCP_OK) return rc;
   const double g_lo = c->sc_host->hstat[0], g_hi = c->sc_host->hstat[1];
   const double trH = c->sc_host->hstat[2];
   if (!given) {
@@ -724,10 +793,10 @@ extern "C" int gcp_init(gcp_ctx *c, const double *H, int64_t ldh, int64_t N, dou
       if (std::isnan(target)) {
         alpha = 0.5;
       } else {
-        HIPCHK(c, launch_hdev(H, ldh, c->M, c->Mp, mu, c->part, &c->sc->hstat[3], c->stream));
-        HIPCHK(c, hipMemcpyAsync(c->sc_host, c->sc, sizeof(Scalars), hipMemcpyDeviceToHost,
-                                 c->stream));
-        HIPCHK(c, hipStreamSynchronize(c->stream));
+        HIPCHK(c, launch_hdev(H, ldh, c->M, c->Mp, mu, c->part, &c->sc->hstat[3], c->post,
+                              ++c->seq, c->stream));
+        rc = wait_scalars(c, c->seq);
+        if (rc != GCP_OK) return rc;
         const double S = c->sc_host->hstat[3];
         c->hdev = S;
         const double b2 = (target - (double)N * theta) / S;
@@ -793,10 +862,12 @@ static int build_guess(gcp_ctx *c, const double *H, int64_t ldh, double theta, d
   a.rD = c->rD0;
   a.part = c->part;
   HIPCHK(c, launch_init(c->opt.precision, a, c->stream));
-  HIPCHK(c, launch_reduce(reduction(c, (int)(c->Mp / 64), 0, c->d20, c->dg0, nullptr, 0, 0),
-                          c->stream));
-  HIPCHK(c, hipMemcpyAsync(c->sc_host, c->sc, sizeof(Scalars), hipMemcpyDeviceToHost, c->stream));
-  HIPCHK(c, hipStreamSynchronize(c->stream));
+  RedArgs red = reduction(c, (int)(c->Mp / 64), 0, c->d20, c->dg0, nullptr, 0, 0);
+  const uint32_t seq = number(c, red, POST_ALL);
+  HIPCHK(c, launch_reduce(red, c->stream));
+  // also the point up to which H is read
+  const int st = wait_scalars(c, seq);
+  if (st != GCP_OK) return st;
   c->t1_0 = c->sc_host->t1;
   c->t2_0 = c->sc_host->t2;
   return GCP_OK;
@@ -843,11 +914,10 @@ static int first_traces(gcp_ctx *c) {
   g.rD = c->rD0;
   g.d2 = c->d20;
   g.red = reduction(c, (int)(c->Mp / 128), 1, c->d3, nullptr, c->tpart, c->pc[0].ntpart, 0);
-  int st = run_product(c, g, 0, nullptr);
+  const uint32_t seq = number(c, g.red, POST_ALL);
+  const int st = run_product(c, g, 0, nullptr);
   if (st != GCP_OK) return st;
-  HIPCHK(c, hipMemcpyAsync(c->sc_host, c->sc, sizeof(Scalars), hipMemcpyDeviceToHost, c->stream));
-  HIPCHK(c, hipStreamSynchronize(c->stream));
-  return GCP_OK;
+  return wait_scalars(c, seq);
 }
 
 extern "C" int gcp_get_init_scalars(const gcp_ctx *c, double *mu, double *beta, double *emin,
@@ -862,16 +932,31 @@ extern "C" int gcp_get_init_scalars(const gcp_ctx *c, double *mu, double *beta, 
   return GCP_OK;
 }
 
+static void free_slots(gcp_ctx *c) {
+  for (void *p : c->slot_chunks) (void)hipFree(p);
+  c->slot_chunks.clear();
+  c->slots.clear();
+}
+
 // Keeps iterate D_n (forward planes Dp[k] plus its FP64 diagonal) as slot n.
 static int store_iterate(gcp_ctx *c, int n, int k, int prec) {
   const size_t bytes = (size_t)c->Mp * (size_t)c->Mp * (size_t)elem_size(c->opt.bwd_precision);
   while ((int)c->slots.size() <= n) {
+    // several at a time up to 256 MB (one at a time when that does not fit)
+    size_t k = std::max<size_t>(1, std::min<size_t>(8, ((size_t)256 << 20) / bytes));
     void *p = nullptr;
-    if (hipMalloc(&p, bytes) != hipSuccess) {
+    hipError_t e = hipMalloc(&p, k * bytes);
+    if (e != hipSuccess && k > 1) {
+      (void)hipGetLastError();
+      k = 1;
+      e = hipMalloc(&p, bytes);
+    }
+    if (e != hipSuccess) {
       c->err = "gcp_purify: out of device memory for the iterates kept for gcp_backward";
       return GCP_ERR_NO_MEMORY;
     }
-    c->slots.push_back(p);
+    c->slot_chunks.push_back(p);
+    for (size_t q = 0; q < k; ++q) c->slots.push_back((char *)p + q * bytes);
   }
   HIPCHK(c, launch_bwd_store(prec, c->opt.bwd_precision, c->Dp[k], c->dg[k], c->Mp,
                              c->slots[n], c->stream));
@@ -881,7 +966,7 @@ static int store_iterate(gcp_ctx *c, int n, int k, int prec) {
 // K1 of update n on the iterate in buffer k: X2 = D D and the scalar step.
 // recheck: the same iterate once more, in a new encoding (after a switch).
 static int step_k1(gcp_ctx *c, GemmArgs &g, int pi, int k, int n, LaunchLog *log,
-                   bool recheck = false) {
+                   bool recheck = false, int what = POST_NONE) {
   g.mode = 0;
   g.A = c->Dp[k];
   g.B = c->Dp[k];
@@ -891,11 +976,14 @@ static int step_k1(gcp_ctx *c, GemmArgs &g, int pi, int k, int n, LaunchLog *log
   g.d2 = c->d2[k];
   g.red = reduction(c, (int)(c->Mp / 128), 1, c->d3, nullptr, c->tpart, c->pc[pi].ntpart, n,
                     g.status != nullptr, c->pc[pi].floor_ddbar, false, recheck);
+  if (g.status == nullptr) g.red.post = nullptr;   // recomputed for the adjoint
+  number(c, g.red, what);
   return run_product(c, g, pi, log);
 }
 
 // K2 of update n: D_{n+1} into buffer 1 - k.
-static int step_k2(gcp_ctx *c, GemmArgs &g, int pi, int k, int n, LaunchLog *log) {
+static int step_k2(gcp_ctx *c, GemmArgs &g, int pi, int k, int n, LaunchLog *log,
+                   int what = POST_NONE) {
   g.mode = 1;
   g.A = c->X2p;
   g.B = c->Dp[k];
@@ -909,6 +997,8 @@ static int step_k2(gcp_ctx *c, GemmArgs &g, int pi, int k, int n, LaunchLog *log
   g.red = reduction(c, (int)(c->Mp / 128), 2, c->d2[1 - k], c->dg[1 - k], c->tpart,
                     c->pc[pi].ntpart, n, solve, c->pc[pi].floor_ddbar,
                     solve && !(c->opt.tol_idem > 0.0));
+  if (!solve) g.red.post = nullptr;
+  number(c, g.red, what);
   return run_product(c, g, pi, log);
 }
 
@@ -1010,14 +1100,25 @@ extern "C" int gcp_purify(gcp_ctx *c, void *D, int32_t dtype, int64_t ldd, gcp_r
   const int64_t PS = c->Mp * c->Mp;
   const int max_iter = c->opt.max_iter;
 
-  // start from D_0
+  // start from D_0: update 0 reads it where gcp_init left it, unless D_0 has to
+  // stay apart from what the loop reads (a change of encoding replaces the
+  // buffer, checkpoints and kept iterates are taken from it); a one-shot solve
+  // has built it in the first buffer
   c->cur = 0;
-  if (c->D0p != c->Dp[0]) {   // (a one-shot solve builds D_0 in place)
+  const bool in_place = c->D0p == c->Dp[0];
+  const bool direct = !in_place && c->nprec == 1 && !c->opt.keep_iterates;
+  if (!in_place && !direct) {
     HIPCHK(c, hipMemcpyAsync(c->Dp[0], c->D0p, plane_bytes(c), hipMemcpyDeviceToDevice, c->stream));
     HIPCHK(c, hipMemcpyAsync(c->dg[0], c->dg0, vec, hipMemcpyDeviceToDevice, c->stream));
     HIPCHK(c, hipMemcpyAsync(c->rD[0], c->rD0, vec, hipMemcpyDeviceToDevice, c->stream));
     HIPCHK(c, hipMemcpyAsync(c->d2[0], c->d20, vec, hipMemcpyDeviceToDevice, c->stream));
   }
+  auto swap_d0 = [&] {   // the first buffer and D_0 change places
+    std::swap(c->Dp[0], c->D0p);
+    std::swap(c->dg[0], c->dg0);
+    std::swap(c->rD[0], c->rD0);
+    std::swap(c->d2[0], c->d20);
+  };
   Scalars s0{};
   s0.t1 = c->t1_0;
   s0.t2 = c->t2_0;
@@ -1048,81 +1149,81 @@ extern "C" int gcp_purify(gcp_ctx *c, void *D, int32_t dtype, int64_t ldd, gcp_r
   for (int q = 0; q < 3; ++q) c->n_switch[q] = -1;
 
   // Update n reads D_n from buffer n % 2 and writes D_{n+1} to the other.
-  // The decision to stop is taken on the device (k_reduce, before c_n is
-  // formed); the host enqueues sync_every updates at a time and reads the
-  // decision after each batch.  Until a precision schedule has switched, the
-  // host checks after every D^2, because the switch is decided there.
-  int status = 0, n = 0, syncs = 0;
-  for (;;) {
+  // The decision to stop is taken on the device (scalar_step, before c_n is
+  // formed) and posted to the host, which stays at most `ahead` updates ahead
+  // of the device, so that the GPU never waits for it and few launches follow
+  // the stop (they do nothing).  Without posts (gcp_purify_static) the host
+  // reads the decision after every sync_every updates.  Until a precision
+  // schedule has switched, the host checks after every D^2, because the switch
+  // is decided there.
+  const int ahead = std::min(c->opt.sync_every, 2);
+  int n = 0, syncs = 0, unchecked = 0, st = GCP_OK;
+  uint32_t done[4] = {};   // reduction of update n's K2, at n % 4
+  auto check = [&](uint32_t seq) {   // true: the solve has stopped (or st != OK)
+    st = wait_scalars(c, seq, true);
+    return st != GCP_OK || c->sc_host->status != 0;
+  };
+  auto fail = [&] {   // nothing in flight may post to a later solve
+    (void)hipStreamSynchronize(c->stream);
+    return st;
+  };
+  for (bool stopped = false; !stopped && n <= max_iter; ++n) {
+    const int k = n & 1;
     const bool per_step = pi + 1 < c->nprec;
-    const int nb = per_step ? 1 : c->opt.sync_every;
-    bool stopped = false;
-    for (int q = 0; q < nb && n <= max_iter; ++q, ++n) {
-      const int k = n & 1;
-      if (ck && n % ck == 0) {
-        int st = save_checkpoint(c, n / ck, k, pi);
-        if (st != GCP_OK) return st;
-      }
-      int st = step_k1(c, g, pi, k, n, &lg);
-      if (st != GCP_OK) return st;
-      if (per_step) {
-        HIPCHK(c, hipMemcpyAsync(c->sc_host, c->sc, sizeof(Scalars), hipMemcpyDeviceToHost,
-                                 c->stream));
-        HIPCHK(c, hipStreamSynchronize(c->stream));
-        ++syncs;
-        if (c->sc_host->status != 0) {
-          stopped = true;
-          break;
-        }
-        int to = pi;
-        while (to + 1 < c->nprec &&
-               std::fabs(c->sc_host->t1 - c->sc_host->t2) <= c->pc[to + 1].enter_ddbar) {
-          ++to;
-          c->n_switch[to] = n;
-        }
-        if (to != pi) {
-          st = switch_precision(c, k, pi, to);
-          if (st != GCP_OK) return st;
-          pi = to;
-          prec = c->pc[pi].prec;
-          st = step_k1(c, g, pi, k, n, &lg, true);
-          if (st != GCP_OK) return st;
-          ++lg.reruns;
-          HIPCHK(c, hipMemcpyAsync(c->sc_host, c->sc, sizeof(Scalars), hipMemcpyDeviceToHost,
-                                   c->stream));
-          HIPCHK(c, hipStreamSynchronize(c->stream));
-          ++syncs;
-          if (c->sc_host->status != 0) {
-            stopped = true;
-            break;
-          }
-        }
-      }
-      // the iterate K2 reads, in the encoding it reads it (after a switch)
-      if (keep && !ck) {
-        st = store_iterate(c, n, k, prec);
-        if (st != GCP_OK) return st;
-      }
-      st = step_k2(c, g, pi, k, n, &lg);
-      if (st != GCP_OK) return st;
+    if (c->post ? n >= ahead : unchecked >= c->opt.sync_every) {
+      stopped = check(c->post ? done[(n - ahead) & 3] : c->seq);
+      if (!c->post) ++syncs;
+      unchecked = 0;
+      if (stopped) break;
     }
-    if (!stopped) {
-      HIPCHK(c, hipMemcpyAsync(c->sc_host, c->sc, sizeof(Scalars), hipMemcpyDeviceToHost,
-                               c->stream));
-      HIPCHK(c, hipStreamSynchronize(c->stream));
+    if (ck && n % ck == 0) {
+      st = save_checkpoint(c, n / ck, k, pi);
+      if (st != GCP_OK) return fail();
+    }
+    if (direct && n == 0) swap_d0();
+    st = step_k1(c, g, pi, k, n, &lg, false, per_step ? POST_ALL : POST_NONE);
+    if (st == GCP_OK && per_step) {
       ++syncs;
+      if (check(c->seq)) break;
+      int to = pi;
+      while (to + 1 < c->nprec &&
+             std::fabs(c->sc_host->t1 - c->sc_host->t2) <= c->pc[to + 1].enter_ddbar) {
+        ++to;
+        c->n_switch[to] = n;
+      }
+      if (to != pi) {
+        st = switch_precision(c, k, pi, to);
+        if (st != GCP_OK) return fail();
+        pi = to;
+        prec = c->pc[pi].prec;
+        st = step_k1(c, g, pi, k, n, &lg, true, POST_ALL);
+        if (st != GCP_OK) return fail();
+        ++lg.reruns;
+        ++syncs;
+        if (check(c->seq)) break;
+      }
     }
-    if (c->sc_host->status != 0) break;
+    // the iterate K2 reads, in the encoding it reads it (after a switch)
+    if (st == GCP_OK && keep && !ck) st = store_iterate(c, n, k, prec);
+    if (st == GCP_OK) st = step_k2(c, g, pi, k, n, &lg, POST_SEQ);
+    if (direct && n == 0) swap_d0();
+    if (st != GCP_OK) return fail();
+    done[n & 3] = c->seq;
+    ++unchecked;
   }
-  status = c->sc_host->status;
+  if (st == GCP_OK && c->sc_host->status == 0) (void)check(c->seq);
+  if (st != GCP_OK) return fail();
+  ++syncs;
+  const int status = c->sc_host->status;
   n = c->sc_host->iter;
+  const bool at_d0 = direct && n == 0;   // no update applied
   c->cur = n & 1;
   const int iters = n;
   if (keep) c->bwd_p = iters;
   // output D_p
   OutArgs oa{};
-  oa.planes = c->Dp[c->cur];
-  oa.dg = c->dg[c->cur];
+  oa.planes = at_d0 ? c->D0p : c->Dp[c->cur];
+  oa.dg = at_d0 ? c->dg0 : c->dg[c->cur];
   oa.M = c->M;
   oa.Mp = c->Mp;
   oa.pstride = PS;
@@ -1135,13 +1236,16 @@ extern "C" int gcp_purify(gcp_ctx *c, void *D, int32_t dtype, int64_t ldd, gcp_r
   double c_last = NAN;
   if (!c->one_shot) {
     c->hist_host.assign((size_t)c->hist_rows * GCP_HIST_COLS, NAN);
-    HIPCHK(c, hipMemcpyAsync(c->hist_host.data(), c->hist, c->hist_host.size() * sizeof(double),
-                             hipMemcpyDeviceToHost, c->stream));
+    HIPCHK(c, hipMemcpyAsync(c->hist_pin ? c->hist_pin : c->hist_host.data(), c->hist,
+                             c->hist_host.size() * sizeof(double), hipMemcpyDeviceToHost,
+                             c->stream));
   } else if (iters > 0) {   // only c of the last update
     HIPCHK(c, hipMemcpyAsync(&c_last, c->hist + (size_t)(iters - 1) * GCP_HIST_COLS + 4,
                              sizeof(double), hipMemcpyDeviceToHost, c->stream));
   }
   HIPCHK(c, hipStreamSynchronize(c->stream));
+  if (!c->one_shot && c->hist_pin)
+    std::memcpy(c->hist_host.data(), c->hist_pin, c->hist_host.size() * sizeof(double));
   if (!c->one_shot && iters > 0) c_last = c->hist_host[(size_t)(iters - 1) * GCP_HIST_COLS + 4];
   const auto t_end = std::chrono::steady_clock::now();
 

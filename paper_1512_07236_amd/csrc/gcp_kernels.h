@@ -72,8 +72,12 @@ struct Scalars {
   double prev_ddbar;   // |Tr(D Dbar)| of the previous iterate (+inf before the first)
   int32_t on_traces;   // 1: the stop was decided from the update's traces, before
                        // the square of the last iterate was formed
-  int32_t pad;
+  uint32_t seq;        // host copy only: the last reduction posted to it
 };
+
+// What a reduction tells the host: nothing, that it has run (seq), or also the
+// scalars.  A reduction that stops the solve always posts everything.
+enum { POST_NONE = 0, POST_SEQ = 1, POST_ALL = 2 };
 
 struct RedArgs {
   const double *part;
@@ -96,6 +100,9 @@ struct RedArgs {
                        // no stall test against, and no update of, prev_ddbar
   Scalars *sc;
   double *hist;
+  Scalars *post;       // pinned host memory (NULL: the host copies sc instead)
+  uint32_t seq;        // number of this reduction, for post->seq
+  int what;            // POST_*
 };
 
 // Product kernels: one 32 x 32 or 64 x 64 tile per block, with the reduction
@@ -228,11 +235,12 @@ hipError_t launch_reduce(const RedArgs &a, hipStream_t st);
 hipError_t launch_stream_lds(const void *buf, int64_t bytes, hipStream_t st);
 // n 32-bit words of p set to zero by a kernel (no memset node in a captured graph)
 hipError_t launch_zero(void *p, int64_t nwords, hipStream_t st);
+// Gershgorin bounds and trace into out[0..2], posted as hstat[0..2].
 hipError_t launch_hstats(const double *H, int64_t ldh, int64_t M, double *lo, double *hi,
-                         double *hd, double *out, hipStream_t st);
+                         double *hd, double *out, Scalars *post, uint32_t seq, hipStream_t st);
 // out[0] = || (H + H^T)/2 - mu I ||_F^2 over M x M (fixed order); scratch holds
 // one partial per pair of mirrored 64 x 64 tiles.
 hipError_t launch_hdev(const double *H, int64_t ldh, int64_t M, int64_t Mp, double mu,
-                       double *scratch, double *out, hipStream_t st);
+                       double *scratch, double *out, Scalars *post, uint32_t seq, hipStream_t st);
 
 }  // namespace gcp

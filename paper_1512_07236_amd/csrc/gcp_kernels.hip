@@ -33,9 +33,9 @@ __device__ __forceinline__ void st_agent(double *p, double v) {
   __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// The scalar step at this point of the iteration (one thread).
-__device__ void scalar_step(const RedArgs &a, double sum_out, double sum_extra,
-                            double sum_tiles) {
+// The scalar step at this point of the iteration (one thread); returns the
+// solve's status.
+__device__ int take_step(const RedArgs &a, double sum_out, double sum_extra, double sum_tiles) {
   Scalars *sc = a.sc;
   if (a.mode == 0) {            // after the initial guess
     sc->t2 = sum_out;
@@ -78,12 +78,13 @@ __device__ void scalar_step(const RedArgs &a, double sum_out, double sum_extra,
       h[3] = h[4] = h[6] = h[7] = NAN;
     }
     h[8] = NAN;
+    return status;
   } else {                      // after the update: traces of D_{n+1}
     sc->t2 = sum_out;
     sc->t1 = sum_extra;
     sc->step = sum_tiles;
     a.hist[(int64_t)a.iter * 9 + 8] = sqrt(sum_tiles);
-    if (!a.early_stop) return;
+    if (!a.early_stop) return 0;
     // The stops of the mode-1 decision that need only T1 and T2 of D_{n+1},
     // taken here so that the square of the last iterate is never formed:
     // |Tr(D Dbar)| within tol_ddbar, or within the rounding floor while not
@@ -100,7 +101,7 @@ __device__ void scalar_step(const RedArgs &a, double sum_out, double sum_extra,
                fabs(ddbar) <= a.floor_ddbar)
         status = 4;
     }
-    if (status == 0) return;
+    if (status == 0) return 0;
     sc->status = status;
     sc->iter = nx;
     sc->on_traces = 1;
@@ -108,7 +109,37 @@ __device__ void scalar_step(const RedArgs &a, double sum_out, double sum_extra,
     double *h = a.hist + (int64_t)nx * 9;
     h[0] = nx; h[1] = t1; h[2] = t2;
     h[3] = h[4] = h[5] = h[6] = h[7] = h[8] = NAN;
+    return status;
   }
+  return 0;
+}
+
+// Stores to pinned host memory, which the host polls: the values are out
+// before the word that announces them.
+template <class T>
+__device__ __forceinline__ void st_host(T *p, T v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+__device__ __forceinline__ void host_order() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
+__device__ void scalar_step(const RedArgs &a, double sum_out, double sum_extra,
+                            double sum_tiles) {
+  const int status = take_step(a, sum_out, sum_extra, sum_tiles);
+  if (!a.post || (status == 0 && a.what == POST_NONE)) return;
+  Scalars *p = a.post;
+  if (status != 0 || a.what == POST_ALL) {
+    const Scalars *sc = a.sc;
+    st_host(&p->t1, sc->t1);
+    st_host(&p->t2, sc->t2);
+    st_host(&p->t3, sc->t3);
+    st_host(&p->omega, sc->omega);
+    st_host(&p->iter, sc->iter);
+    st_host(&p->on_traces, sc->on_traces);
+    host_order();
+    st_host(&p->status, status);
+    host_order();
+  }
+  st_host(&p->seq, a.seq);
 }
 
 // ------------------------------------------------- epilogue of one tile
@@ -1097,7 +1128,8 @@ __global__ __launch_bounds__(256) void k_hstats(const double *__restrict__ H, in
 
 // Single block: min of lo, max of hi and the (fixed-order) sum of hd.
 __global__ __launch_bounds__(256) void k_hfinal(const double *lo, const double *hi,
-                                                const double *hd, int64_t M, double *out) {
+                                                const double *hd, int64_t M, double *out,
+                                                Scalars *post, uint32_t seq) {
   __shared__ double smin[256], smax[256], ssum[256];
   double mn = INFINITY, mx = -INFINITY, sm = 0.0;
   for (int64_t i = threadIdx.x; i < M; i += 256) {
@@ -1121,6 +1153,13 @@ __global__ __launch_bounds__(256) void k_hfinal(const double *lo, const double *
     out[0] = smin[0];
     out[1] = smax[0];
     out[2] = ssum[0];
+    if (post) {
+      st_host(&post->hstat[0], smin[0]);
+      st_host(&post->hstat[1], smax[0]);
+      st_host(&post->hstat[2], ssum[0]);
+      host_order();
+      st_host(&post->seq, seq);
+    }
   }
 }
 
@@ -1150,7 +1189,8 @@ __global__ __launch_bounds__(256) void k_hdev(const double *__restrict__ H, int6
   if (threadIdx.x == 0) part[blockIdx.x] = ((red[0] + red[1]) + red[2]) + red[3];
 }
 
-__global__ __launch_bounds__(256) void k_hdev_sum(const double *part, int n, double *out) {
+__global__ __launch_bounds__(256) void k_hdev_sum(const double *part, int n, double *out,
+                                                  Scalars *post, uint32_t seq) {
   __shared__ double red[256];
   double s = 0.0;
   for (int t = threadIdx.x; t < n; t += 256) s += part[t];
@@ -1160,7 +1200,14 @@ __global__ __launch_bounds__(256) void k_hdev_sum(const double *part, int n, dou
     if (threadIdx.x < w) red[threadIdx.x] += red[threadIdx.x + w];
     __syncthreads();
   }
-  if (threadIdx.x == 0) *out = red[0];
+  if (threadIdx.x == 0) {
+    *out = red[0];
+    if (post) {
+      st_host(&post->hstat[3], red[0]);
+      host_order();
+      st_host(&post->seq, seq);
+    }
+  }
 }
 
 // ------------------------------------------------------------ initial guess
@@ -1448,17 +1495,18 @@ hipError_t launch_output(int prec, const OutArgs &a, hipStream_t st) {
 }
 
 hipError_t launch_hstats(const double *H, int64_t ldh, int64_t M, double *lo, double *hi,
-                         double *hd, double *out, hipStream_t st) {
+                         double *hd, double *out, Scalars *post, uint32_t seq, hipStream_t st) {
   k_hstats<<<(unsigned)M, 256, 0, st>>>(H, ldh, M, lo, hi, hd);
-  k_hfinal<<<1, 256, 0, st>>>(lo, hi, hd, M, out);
+  k_hfinal<<<1, 256, 0, st>>>(lo, hi, hd, M, out, post, seq);
   return hipGetLastError();
 }
 
 hipError_t launch_hdev(const double *H, int64_t ldh, int64_t M, int64_t Mp, double mu,
-                       double *scratch, double *out, hipStream_t st) {
+                       double *scratch, double *out, Scalars *post, uint32_t seq,
+                       hipStream_t st) {
   const int64_t nt = Mp / 64, np = nt * (nt + 1) / 2;
   k_hdev<<<(unsigned)np, 256, 0, st>>>(H, ldh, M, mu, scratch);
-  k_hdev_sum<<<1, 256, 0, st>>>(scratch, (int)np, out);
+  k_hdev_sum<<<1, 256, 0, st>>>(scratch, (int)np, out, post, seq);
   return hipGetLastError();
 }
 
