@@ -173,7 +173,7 @@ def summarize_pmc(precision: str, scale: int, fetch_dir: str, write_dir: str) ->
     import paper_1512_07236_amd as gcp
     prec = gcp.Precision.parse(precision)
     M = 8192 // scale
-    kname = "k_gemm16" if gcp.MFMA_DTYPE[prec] in ("fp16", "bf16") else "k_gemm"
+    kname = "k_gemm16" if gcp.MFMA_DTYPE[prec] in ("fp16", "bf16") else "k_tile"
     tag = f"gemm_{prec.name.lower()}_M{M}"
     out = {"kernel": f"{kname}<{int(prec)}>", "workload": f"M={M}", "precision": prec.name.lower()}
     for name, d in (("FETCH_SIZE", fetch_dir), ("WRITE_SIZE", write_dir)):
@@ -543,7 +543,7 @@ def main() -> int:
         "other_workloads": extra,
         "roofline": {"bound": "mfma", "achieved": achieved, "peak": peak, "unit": "TFLOP/s",
                      "frac": achieved / peak, "traffic": traffic,
-                     "kernel": (("k_gemm16" if gcp.MFMA_DTYPE[prec] in ("fp16", "bf16") else "k_gemm")
+                     "kernel": (("k_gemm16" if gcp.MFMA_DTYPE[prec] in ("fp16", "bf16") else "k_tile")
                                 + f"<{prec.name}>"),
                      "algorithmic_flops_per_launch": flops_product,
                      "launches_per_solve": launches,
