@@ -249,11 +249,18 @@ static void init_prec_cfg(gcp_ctx *c, int k) {
     const size_t unit = 64 * 64 * (size_t)(prec == GCP_FP64 ? 8 : 4);
     const size_t cap = c->M <= GCP_STATIC_MAX_M ? (size_t)13 << 20 : SIZE_MAX;
     const double t_stage = np == 3 ? 0.8 : 0.5, t_part = prec == GCP_FP64 ? 1.2 : 0.6;
+    // A tail of just over half a round, which two splits no longer fit, in three
+    // splits over two short rounds: FP64 M = 1790 128 -> 120, 2300 219 -> 205,
+    // 3392 614 -> 586 us; FP32 78 -> 73, 136 -> 126, 354 -> 341.  16-bit tiles
+    // gain nothing (FP16X3 M = 2300 63 / 65, BF16X6 M = 1790 63 / 69), nor do
+    // two rounds that are full (FP64 M = 3968, 161 tiles: 940 / 954).
+    const bool two_thirds = elem_size(prec) != 2 && 2 * tail > cus && 8 * tail <= 5 * cus;
     q.ntpart = ntiles;
     q.nfull = ntiles;
     double best = t_stage * nk;
     for (int S = 2; tail > 0 && S <= 16; ++S) {
-      if (nk / S < 4 || (size_t)tail * S * unit > cap || (ntiles > cus && tail * S > cus)) break;
+      if (nk / S < 4 || (size_t)tail * S * unit > cap) break;
+      if (ntiles > cus && tail * S > cus && !(S == 3 && two_thirds)) continue;
       const double t = t_stage * nk * ((tail * S + cus - 1) / cus) / S + 2.0 + t_part * S;
       if (t < best) {
         best = t;
@@ -313,10 +320,15 @@ static void init_bwd_cfg(gcp_ctx *c) {
   const int nt = (int)(c->Mp / 64), ntiles = nt * (nt + 1) / 2, tail = ntiles % cus;
   const int nk = (int)(c->Mp * elem_size(c->opt.bwd_precision) / 128);
   const double t_part = c->opt.bwd_precision == GCP_FP64 ? 1.2 : 0.6;
+  // tails of just over half a round as in init_prec_cfg, three splits to each
+  // product: FP32 M = 2300 four updates 2.22 -> 1.89 ms, M = 3392 5.58 -> 5.40;
+  // FP64 M = 1790 2.18 -> 2.11, M = 3392 10.7 -> 10.1
+  const bool two_thirds = 2 * tail > cus && 8 * tail <= 5 * cus;
   c->b_nfull = ntiles;
   double best = 0.5 * 2 * nk;
   for (int S = 2; tail > 0 && S <= 16; S += 2) {
-    if (2 * nk / S < 4 || (ntiles > cus && tail * S > cus)) break;
+    if (2 * nk / S < 4) break;
+    if (ntiles > cus && tail * S > cus && !(S == 6 && two_thirds)) continue;
     const double t = 0.5 * 2 * nk * ((tail * S + cus - 1) / cus) / S + 2.0 + t_part * S;
     if (t < best) {
       best = t;

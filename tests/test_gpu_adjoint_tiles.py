@@ -1,7 +1,7 @@
 """The adjoint's tile launches at the sizes where their shape changes, against
 the oracle's adjoint at the GPU's p: one tile and two tile rows (both products
-of every tile split), seven tile rows (28 split tiles), and 300 tiles of which
-44 are split; PMCP, whose kappa needs the D^2 tiles, at seven tile rows."""
+of every tile split), seven tile rows (28 split tiles), 300 tiles of which 44
+are split and 406 of which 150 are, six times each; PMCP, whose kappa needs the D^2 tiles, at seven tile rows."""
 import pytest
 
 from oracle import grad
@@ -15,7 +15,7 @@ if not torch.cuda.is_available():
 
 from test_gpu_adjoint import _oracle, fp64_tol, gpu_grad, log, rel_max  # noqa: E402,F401
 
-SIZES = [(40, 15), (65, 30), (449, 180), (1473, 560)]
+SIZES = [(40, 15), (65, 30), (449, 180), (1473, 560), (1750, 700)]
 
 
 @pytest.mark.parametrize("M,N,method", [(M, N, "hpcp") for M, N in SIZES] + [(449, 180, "pmcp")])

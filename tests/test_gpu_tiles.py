@@ -2,7 +2,8 @@
 at a time against the oracle within the derived bounds: 32 x 32 tiles (every
 encoding) with one row of them half empty, with fewer K stages than waves, and
 with an odd row of padding; around the sizes at which 64 x 64 tiles take over,
-where every tile is split along K; 300 of those, of which 44 are split; and
+where every tile is split along K; 300 of those, of which 44 are split; 406,
+of which 150 are split over three blocks each; and
 the two sides of the size at which the 16-bit encodings change to tile
 pairs."""
 import pytest
@@ -21,6 +22,7 @@ CASES = [(M, N, p) for M, N in ((20, 8), (64, 24), (65, 30), (385, 150)) for p i
 CASES += [(M, 350, p) for M in (896, 897) for p in ("fp32", "bf16", "fp16x3", "bf16x6")]
 CASES += [(M, 500, "fp64") for M in (1280, 1281)]
 CASES += [(1473, 560, p) for p in ("fp64", "fp32", "fp16x3", "bf16x6")]
+CASES += [(1750, 700, p) for p in ("fp64", "fp32")]
 CASES += [(M, 1200, p) for M in (3008, 3009) for p in ("fp16x3", "bf16x6")]
 
 
