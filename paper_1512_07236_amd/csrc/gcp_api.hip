@@ -1364,6 +1364,7 @@ extern "C" int gcp_backward(gcp_ctx *c, const void *dLdD, int64_t ldg, void *dLd
   int cur = 0;
   double *kappa = c->bvec + 2 * c->Mp;
   BwdArgs a{};
+  a.M = c->M;
   a.Mp = c->Mp;
   a.nt = nt;
   a.fold = fp32_fold(c->Mp);

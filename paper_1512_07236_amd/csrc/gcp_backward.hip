@@ -266,10 +266,13 @@ __global__ __launch_bounds__(NTH, BwdCfg<P>::BLOCKS) void k_bstep(BwdArgs a) {
     const int row = q * 16 + me.r0;
     const int64_t o = (i0 + row) * Mp + j0 + me.c4;
     const v4t dv = *(const v4t *)(D + o), gv = *(const v4t *)(G + o), sv = *(const v4t *)(Sm + o);
+    // the I of c (I - 2D) is that of the M x M problem: the padding of Gbar
+    // stays zero, as Tr Gbar_0 and <Gbar_0, D_0> take it to be
+    const bool drow = dtile && i0 + row < a.M;
 #pragma unroll
     for (int e = 0; e < 4; ++e)
       p[q][e] = (S)(a.a * (double)gv[e] + a.b * (double)sv[e] + a.e * v[q][e] + kd * (double)dv[e] +
-                    (dtile && row == me.c4 + e ? ki : 0.0));
+                    (drow && row == me.c4 + e ? ki : 0.0));
   }
   T *O = (T *)a.out;
   if (!dtile) me.store(O, i0, j0, Mp, p);

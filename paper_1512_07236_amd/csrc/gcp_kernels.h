@@ -170,7 +170,7 @@ struct BwdArgs {
   const void *G;       // Gbar_{n+1} = dL/dD_{n+1}
   void *S, *T;         // D G + G D, and G D (BWD_PAIR writes, BWD_STEP reads)
   void *out;           // Gbar_n (BWD_STEP)
-  int64_t Mp;
+  int64_t M, Mp;
   int nt;              // Mp / 64
   int fold;            // fold period of the FP32 products, in K stages
   // Blocks [0, nfull) compute whole tiles; each remaining tile is split over
