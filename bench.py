@@ -54,7 +54,7 @@ def product_kernel_hash() -> str:
     a = k.index("// ------------------------------------------------ 16-bit product kernel")
     b = k.index("int pair_count(int nt)")
     h = hashlib.sha256(k[a:b].encode())
-    for f in ("gcp_encode.h", "gcp_mma.h", "gcp_kernels.h"):
+    for f in ("gcp_encode.h", "gcp_mma.h", "gcp_kernels.h", "gcp_posts.h"):
         h.update(open(os.path.join(csrc, f), "rb").read())
     return h.hexdigest()
 

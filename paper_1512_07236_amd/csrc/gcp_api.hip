@@ -106,7 +106,7 @@ struct gcp_ctx {
   Scalars *sc_host = nullptr;  // host copy
   Scalars *post = nullptr;     // sc_host when it is pinned: reductions post to it
   double *hist_pin = nullptr;  // pinned staging of the history (behind sc_host)
-  uint32_t seq = 0;            // number of the last reduction enqueued
+  uint32_t seq = kFirstSeq;    // number of the last reduction enqueued
   void *arena = nullptr;       // one allocation for the small buffers
   double *hist = nullptr;   // device, (max_iter + 1) x 9
   std::vector<double> hist_host;
@@ -583,6 +583,7 @@ extern "C" int gcp_create(gcp_ctx **out, int64_t M, const gcp_options *opt, void
     ok = false;
   if (ok) {
     std::memset((void *)c->sc_host, 0, sizeof(Scalars));
+    c->sc_host->seq = c->seq;
     c->post = c->sc_host;
     if (pin_hist) c->hist_pin = (double *)((char *)c->sc_host + 256);
   }
@@ -676,8 +677,7 @@ static int wait_scalars(gcp_ctx *c, uint32_t seq, bool in_loop = false) {
     return GCP_OK;
   }
   auto reached = [&] {
-    const uint32_t at = __atomic_load_n(&c->post->seq, __ATOMIC_ACQUIRE);
-    return (int32_t)(at - seq) >= 0 ||
+    return posted(__atomic_load_n(&c->post->seq, __ATOMIC_ACQUIRE), seq) ||
            (in_loop && __atomic_load_n(&c->post->status, __ATOMIC_ACQUIRE) != 0);
   };
   for (uint32_t spin = 1; !reached(); ++spin) {
@@ -1064,11 +1064,9 @@ static int recompute_segment(gcp_ctx *c, int n0, int n1) {
   HIPCHK(c, hipMemcpyAsync(c->dg[0], q.vec, vec, hipMemcpyDeviceToDevice, c->stream));
   HIPCHK(c, hipMemcpyAsync(c->rD[0], q.vec + c->Mp, vec, hipMemcpyDeviceToDevice, c->stream));
   HIPCHK(c, hipMemcpyAsync(c->d2[0], q.vec + 2 * c->Mp, vec, hipMemcpyDeviceToDevice, c->stream));
-  Scalars s0{};   // traces of D_{n0}, as K1's reduction expects them
-  s0.t1 = c->hist_host[(size_t)n0 * GCP_HIST_COLS + 1];
-  s0.t2 = c->hist_host[(size_t)n0 * GCP_HIST_COLS + 2];
-  s0.prev_ddbar = INFINITY;
-  *c->sc_host = s0;
+  // traces of D_{n0}, as K1's reduction expects them
+  *c->sc_host = start_scalars(c->hist_host[(size_t)n0 * GCP_HIST_COLS + 1],
+                              c->hist_host[(size_t)n0 * GCP_HIST_COLS + 2], c->seq);
   HIPCHK(c, hipMemcpyAsync(c->sc, c->sc_host, sizeof(Scalars), hipMemcpyHostToDevice, c->stream));
   int pi = q.pi, k = 0;
   if (n0 == n1) {   // no update applied (p = 0): keep D_{n0} itself
@@ -1135,11 +1133,7 @@ extern "C" int gcp_purify(gcp_ctx *c, void *D, int32_t dtype, int64_t ldd, gcp_r
     std::swap(c->rD[0], c->rD0);
     std::swap(c->d2[0], c->d20);
   };
-  Scalars s0{};
-  s0.t1 = c->t1_0;
-  s0.t2 = c->t2_0;
-  s0.prev_ddbar = INFINITY;
-  *c->sc_host = s0;
+  *c->sc_host = start_scalars(c->t1_0, c->t2_0, c->seq);
   HIPCHK(c, hipMemcpyAsync(c->sc, c->sc_host, sizeof(Scalars), hipMemcpyHostToDevice, c->stream));
 
   const bool keep = c->opt.keep_iterates != 0;

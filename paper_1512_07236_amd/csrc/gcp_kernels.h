@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "gcp_posts.h"
+
 namespace gcp {
 
 // Default fold period of the FP32 tile product, in K stages of 32 values:
@@ -61,23 +63,6 @@ __host__ __device__ inline void update_coef_derivs(int method, double c, double 
     de = r * r;
   }
 }
-
-// Device-resident scalars of one solve (FP64 traces and the decision).
-struct Scalars {
-  double t1, t2, t3, omega, c, step;
-  int32_t status;   // 0 continue, 1 converged, 2 max_iter reached, 3 breakdown,
-                    // 4 stopped at the rounding floor
-  int32_t iter;     // update at which status became non-zero
-  double hstat[4];  // Gershgorin min, max, Tr H
-  double prev_ddbar;   // |Tr(D Dbar)| of the previous iterate (+inf before the first)
-  int32_t on_traces;   // 1: the stop was decided from the update's traces, before
-                       // the square of the last iterate was formed
-  uint32_t seq;        // host copy only: the last reduction posted to it
-};
-
-// What a reduction tells the host: nothing, that it has run (seq), or also the
-// scalars.  A reduction that stops the solve always posts everything.
-enum { POST_NONE = 0, POST_SEQ = 1, POST_ALL = 2 };
 
 struct RedArgs {
   const double *part;
