@@ -190,7 +190,9 @@ typedef struct {
     int32_t gemm_launches; /* number of matrix-product launches that did work: 2p, or
                               2p + 1 when the stop needed the square of D_p */
     int32_t host_syncs;  /* times the loop of gcp_purify let the device run dry to read a
-                            decision (one at its end, and each check of a schedule) */
+                            decision: at its end, after every update with sync_every = 1,
+                            after every sync_every updates in gcp_purify_static, and at
+                            each check of a schedule */
     double gemm_flops;   /* algorithmic flops of those launches (M^3 per product,
                             upper-triangle output; split products not counted) */
     double mfma_flops;   /* flops issued to the matrix cores, counted as whole 128x128

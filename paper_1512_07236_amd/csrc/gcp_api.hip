@@ -1169,7 +1169,10 @@ extern "C" int gcp_purify(gcp_ctx *c, void *D, int32_t dtype, int64_t ldd, gcp_r
   const int ahead = std::min(c->opt.sync_every, 2);
   int n = 0, syncs = 0, unchecked = 0, st = GCP_OK;
   uint32_t done[4] = {};   // reduction of update n's K2, at n % 4
+  bool stopped = false, dry = false;   // dry: nothing was enqueued behind the last wait
   auto check = [&](uint32_t seq) {   // true: the solve has stopped (or st != OK)
+    dry = seq == c->seq;
+    if (dry) ++syncs;
     st = wait_scalars(c, seq, true);
     return st != GCP_OK || c->sc_host->status != 0;
   };
@@ -1177,12 +1180,11 @@ extern "C" int gcp_purify(gcp_ctx *c, void *D, int32_t dtype, int64_t ldd, gcp_r
     (void)hipStreamSynchronize(c->stream);
     return st;
   };
-  for (bool stopped = false; !stopped && n <= max_iter; ++n) {
+  for (; n <= max_iter; ++n) {
     const int k = n & 1;
     const bool per_step = pi + 1 < c->nprec;
     if (c->post ? n >= ahead : unchecked >= c->opt.sync_every) {
       stopped = check(c->post ? done[(n - ahead) & 3] : c->seq);
-      if (!c->post) ++syncs;
       unchecked = 0;
       if (stopped) break;
     }
@@ -1193,8 +1195,8 @@ extern "C" int gcp_purify(gcp_ctx *c, void *D, int32_t dtype, int64_t ldd, gcp_r
     if (direct && n == 0) swap_d0();
     st = step_k1(c, g, pi, k, n, &lg, false, per_step ? POST_ALL : POST_NONE);
     if (st == GCP_OK && per_step) {
-      ++syncs;
-      if (check(c->seq)) break;
+      stopped = check(c->seq);
+      if (stopped) break;
       int to = pi;
       while (to + 1 < c->nprec &&
              std::fabs(c->sc_host->t1 - c->sc_host->t2) <= c->pc[to + 1].enter_ddbar) {
@@ -1209,8 +1211,8 @@ extern "C" int gcp_purify(gcp_ctx *c, void *D, int32_t dtype, int64_t ldd, gcp_r
         st = step_k1(c, g, pi, k, n, &lg, true, POST_ALL);
         if (st != GCP_OK) return fail();
         ++lg.reruns;
-        ++syncs;
-        if (check(c->seq)) break;
+        stopped = check(c->seq);
+        if (stopped) break;
       }
     }
     // the iterate K2 reads, in the encoding it reads it (after a switch)
@@ -1221,9 +1223,9 @@ extern "C" int gcp_purify(gcp_ctx *c, void *D, int32_t dtype, int64_t ldd, gcp_r
     done[n & 3] = c->seq;
     ++unchecked;
   }
-  if (st == GCP_OK && c->sc_host->status == 0) (void)check(c->seq);
+  if (!stopped) (void)check(c->seq);
   if (st != GCP_OK) return fail();
-  ++syncs;
+  if (!dry) ++syncs;   // the stop was seen behind launches that do nothing
   const int status = c->sc_host->status;
   n = c->sc_host->iter;
   const bool at_d0 = direct && n == 0;   // no update applied
