@@ -1170,6 +1170,7 @@ extern "C" int gcp_purify(gcp_ctx *c, void *D, int32_t dtype, int64_t ldd, gcp_r
   int n = 0, syncs = 0, unchecked = 0, st = GCP_OK;
   uint32_t done[4] = {};   // reduction of update n's K2, at n % 4
   bool stopped = false, dry = false;   // dry: nothing was enqueued behind the last wait
+  bool kept = false;   // D_0 is in slot 0
   auto check = [&](uint32_t seq) {   // true: the solve has stopped (or st != OK)
     dry = seq == c->seq;
     if (dry) ++syncs;
@@ -1216,7 +1217,10 @@ extern "C" int gcp_purify(gcp_ctx *c, void *D, int32_t dtype, int64_t ldd, gcp_r
       }
     }
     // the iterate K2 reads, in the encoding it reads it (after a switch)
-    if (st == GCP_OK && keep && !ck) st = store_iterate(c, n, k, prec);
+    if (st == GCP_OK && keep && !ck) {
+      st = store_iterate(c, n, k, prec);
+      kept = true;
+    }
     if (st == GCP_OK) st = step_k2(c, g, pi, k, n, &lg, POST_SEQ);
     if (direct && n == 0) swap_d0();
     if (st != GCP_OK) return fail();
@@ -1226,6 +1230,10 @@ extern "C" int gcp_purify(gcp_ctx *c, void *D, int32_t dtype, int64_t ldd, gcp_r
   if (!stopped) (void)check(c->seq);
   if (st != GCP_OK) return fail();
   if (!dry) ++syncs;   // the stop was seen behind launches that do nothing
+  if (keep && !ck && !kept) {   // a schedule's check has stopped update 0: the guess's adjoint reads D_0
+    st = store_iterate(c, 0, 0, prec);
+    if (st != GCP_OK) return fail();
+  }
   const int status = c->sc_host->status;
   n = c->sc_host->iter;
   const bool at_d0 = direct && n == 0;   // no update applied
