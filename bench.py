@@ -27,6 +27,7 @@ import argparse
 import json
 import math
 import os
+import re
 import sys
 import time
 
@@ -45,13 +46,22 @@ def log(msg: str) -> None:
     print(msg, file=sys.stderr, flush=True)
 
 
+def product_kernel(prec, M: int) -> str:
+    """The product kernel of an encoding at size M, as product_path in
+    gcp_api.hip chooses it (without the ksplit option)."""
+    import paper_1512_07236_amd as gcp
+    if gcp.MFMA_DTYPE[prec] in ("fp16", "bf16") and M > 3008:
+        return "k_gemm16"
+    return "k_small" if M <= (1280 if prec == gcp.Precision.FP64 else 896) else "k_tile"
+
+
 def product_kernel_hash() -> str:
-    """sha256 of the source the 16-bit product kernel is built from: its text
-    in gcp_kernels.hip and the headers it includes from the package."""
+    """sha256 of the source the product kernels are built from: their text in
+    gcp_kernels.hip and the headers it includes from the package."""
     import hashlib
     csrc = os.path.join(ROOT, "paper_1512_07236_amd", "csrc")
     k = open(os.path.join(csrc, "gcp_kernels.hip")).read()
-    a = k.index("// ------------------------------------------------ 16-bit product kernel")
+    a = k.index("namespace gcp {")
     b = k.index("int pair_count(int nt)")
     h = hashlib.sha256(k[a:b].encode())
     for f in ("gcp_encode.h", "gcp_mma.h", "gcp_kernels.h", "gcp_posts.h"):
@@ -173,14 +183,15 @@ def summarize_pmc(precision: str, scale: int, fetch_dir: str, write_dir: str) ->
     import paper_1512_07236_amd as gcp
     prec = gcp.Precision.parse(precision)
     M = 8192 // scale
-    kname = "k_gemm16" if gcp.MFMA_DTYPE[prec] in ("fp16", "bf16") else "k_tile"
+    kname = product_kernel(prec, M)
     tag = f"gemm_{prec.name.lower()}_M{M}"
     out = {"kernel": f"{kname}<{int(prec)}>", "workload": f"M={M}", "precision": prec.name.lower()}
     for name, d in (("FETCH_SIZE", fetch_dir), ("WRITE_SIZE", write_dir)):
         rows = [r for r in _counter_rows(d) if r["Counter_Name"] == name]
         # launches that did work (a solve's launches past its stop do nothing)
         kern = [float(r["Counter_Value"]) for r in rows
-                if f"{kname}<{int(prec)}>" in r["Kernel_Name"] and float(r["Counter_Value"]) > 1024]
+                if re.search(rf"\b{kname}<{int(prec)}[,>]", r["Kernel_Name"])
+                and float(r["Counter_Value"]) > 1024]
         # yardsticks of known size: the global-to-LDS stream for FETCH_SIZE
         # (the product kernel's load type), the plain copy for WRITE_SIZE
         if name == "FETCH_SIZE":
@@ -543,8 +554,7 @@ def main() -> int:
         "other_workloads": extra,
         "roofline": {"bound": "mfma", "achieved": achieved, "peak": peak, "unit": "TFLOP/s",
                      "frac": achieved / peak, "traffic": traffic,
-                     "kernel": (("k_gemm16" if gcp.MFMA_DTYPE[prec] in ("fp16", "bf16") else "k_tile")
-                                + f"<{prec.name}>"),
+                     "kernel": product_kernel(prec, M) + f"<{prec.name}>",
                      "algorithmic_flops_per_launch": flops_product,
                      "launches_per_solve": launches,
                      "ms_per_launch": gemm_ms_avg,
