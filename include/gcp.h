@@ -24,7 +24,7 @@
  *    current when the context was created, owned by the caller.
  *  - Work is enqueued on the stream given to gcp_create (a hipStream_t passed
  *    as void*; NULL = the default stream).  Entry points that must decide on
- *    the host (gcp_init, gcp_purify, gcp_backward) synchronise that stream.
+ *    the host (gcp_init, gcp_purify, gcp_backward) wait for that stream.
  *  - Every function returns a gcp_status; nothing throws across the ABI.
  *    gcp_last_error() gives a text description of the last failure.
  *  - A context is not thread-safe; use one context per stream.
@@ -93,7 +93,11 @@ typedef struct {
                             accumulations per stage), which minimises the accumulated
                             rounding, the dominant error of the split encodings and
                             of FP32 at large M; a value >= the stage count never
-                            folds.  FP64 keeps one accumulator. */
+                            folds.  Where the totals go on into FP64 ones (16-bit
+                            encodings, 896 < M <= 3008, without ksplit) FP16X3 and
+                            BF16X6 fold every second stage at the latest; for M <= 896
+                            (FP64: 1280) the stages are those of one of four waves.
+                            FP64 keeps one accumulator. */
     int32_t profile;     /* 1: time every matrix-product launch with HIP events */
     int32_t keep_iterates; /* 1: gcp_purify keeps D_0 .. D_{p-1} for gcp_backward, one
                               M x M matrix of the adjoint's type per update (default 0) */
@@ -101,8 +105,8 @@ typedef struct {
                               (FP32 MFMA and storage; kappa and the traces stay FP64) */
     int32_t late_precision; /* precision schedule: -1 (default) = none; otherwise the
                                encoding of every product once |Tr(D Dbar)| <= switch_ddbar.
-                               The switch re-encodes D and D^2 (the FP64 diagonal is
-                               kept), so Tr D stays exact.  Rounding already made in the
+                               The switch re-encodes D (the FP64 diagonal is kept, so
+                               Tr D stays exact) and forms D^2 again.  Rounding already made in the
                                occupied-virtual block is not undone by a later, more
                                precise encoding: a late FP64 phase makes the result
                                idempotent to FP64 level and lets it reach tolerances
@@ -273,9 +277,9 @@ int gcp_backward(gcp_ctx *ctx, const void *dL_dD, int64_t ldg, void *dL_dH, int6
  *   idem      ||D^2 - D||_F
  *   energy    Tr(D H) (the sum of the N lowest eigenvalues at the ground state)
  *   comm      ||H D - D H||_F
- * Work: two M^3-class FP64 products (D^2 on upper tiles, H D on all tiles).
- * The first call allocates three M x M FP64 matrices of workspace, kept by
- * the context.  Errors: INVALID_ARG for NULL pointers, ld < M or a bad dtype;
+ * Work: three FP64 products over the upper triangle (D^2, and H D and D H for
+ * the commutator).  The first call allocates two M x M FP64 matrices of
+ * workspace, kept by the context.  Errors: INVALID_ARG for NULL pointers, ld < M or a bad dtype;
  * NO_MEMORY if the workspace cannot be allocated. */
 typedef struct {
     double trace, fro2, idem, energy, comm;

@@ -1,9 +1,10 @@
 // gcp_api.hip -- host side of libgcp: the C ABI declared in include/gcp.h.
 //
 // Owns the device workspace of one solve and drives the iteration: per
-// update two MFMA products (gcp_kernels.hip) and two fixed-order reductions;
-// the host reads five FP64 scalars after each D^2 to decide whether to stop
-// (the paper's test on Tr(D Dbar) is made before c_n is formed).
+// update two MFMA products (gcp_kernels.hip), each with its fixed-order
+// reduction.  The device decides whether to stop (the paper's test on
+// Tr(D Dbar) is made before c_n is formed) and posts the decision to the host,
+// which enqueues at most two updates ahead of it.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -717,8 +718,9 @@ static double rounding_floor(const gcp_ctx *c, int k) {
     default: break;
   }
   const double u_acc = std::ldexp(1.0, prec == GCP_FP64 ? -53 : -24);
-  // one accumulator over K, or chunks of the default (or given) fold period;
-  // a product that is also split along K rounds less often
+  // one accumulator over K, or chunks of the default (or given) fold period
+  // and an FP32 total, of the size rounded up to 256; a product that is also
+  // split along K, or goes on in FP64 (tile_mma), rounds less often
   const double Mn = 128.0 * c->nt_nominal;
   double kappa = Mn + 1.0;
   if (prec == GCP_FP32) {                // stages of 32 K values

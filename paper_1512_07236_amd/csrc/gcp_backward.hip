@@ -19,11 +19,12 @@
 //   k_bpair   D_i G_j and D_j G_i, i.e. both tiles of A = D Gbar' of a mirrored
 //             pair: stores S = A + A^T and T = A^T, and sums <A, D> = <Gbar', D^2>
 //             and <Gbar', D> (both = 1/2 <S, .> by symmetry)
-//   k_bstep   D_i T_j + S_i D_j = D^2 Gbar' + (D Gbar' D + Gbar' D^2), one
-//             accumulator; epilogue: Gbar_n from Gbar', S, D and the product
+//   k_bstep   D_i T_j + S_i D_j = D^2 Gbar' + (D Gbar' D + Gbar' D^2), the two
+//             added in FP64; epilogue: Gbar_n from Gbar', S, D and their sum
 // with S = D Gbar' + Gbar' D.  The term -3 kappa D^2 / (T1 - T2) is linear in
 // a third product D D, which k_badd folds into the first one by adding a
-// multiple of D to T once kappa is known.  That is 4 M^3 flops per step; with
+// multiple of D to T once kappa is known (T is then rounded once more in the
+// adjoint's type).  That is 4 M^3 flops per step; with
 // D^2 formed for itself, D Gbar' and D^2 Gbar' as general products and D
 // Gbar' D it was 6 M^3.  PMCP alone needs D^2: k_bx2 forms its tiles for the
 // sum <Gbar', D^3> = 1/2 <S, D^2> and does not store them.
@@ -54,7 +55,8 @@ template <int P> struct BwdCfg {
   static constexpr int V = T64 * VP * (int)sizeof(S);
   static constexpr int MM = TileCfg<P>::SMEM > V ? TileCfg<P>::SMEM : V;
   static constexpr int SMEM = MM + 8 * 8;    // and two sums per wave
-  static constexpr int BLOCKS = Enc<P>::KIND == 0 ? 4 : 2;   // per CU, as k_tile
+  // per CU, as k_tile; in FP64 k_bpair spills 29 registers and k_bstep 6
+  static constexpr int BLOCKS = Enc<P>::KIND == 0 ? 4 : 2;
 };
 
 // Tile of this block, and for a tile of the last partial round its split: the

@@ -9,7 +9,7 @@
 
 namespace gcp {
 
-// Default fold period of the FP32 tile product, in K stages of 32 values:
+// Fold period of the adjoint's FP32 tile products, in K stages of 32 values:
 // with 8 accumulating MFMA steps per stage and n stages, a chunk accumulator
 // added into a running total every f stages rounds each term about 8f + n/f
 // times; f = sqrt(n / 8) minimises that (one accumulator: 8n).

@@ -3,8 +3,9 @@
 // One purification iteration (eq. (hpcp3) expanded with Dbar = I - D):
 //   D_{n+1} = (1 - 2c) D + (2 + 2c) D^2 - 2 D^3,   c = (T2 - T3) / (T1 - T2),
 //   T_k = Tr D^k.
-// It is two symmetric matrix products, each an MFMA GEMM over the upper
-// triangle of 128 x 128 output tiles (results mirrored):
+// It is two symmetric matrix products over the upper triangle of output tiles
+// (results mirrored), 32 x 32 (k_small), 64 x 64 (k_tile) or, for 16-bit
+// encodings above M = 3008, pairs of 128 x 128 (k_gemm16):
 //   K1 (mode 0):  X2 = D D        epilogue: store X2, row sums of X2 o D
 //                                 (diag of D^3) and ||X2 - D||_F^2
 //   K2 (mode 1):  X3 = X2 D       epilogue: D_{n+1} from D, X2 and X3 (X3 never
@@ -12,8 +13,9 @@
 //                                 of D_{n+1}^2) and ||D_{n+1} - D_n||_F^2
 // Both are A * B^T products of row panels (all iterates are symmetric), so
 // both operands are read along contiguous K.  Row sums go to a [slot][row]
-// FP64 buffer (one writer per slot) and a reduction kernel adds them in a
-// fixed order: every trace, and therefore c_n, is bitwise reproducible.
+// FP64 buffer (one writer per slot).  The last block of a tile kernel, or
+// k_reduce after pairs, adds them in a fixed order and runs the scalar step:
+// every trace, and therefore c_n, is bitwise reproducible.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -453,7 +455,8 @@ template <int P> struct TileKernel {
   static constexpr int VS = T64 * VP * (int)sizeof(typename C::S);
   static constexpr int MM = C::SMEM > VS ? C::SMEM : VS;
   static constexpr int SMEM = FinCfg<P, T64>::SMEM > MM ? FinCfg<P, T64>::SMEM : MM;
-  static constexpr int BLOCKS = C::KIND == 0 ? 4 : C::KIND == 1 ? 2 : 3;   // per CU
+  // per CU; at four, FP64 has 128 registers and its epilogue spills 26
+  static constexpr int BLOCKS = C::KIND == 0 ? 4 : C::KIND == 1 ? 2 : 3;
 };
 
 template <int P>
